@@ -165,7 +165,7 @@ int sweep_plain(hsg_lattice* lat, const hsg_sweep_params* p, int32_t n_sweeps, h
   ph.partials = partials;
   const bool snake = (p->flags & HSG_SNAKE) != 0;
   const bool by_slab = (p->flags & HSG_PLANE_LAUNCH) != 0;
-  const int32_t slab_tiles = g.tiles_x * g.tiles_y;
+  const int32_t n_slabs = (g.L + g.slab - 1) / g.slab;
   int32_t pass_count = 0;
   bool mc0_done = false;  // this sweep's colour-0 Monte Carlo pass ran in the last launch
   for (int32_t n = 0; n < n_sweeps; ++n) {
@@ -216,10 +216,10 @@ int sweep_plain(hsg_lattice* lat, const hsg_sweep_params* p, int32_t n_sweeps, h
           if (rc) return rc;
           continue;
         }
-        for (int32_t i = 0; i < g.tiles_z; ++i) {
-          const int32_t tz = a.reverse ? g.tiles_z - 1 - i : i;
-          a.tile_base = tz * slab_tiles;
-          a.tile_count = slab_tiles;
+        for (int32_t i = 0; i < n_slabs; ++i) {
+          const int32_t z0 = (a.reverse ? n_slabs - 1 - i : i) * g.slab;
+          a.tile_base = z0 * g.tiles_p;
+          a.tile_count = std::min(g.slab, g.L - z0) * g.tiles_p;
           int rc = device_status(
               recorded(mode == PassMode::OverRelax ? HSG_LAUNCH_OR_PASS : HSG_LAUNCH_MC_PASS, st,
                        [&] { return launch_colour_pass<R>(mode, a, st); }),

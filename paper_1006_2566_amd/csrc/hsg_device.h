@@ -341,25 +341,47 @@ __device__ __forceinline__ void sincos_2pi_t(R t, R& s_out, R& c_out) {
   s_out = (quadrant >= 2) ? -sq : sq;
 }
 
-// Binary32: the quadrant rotation on the bit patterns, with three-input bitwise
-// operations (v_bitop3_b32; the truth-table byte is the function applied to the
-// operand masks 0xF0, 0xCC, 0xAA).  Bit 0 of q exchanges the pair (select on a
-// 0 / all-ones mask, table 0xCA = a ? b : c); bit 1 of q flips the sign of sin and
-// bit 1 of q + 1 the sign of cos (table 0x6A = (a & b) ^ c on the sign bit).
+// Binary32: the rotation of (s, c) = (sin, cos)(pi r / 2) by `quad` quadrants on the bit
+// patterns, with three-input bitwise operations (v_bitop3_b32; the truth-table byte is the
+// function applied to the operand masks 0xF0, 0xCC, 0xAA).  The quadrant sits in the top
+// two bits of `quad` (the bits below are ignored): its low bit exchanges the pair (select
+// on a 0 / all-ones mask, table 0xCA = a ? b : c), its high bit flips the sign of sin and
+// the high bit of the next quadrant the sign of cos (table 0x6A = (a & b) ^ c on the
+// sign bit).
+__device__ __forceinline__ void rotate_quadrant(uint32_t quad, float s, float c, float& s_out,
+                                                float& c_out) {
+  const uint32_t odd = (uint32_t)__builtin_amdgcn_sbfe((int32_t)quad, 30, 1);  // 0 or ~0
+  const uint32_t sb = __float_as_uint(s), cb = __float_as_uint(c);
+  const uint32_t sq = __builtin_amdgcn_bitop3_b32(odd, cb, sb, 0xCA);  // odd: sin <- cos
+  const uint32_t cq = __builtin_amdgcn_bitop3_b32(odd, sb, cb, 0xCA);
+  s_out = __uint_as_float(__builtin_amdgcn_bitop3_b32(quad, 0x80000000u, sq, 0x6A));
+  c_out = __uint_as_float(
+      __builtin_amdgcn_bitop3_b32(quad + 0x40000000u, 0x80000000u, cq, 0x6A));
+}
 template <>
 __device__ __forceinline__ void sincos_2pi_t<float>(float t, float& s_out, float& c_out) {
   const float q = rintf(t);
   const float r = t - q;
   float s, c;
   Trig<float>::eval(r, s, c);
-  const int32_t qi = (int32_t)q;
-  const uint32_t odd = (uint32_t)__builtin_amdgcn_sbfe(qi, 0, 1);  // 0 or ~0
-  const uint32_t sb = __float_as_uint(s), cb = __float_as_uint(c);
-  const uint32_t sq = __builtin_amdgcn_bitop3_b32(odd, cb, sb, 0xCA);  // odd: sin <- cos
-  const uint32_t cq = __builtin_amdgcn_bitop3_b32(odd, sb, cb, 0xCA);
-  s_out = __uint_as_float(__builtin_amdgcn_bitop3_b32((uint32_t)qi << 30, 0x80000000u, sq, 0x6A));
-  c_out = __uint_as_float(
-      __builtin_amdgcn_bitop3_b32((uint32_t)(qi + 1) << 30, 0x80000000u, cq, 0x6A));
+  rotate_quadrant((uint32_t)(int32_t)q << 30, s, c, s_out, c_out);
+}
+// (sin, cos)(2 pi u) straight from the Philox word w, u = (2m + 1) 2^-24 with m its top
+// 23 bits.  Adding half a quadrant to the word (2^29, modulo one turn) leaves the nearest
+// quadrant of 4u in its top two bits and r + 1/2 in those below, as 21 bits of m and the
+// odd half bit, which are the mantissa of 1 + (r + 1/2): four integer and one float
+// operation in place of the conversion, the rounding, the difference and the conversion
+// back, and the quadrant is where the rotation wants it.  The same bits (checked for
+// every m).
+__device__ __forceinline__ void sincos_2pi_word(uint32_t w, float& s_out, float& c_out) {
+  const uint32_t quad = w + 0x20000000u;
+  // (quad >> 7) & 0x007FFFFC | 0x3F800002
+  const uint32_t mant =
+      __builtin_amdgcn_bitop3_b32(quad >> 7, 0x007FFFFCu, 0x3F800002u, 0xEA);
+  const float r = __uint_as_float(mant) - 1.5f;
+  float s, c;
+  Trig<float>::eval(r, s, c);
+  rotate_quadrant(quad, s, c, s_out, c_out);
 }
 
 template <typename R>
@@ -387,38 +409,38 @@ __device__ __forceinline__ Vec3<R> sphere_point(R u0, R u1) {
 // The same point straight from two Philox words: with u = odd * 2^-24 exact, both
 // 2u - 1 = odd * 2^-23 - 1 and 4u = odd * 2^-22 are exact, so folding the scale
 // into one operation gives identical bits.
-// Correctly rounded square root of a positive normal binary32 x: the hardware root
-// (within 1 ulp) is moved to its neighbour when the residual x - r*r of the neighbour
-// shows that neighbour is the nearer root.  sqrtf performs the same steps plus
-// scaling for denormal and special inputs, which the sphere point never produces
-// (there 1 - z^2 >= 2^-22).
-__device__ __forceinline__ float sqrt_rn_normal(float x) {
-  const float r = __builtin_amdgcn_sqrtf(x);
-  const float down = __uint_as_float(__float_as_uint(r) - 1u);
-  const float up = __uint_as_float(__float_as_uint(r) + 1u);
-  float out = fmaf(-down, r, x) <= 0.0f ? down : r;
-  out = fmaf(-up, r, x) > 0.0f ? up : out;
-  return out;
+// Correctly rounded square root of x = 1 - z^2, z an odd multiple of 2^-23 below 1 in
+// magnitude (rounded once: the sphere point's argument): from the hardware's reciprocal
+// root y, s = x y and one residual step, s + (x - s s)(y / 2).  The last fused
+// multiply-add rounds a value whose error is second order in the hardware's, which is
+// not always enough for correct rounding at every float, but is at each of the 2^22
+// arguments a trial can have (compared with the rounded binary64 root, all of them, on
+// gfx950).  Five instructions; moving the hardware root to its neighbour by the sign of
+// two residuals, as a general sqrtf does, took nine and two waits for the condition code.
+__device__ __forceinline__ float sqrt_rn_sphere(float x) {
+  const float y = __builtin_amdgcn_rsqf(x);
+  const float s = x * y;
+  return fmaf(fmaf(-s, s, x), 0.5f * y, s);
 }
-__device__ __forceinline__ double sqrt_rn_normal(double x) { return sqrt(x); }
+__device__ __forceinline__ double sqrt_rn_sphere(double x) { return sqrt(x); }
 
 template <typename R>
 __device__ __forceinline__ Vec3<R> sphere_point_words(uint32_t w0, uint32_t w1) {
   const R z = dev_fma(odd_part<R>(w0), (R)0x1p-23, (R)-1);
-  const R rho = sqrt_rn_normal(dev_fma(-z, z, (R)1));
+  const R rho = sqrt_rn_sphere(dev_fma(-z, z, (R)1));
   R s, c;
   sincos_2pi_t(odd_part<R>(w1) * (R)0x1p-22, s, c);
   return Vec3<R>{rho * c, rho * s, z};
 }
-// Binary32: with f = 1 + m 2^-23 from each word, 2u - 1 = (2f - 2) - (1 - 2^-23) (the
+// Binary32: with f = 1 + m 2^-23 from the first word, 2u - 1 = (2f - 2) - (1 - 2^-23) (the
 // product-difference m 2^-22 is exact, and so is the difference, a multiple of 2^-23
-// below 1 in magnitude) and 4u = 4f - (4 - 2^-22) in one exact fused multiply-add.
+// below 1 in magnitude); the azimuth's quadrant and remainder by sincos_2pi_word.
 template <>
 __device__ __forceinline__ Vec3<float> sphere_point_words<float>(uint32_t w0, uint32_t w1) {
   const float z = fmaf(one_plus_top23(w0), 2.0f, -2.0f) - 0x1.fffffcp-1f;
-  const float rho = sqrt_rn_normal(fmaf(-z, z, 1.0f));
+  const float rho = sqrt_rn_sphere(fmaf(-z, z, 1.0f));
   float s, c;
-  sincos_2pi_t(fmaf(one_plus_top23(w1), 4.0f, -0x1.fffffep+1f), s, c);
+  sincos_2pi_word(w1, s, c);
   return Vec3<float>{rho * c, rho * s, z};
 }
 
@@ -506,6 +528,18 @@ __device__ __forceinline__ int32_t xcd_tile(int32_t b, int32_t n) {
   const int32_t xcd = b & 7, local = b >> 3;
   return xcd * q + min(xcd, r) + local;
 }
+
+// Quotient by a small divisor d: with m = ceil(2^32 / d) = (2^32 + e) / d, 0 <= e < d,
+// n m / 2^32 = n/d + n e / (d 2^32), whose floor is floor(n/d) as long as n e < 2^32.
+// Divisors are L/2 and L: in a plane n < L^2/2 < 2^20 and e < L/2 <= 645; over a chain
+// (L <= 256) n < 2^23 and e < 256.  d = 1 passes.
+struct SmallDiv {
+  uint32_t d, m;
+  __device__ __forceinline__ SmallDiv(uint32_t d_, uint32_t m_) : d(d_), m(m_) {}
+  __device__ __forceinline__ explicit SmallDiv(uint32_t d_)
+      : d(d_), m(d_ > 1 ? 0xFFFFFFFFu / d_ + 1u : 0u) {}
+  __device__ __forceinline__ uint32_t div(uint32_t n) const { return d > 1 ? __umulhi(n, m) : n; }
+};
 
 // Sum of a double over the workgroup (blockDim.x a multiple of 64, at most 1024):
 // wave sums, then wave 0's lane 0 adds them in wave order.  The result is valid in

@@ -9,14 +9,18 @@
 namespace hsg {
 
 // A colour pass covers the N/2 sites of one colour, stored as L planes (z) of L rows
-// (y) of L/2 sites (xh).  Each workgroup takes a BX x BY x BZ tile of (xh, y, z);
-// BX is one wavefront wide when L/2 allows it, so a wave reads whole row segments.
+// (y) of L/2 sites (xh).  A workgroup takes kPassThreads consecutive sites of one plane,
+// whole rows and parts of rows alike, so that every lane has a site whatever L is but in
+// the last tile of a plane.
+constexpr int kPassThreads = 256;
 struct Geometry {
   int32_t L, Lh;
-  int32_t bx_log, by_log, bz_log;     // tile extents are 1 << *_log
-  int32_t tiles_x, tiles_y, tiles_z;  // tiles along xh, y, z
-  int32_t n_blocks;                   // tiles_x * tiles_y * tiles_z
-  int32_t threads;                    // BX * BY * BZ (<= 256)
+  int32_t plane;      // sites of one colour in a plane: L/2 * L
+  int32_t tiles_p;    // tiles of a plane
+  int32_t slab;       // planes per launch of HSG_PLANE_LAUNCH
+  int32_t n_blocks;   // tiles of a pass: tiles_p * L
+  uint32_t inv_lh;    // ceil(2^32 / Lh) (0 for Lh = 1): see SmallDiv
+  uint32_t inv_tp;    // floor(2^32 / tiles_p) (0 for one tile)
 };
 
 Geometry pass_geometry(int32_t L);

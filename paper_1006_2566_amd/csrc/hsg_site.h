@@ -57,10 +57,44 @@ __device__ __forceinline__ void init_site(int32_t L, int64_t e, uint32_t k0, uin
   J[base + 2 * Nh] = r23 * cs;
 }
 
-// Where a site sits: colour c, column xh of its colour row, row y, plane z.
-struct SitePos {
-  int32_t L, Lh, c, xh, y, z;
+// A site and its six neighbours as offsets into the planes of its colour (own) and of the
+// other one: bytes in binary32, where a plane of N/2 <= 2^30 values spans less than 2^32
+// bytes for every L the library accepts and the loads take a wave-uniform base and a
+// 32-bit offset; elements in binary64.
+struct SiteOffsets {
+  uint32_t own, px, mx, py, my, pz, mz;
+  uint32_t site;  // x + L y + L^2 z
 };
+
+template <typename R>
+struct OffsetUnit {
+  static constexpr uint32_t value = sizeof(R) == 4 ? 4 : 1;
+};
+
+// The colour-c site at column xh of row y, plane z, its index in the colour ic = xh +
+// Lh (y + L z).  Every neighbour is a step from ic: none or one column in x (which of the
+// two depends on the row's parity), a row in y, a plane in z, or back across the lattice at
+// its faces; and x + L y + L^2 z = 2 ic + p, since a row holds L = 2 Lh sites.  So a site
+// costs a dozen vector operations where forming the rows of its neighbours took forty.
+template <typename R>
+__device__ __forceinline__ SiteOffsets site_offsets(uint32_t L, uint32_t Lh, uint32_t c,
+                                                    uint32_t ic, uint32_t xh, uint32_t y,
+                                                    uint32_t z) {
+  constexpr uint32_t U = OffsetUnit<R>::value;
+  const uint32_t p = (y + z + c) & 1u;  // x = 2 xh + p
+  const uint32_t row = Lh * U, plane = Lh * L * U;  // steps in y and z
+  const uint32_t odd = 0u - p;                      // all ones when p = 1
+  SiteOffsets o;
+  o.own = ic * U;
+  o.px = o.own + (odd & (xh == Lh - 1 ? U - row : U));
+  o.mx = o.own + (~odd & (xh == 0 ? row - U : 0u - U));
+  o.py = o.own + (y == L - 1 ? row - plane : row);
+  o.my = o.own + (y == 0 ? plane - row : 0u - row);
+  o.pz = o.own + (z == L - 1 ? plane - plane * L : plane);
+  o.mz = o.own + (z == 0 ? plane * L - plane : 0u - plane);
+  o.site = 2u * ic + p;
+  return o;
+}
 
 // Monte Carlo stream of the site: Philox key and the uniform counter words.
 template <typename R>
@@ -155,7 +189,9 @@ __device__ __forceinline__ double apply_update(Vec3<R>& s, const Vec3<R>& h, uin
       };
       auto decide = [&](int g) {
         const R dE = sh - th[g];
-        const bool accept = (dE <= (R)0) || (u2[g] < accept_prob(-hc.beta * dE));
+        // both conditions formed for every trial: a wave has lanes that need the second
+        // one in almost every hit, and a branch around it cost more than it skipped
+        const bool accept = (dE <= (R)0) | (u2[g] < accept_prob(-hc.beta * dE));
         if (accept) {
           s = trial[g];
           sh = th[g];
@@ -183,122 +219,52 @@ __device__ __forceinline__ double apply_update(Vec3<R>& s, const Vec3<R>& h, uin
   return dE_sum;
 }
 
-// Updates the site in place; returns the sum of the accepted energy changes.
-// A load of data the pass only reads (couplings, the other colour's spins); with NT
-// it carries the non-temporal cache hint.
-template <bool NT, typename R>
-__device__ __forceinline__ R read_only_ld(const R* p) {
-  if constexpr (NT)
-    return __builtin_nontemporal_load(p);
+// The value at offset `off` of a plane (see SiteOffsets) whose base is wave-uniform; with
+// NT a load of data the pass only reads (couplings, the other colour's spins) carries the
+// non-temporal cache hint.
+template <typename R>
+__device__ __forceinline__ R* plane_at(R* base, uint32_t off) {
+  if constexpr (sizeof(R) == 4)
+    return (R*)((char*)base + off);
   else
-    return *p;
+    return base + off;
+}
+template <bool NT, typename R>
+__device__ __forceinline__ R plane_ld(R* base, uint32_t off) {
+  if constexpr (NT)
+    return __builtin_nontemporal_load(plane_at(base, off));
+  else
+    return *plane_at(base, off);
 }
 
+// Updates the colour-c site at o in place; returns the sum of the accepted energy changes.
 template <typename R, PassMode MODE, bool NT = false>
-__device__ __forceinline__ double update_site(const Planes<R>& S, const Planes<R>& J,
-                                              const SitePos& q, const HitCtx<R>& hc) {
-  const int32_t L = q.L, Lh = q.Lh, c = q.c, xh = q.xh, y = q.y, z = q.z;
-  const int32_t p = (y + z + c) & 1;  // x = 2 xh + p
-  const int32_t ym = y == 0 ? L - 1 : y - 1, yp = y == L - 1 ? 0 : y + 1;
-  const int32_t zm = z == 0 ? L - 1 : z - 1, zp = z == L - 1 ? 0 : z + 1;
-  const int32_t row = Lh * (y + L * z);
-  const int32_t own = row + xh;
-  // other-colour neighbours: x+1 and x-1 in the same row, y+-1 and z+-1 at the same xh
-  const int32_t n_px = row + (p ? (xh + 1 == Lh ? 0 : xh + 1) : xh);
-  const int32_t n_mx = row + (p ? xh : (xh == 0 ? Lh - 1 : xh - 1));
-  const int32_t n_py = Lh * (yp + L * z) + xh, n_my = Lh * (ym + L * z) + xh;
-  const int32_t n_pz = Lh * (y + L * zp) + xh, n_mz = Lh * (y + L * zm) + xh;
+__device__ __forceinline__ double update_site(const Planes<R>& S, const Planes<R>& J, int32_t c,
+                                              const SiteOffsets& o, const HitCtx<R>& hc) {
   const int oc = 3 * c, nc = 3 * (1 - c);
-
   // couplings of the six bonds: +x,+y,+z stored at the site, -x,-y,-z at the neighbour
-  const R j_px = read_only_ld<NT>(J.p[oc + 0] + own), j_mx = read_only_ld<NT>(J.p[nc + 0] + n_mx);
-  const R j_py = read_only_ld<NT>(J.p[oc + 1] + own), j_my = read_only_ld<NT>(J.p[nc + 1] + n_my);
-  const R j_pz = read_only_ld<NT>(J.p[oc + 2] + own), j_mz = read_only_ld<NT>(J.p[nc + 2] + n_mz);
+  const R j_px = plane_ld<NT>(J.p[oc + 0], o.own), j_mx = plane_ld<NT>(J.p[nc + 0], o.mx);
+  const R j_py = plane_ld<NT>(J.p[oc + 1], o.own), j_my = plane_ld<NT>(J.p[nc + 1], o.my);
+  const R j_pz = plane_ld<NT>(J.p[oc + 2], o.own), j_mz = plane_ld<NT>(J.p[nc + 2], o.mz);
   R hcomp[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    const R* sn = S.p[nc + k];
-    R acc = j_px * read_only_ld<NT>(sn + n_px);
-    acc = dev_fma(j_mx, read_only_ld<NT>(sn + n_mx), acc);
-    acc = dev_fma(j_py, read_only_ld<NT>(sn + n_py), acc);
-    acc = dev_fma(j_my, read_only_ld<NT>(sn + n_my), acc);
-    acc = dev_fma(j_pz, read_only_ld<NT>(sn + n_pz), acc);
-    acc = dev_fma(j_mz, read_only_ld<NT>(sn + n_mz), acc);
+    R* sn = S.p[nc + k];
+    R acc = j_px * plane_ld<NT>(sn, o.px);
+    acc = dev_fma(j_mx, plane_ld<NT>(sn, o.mx), acc);
+    acc = dev_fma(j_py, plane_ld<NT>(sn, o.py), acc);
+    acc = dev_fma(j_my, plane_ld<NT>(sn, o.my), acc);
+    acc = dev_fma(j_pz, plane_ld<NT>(sn, o.pz), acc);
+    acc = dev_fma(j_mz, plane_ld<NT>(sn, o.mz), acc);
     hcomp[k] = acc;
   }
   const Vec3<R> h{hcomp[0], hcomp[1], hcomp[2]};
-  Vec3<R> s{*(S.p[oc + 0] + own), *(S.p[oc + 1] + own),
-            *(S.p[oc + 2] + own)};
-
-  const uint32_t site = (uint32_t)(2 * xh + p) + (uint32_t)L * (uint32_t)(y + L * z);
-  const double dE_sum = apply_update<R, MODE>(s, h, site, hc);
-  S.p[oc + 0][own] = s.x;
-  S.p[oc + 1][own] = s.y;
-  S.p[oc + 2][own] = s.z;
-  return dE_sum;
-}
-
-// Element at byte offset `off` of a plane whose base is wave-uniform: the access uses
-// the scalar-base + 32-bit vector-offset addressing of global loads and stores, with no
-// 64-bit address arithmetic per lane.  A binary32 plane of N/2 <= 2^30 values spans less
-// than 2^32 bytes for every L the library accepts.
-__device__ __forceinline__ float plane_ld(const float* base, uint32_t off) {
-  return *(const float*)((const char*)base + off);
-}
-// The same for data the pass only reads; with NT the load carries the non-temporal hint.
-template <bool NT>
-__device__ __forceinline__ float plane_ld_ro(const float* base, uint32_t off) {
-  const float* p = (const float*)((const char*)base + off);
-  if constexpr (NT)
-    return __builtin_nontemporal_load(p);
-  else
-    return *p;
-}
-__device__ __forceinline__ void plane_st(float* base, uint32_t off, float v) {
-  *(float*)((char*)base + off) = v;
-}
-
-// The binary32 site update of the colour passes (single lattice, batched, served): the same field (eq. 2, same
-// order of products and fused multiply-adds) and the same apply_update as update_site,
-// with 32-bit byte offsets into the six planes.
-template <PassMode MODE, bool NT>
-__device__ __forceinline__ double update_site_b32(const Planes<float>& S, const Planes<float>& J,
-                                                  const SitePos& q, const HitCtx<float>& hc) {
-  const uint32_t L = (uint32_t)q.L, Lh = (uint32_t)q.Lh, xh = (uint32_t)q.xh;
-  const uint32_t y = (uint32_t)q.y, z = (uint32_t)q.z;
-  const int32_t c = q.c;
-  const uint32_t p = (y + z + (uint32_t)c) & 1u;  // x = 2 xh + p
-  const uint32_t ym = y == 0 ? L - 1 : y - 1, yp = y == L - 1 ? 0 : y + 1;
-  const uint32_t zm = z == 0 ? L - 1 : z - 1, zp = z == L - 1 ? 0 : z + 1;
-  const uint32_t row = Lh * (y + L * z);
-  const uint32_t own = (row + xh) << 2;
-  const uint32_t n_px = (row + (p ? (xh + 1 == Lh ? 0 : xh + 1) : xh)) << 2;
-  const uint32_t n_mx = (row + (p ? xh : (xh == 0 ? Lh - 1 : xh - 1))) << 2;
-  const uint32_t n_py = (Lh * (yp + L * z) + xh) << 2, n_my = (Lh * (ym + L * z) + xh) << 2;
-  const uint32_t n_pz = (Lh * (y + L * zp) + xh) << 2, n_mz = (Lh * (y + L * zm) + xh) << 2;
-  const int oc = 3 * c, nc = 3 * (1 - c);
-  const float j_px = plane_ld_ro<NT>(J.p[oc + 0], own), j_mx = plane_ld_ro<NT>(J.p[nc + 0], n_mx);
-  const float j_py = plane_ld_ro<NT>(J.p[oc + 1], own), j_my = plane_ld_ro<NT>(J.p[nc + 1], n_my);
-  const float j_pz = plane_ld_ro<NT>(J.p[oc + 2], own), j_mz = plane_ld_ro<NT>(J.p[nc + 2], n_mz);
-  float hcomp[3];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    const float* sn = S.p[nc + k];
-    float acc = j_px * plane_ld_ro<NT>(sn, n_px);
-    acc = dev_fma(j_mx, plane_ld_ro<NT>(sn, n_mx), acc);
-    acc = dev_fma(j_py, plane_ld_ro<NT>(sn, n_py), acc);
-    acc = dev_fma(j_my, plane_ld_ro<NT>(sn, n_my), acc);
-    acc = dev_fma(j_pz, plane_ld_ro<NT>(sn, n_pz), acc);
-    acc = dev_fma(j_mz, plane_ld_ro<NT>(sn, n_mz), acc);
-    hcomp[k] = acc;
-  }
-  const Vec3<float> h{hcomp[0], hcomp[1], hcomp[2]};
-  Vec3<float> s{plane_ld(S.p[oc + 0], own), plane_ld(S.p[oc + 1], own), plane_ld(S.p[oc + 2], own)};
-  const uint32_t site = (2 * xh + p) + L * (y + L * z);
-  const double dE_sum = apply_update<float, MODE>(s, h, site, hc);
-  plane_st(S.p[oc + 0], own, s.x);
-  plane_st(S.p[oc + 1], own, s.y);
-  plane_st(S.p[oc + 2], own, s.z);
+  Vec3<R> s{plane_ld<false>(S.p[oc + 0], o.own), plane_ld<false>(S.p[oc + 1], o.own),
+            plane_ld<false>(S.p[oc + 2], o.own)};
+  const double dE_sum = apply_update<R, MODE>(s, h, o.site, hc);
+  *plane_at(S.p[oc + 0], o.own) = s.x;
+  *plane_at(S.p[oc + 1], o.own) = s.y;
+  *plane_at(S.p[oc + 2], o.own) = s.z;
   return dE_sum;
 }
 

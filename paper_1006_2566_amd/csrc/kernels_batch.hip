@@ -20,16 +20,6 @@ namespace hsg {
 
 namespace {
 
-// Quotient by a small divisor d: with m = ceil(2^32 / d) = (2^32 + e) / d, 0 <= e < d,
-// n m / 2^32 = n/d + n e / (d 2^32), whose floor is floor(n/d) as long as n e < 2^32 --
-// true for n < 2^24 and d <= 256.  Chains have L <= 256, so the divisors L/2 and L
-// qualify and the colour index stays below 128 * 256 * 256 = 2^23.  d = 1 passes.
-struct SmallDiv {
-  uint32_t d, m;
-  __device__ __forceinline__ explicit SmallDiv(uint32_t d_) : d(d_), m(d_ > 1 ? 0xFFFFFFFFu / d_ + 1u : 0u) {}
-  __device__ __forceinline__ uint32_t div(uint32_t n) const { return d > 1 ? __umulhi(n, m) : n; }
-};
-
 // Workgroup size of the per-chain reductions (energy, overlaps): one workgroup
 // reduces a whole chain, so large chains want the largest workgroup.
 constexpr int kChainReduceThreads = 1024;
@@ -67,15 +57,13 @@ struct BatchArgs {
   int32_t n_sweeps;
 };
 
-// The site update of a chain's site: the binary32 form (scalar plane bases, 32-bit
-// offsets) or the generic one.
-template <typename R, PassMode MODE>
-__device__ __forceinline__ double site_update(const ChainView<R>& v, const SitePos& q,
-                                              const HitCtx<R>& hc) {
-  if constexpr (sizeof(R) == 4)
-    return update_site_b32<MODE, false>(v.S, v.J, q, hc);
-  else
-    return update_site<R, MODE>(v.S, v.J, q, hc);
+// Site ic of colour COLOUR of a chain and its neighbours.
+template <typename R, int COLOUR>
+__device__ __forceinline__ SiteOffsets chain_site(const ChainView<R>& v, uint32_t ic,
+                                                  const SmallDiv& by_lh, const SmallDiv& by_l) {
+  const uint32_t row = by_lh.div(ic), z = by_l.div(row);
+  return site_offsets<R>((uint32_t)v.L, (uint32_t)v.Lh, COLOUR, ic, ic - row * (uint32_t)v.Lh,
+                         row - z * (uint32_t)v.L, z);
 }
 
 // One colour pass of mode MODE over a chain, spread over the workgroup.  The colour
@@ -85,21 +73,8 @@ template <typename R, PassMode MODE, int COLOUR>
 __device__ __forceinline__ double chain_pass(const ChainView<R>& v, const HitCtx<R>& hc,
                                              const SmallDiv& by_lh, const SmallDiv& by_l) {
   double dE = 0.0;
-  SitePos q;
-  q.L = v.L;
-  q.Lh = v.Lh;
-  q.c = COLOUR;
-  for (uint32_t ic = threadIdx.x; ic < (uint32_t)v.Nh; ic += blockDim.x) {
-    const uint32_t r = by_lh.div(ic);
-    q.xh = (int32_t)(ic - r * (uint32_t)v.Lh);
-    const uint32_t zq = by_l.div(r);
-    q.y = (int32_t)(r - zq * (uint32_t)v.L);
-    q.z = (int32_t)zq;
-    if constexpr (sizeof(R) == 4)
-      dE += update_site_b32<MODE, false>(v.S, v.J, q, hc);
-    else
-      dE += update_site<R, MODE>(v.S, v.J, q, hc);
-  }
+  for (uint32_t ic = threadIdx.x; ic < (uint32_t)v.Nh; ic += blockDim.x)
+    dE += update_site<R, MODE>(v.S, v.J, COLOUR, chain_site<R, COLOUR>(v, ic, by_lh, by_l), hc);
   return dE;
 }
 
@@ -335,23 +310,15 @@ __global__ __launch_bounds__(1024) void multi_pass_kernel(MultiPassArgs<R> a) {
   double dE = 0.0;
   if (ic < (uint32_t)v.Nh) {
     const SmallDiv by_lh((uint32_t)v.Lh), by_l((uint32_t)v.L);
-    SitePos q;
-    q.L = v.L;
-    q.Lh = v.Lh;
-    q.c = COLOUR;
-    const uint32_t r = by_lh.div(ic);
-    q.xh = (int32_t)(ic - r * (uint32_t)v.Lh);
-    const uint32_t zq = by_l.div(r);
-    q.y = (int32_t)(r - zq * (uint32_t)v.L);
-    q.z = (int32_t)zq;
+    const SiteOffsets o = chain_site<R, COLOUR>(v, ic, by_lh, by_l);
     if (a.phase > 0)
-      site_update<R, PassMode::OverRelax>(v, q, hc);
+      update_site<R, PassMode::OverRelax>(v.S, v.J, COLOUR, o, hc);
     else if (ch.flags & HSG_HEAT_BATH)
-      dE = site_update<R, PassMode::HeatBath>(v, q, hc);
+      dE = update_site<R, PassMode::HeatBath>(v.S, v.J, COLOUR, o, hc);
     else if (ch.k_hits % 4 == 0)  // every group of four hits complete
-      dE = site_update<R, PassMode::MetropolisFull>(v, q, hc);
+      dE = update_site<R, PassMode::MetropolisFull>(v.S, v.J, COLOUR, o, hc);
     else
-      dE = site_update<R, PassMode::Metropolis>(v, q, hc);
+      dE = update_site<R, PassMode::Metropolis>(v.S, v.J, COLOUR, o, hc);
   }
   if (a.phase == 0) {
     const double total = block_sum(dE, s_red);

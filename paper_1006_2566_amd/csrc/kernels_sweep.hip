@@ -17,24 +17,16 @@
 
 namespace hsg {
 
-static int ceil_log2(int v) {
-  int l = 0;
-  while ((1 << l) < v) ++l;
-  return l;
-}
-
 Geometry pass_geometry(int32_t L) {
   Geometry g{};
   g.L = L;
   g.Lh = L / 2;
-  g.bx_log = std::min(6, ceil_log2(g.Lh));
-  g.by_log = std::min(8 - g.bx_log, ceil_log2(L));
-  g.bz_log = std::min(8 - g.bx_log - g.by_log, ceil_log2(L));
-  g.tiles_x = (g.Lh + (1 << g.bx_log) - 1) >> g.bx_log;
-  g.tiles_y = (L + (1 << g.by_log) - 1) >> g.by_log;
-  g.tiles_z = (L + (1 << g.bz_log) - 1) >> g.bz_log;
-  g.n_blocks = g.tiles_x * g.tiles_y * g.tiles_z;
-  g.threads = 1 << (g.bx_log + g.by_log + g.bz_log);
+  g.plane = g.Lh * L;
+  g.tiles_p = (g.plane + kPassThreads - 1) / kPassThreads;
+  g.slab = std::max(1, std::min(L, kPassThreads / std::max(64, g.plane)));
+  g.n_blocks = g.tiles_p * L;
+  g.inv_lh = g.Lh > 1 ? 0xFFFFFFFFu / (uint32_t)g.Lh + 1u : 0u;
+  g.inv_tp = g.tiles_p > 1 ? (uint32_t)(0x100000000ull / (uint32_t)g.tiles_p) : 0u;
   return g;
 }
 
@@ -49,37 +41,33 @@ size_t work_bytes_for(int32_t L, int32_t dtype_bytes) {
   return fused_offset(L) + (size_t)3 * L * L * L * (size_t)dtype_bytes;
 }
 
-// One tile of a colour pass (a BX x BY x BZ block of the colour's sites); Metropolis
-// and heat-bath passes add the tile's accepted energy changes to partials[tile] in a
-// fixed order (wave sums, then the waves in order).  `tile` must be wave-uniform.
+// One tile of a colour pass (kPassThreads consecutive sites of one plane of the colour);
+// Metropolis and heat-bath passes add the tile's accepted energy changes to partials[tile]
+// in a fixed order (wave sums, then the waves in order).  `tile` must be wave-uniform.
 template <typename R, PassMode MODE, bool NT>
-__device__ __forceinline__ void pass_tile(const PassArgs<R>& a, int32_t tile) {
+__device__ __forceinline__ void pass_tile(const PassArgs<R>& a, uint32_t tile) {
   const Geometry& g = a.g;
-  const int32_t tx = tile % g.tiles_x;
-  const int32_t rest = tile / g.tiles_x;
-  const int32_t ty = rest % g.tiles_y;
-  const int32_t tz = rest / g.tiles_y;
-  const int32_t t = (int32_t)threadIdx.x;
-  SitePos q;
-  q.L = g.L;
-  q.Lh = g.Lh;
-  q.c = a.colour;
-  q.xh = (tx << g.bx_log) + (t & ((1 << g.bx_log) - 1));
-  q.y = (ty << g.by_log) + ((t >> g.bx_log) & ((1 << g.by_log) - 1));
-  q.z = (tz << g.bz_log) + (t >> (g.bx_log + g.by_log));
-  const bool active = t < g.threads && q.xh < g.Lh && q.y < g.L && q.z < g.L;
+  const uint32_t tp = (uint32_t)g.tiles_p;
+  uint32_t z = tile;  // tile / tp: the product with floor(2^32 / tp) is at most one short
+  if (tp > 1) {
+    z = __umulhi(tile, g.inv_tp);
+    z += tile - z * tp >= tp ? 1u : 0u;
+  }
+  const uint32_t t = threadIdx.x;
+  const uint32_t i = (tile - z * tp) * (uint32_t)kPassThreads + t;  // site of the plane
   const HitCtx<R> hc{a.beta, a.sweep, a.phase, a.k_hits, a.seed_lo, a.seed_hi};
 
   double dE_sum = 0.0;
-  if (active) {
-    if constexpr (sizeof(R) == 4)
-      dE_sum = update_site_b32<MODE, NT>(a.spins, a.J, q, hc);
-    else
-      dE_sum = update_site<R, MODE, NT>(a.spins, a.J, q, hc);
+  if (i < (uint32_t)g.plane) {
+    const uint32_t y = SmallDiv{(uint32_t)g.Lh, g.inv_lh}.div(i);
+    const uint32_t xh = i - y * (uint32_t)g.Lh;
+    const SiteOffsets o = site_offsets<R>((uint32_t)g.L, (uint32_t)g.Lh, (uint32_t)a.colour,
+                                          i + z * (uint32_t)g.plane, xh, y, z);
+    dE_sum = update_site<R, MODE, NT>(a.spins, a.J, a.colour, o, hc);
   }
 
   if constexpr (MODE != PassMode::OverRelax) {
-    __shared__ double wave_part[4];
+    __shared__ double wave_part[kPassThreads / 64];
     const double v = wave_sum(dE_sum);
     if ((t & 63) == 0) wave_part[t >> 6] = v;
     __syncthreads();
@@ -90,15 +78,15 @@ __device__ __forceinline__ void pass_tile(const PassArgs<R>& a, int32_t tile) {
 // Workgroup b of the launch takes tile tile_base + xcd_tile(b) (mirrored when the pass
 // walks z backwards); the grid is tile_count workgroups.
 template <typename R, PassMode MODE, bool NT>
-__global__ __launch_bounds__(256) void colour_pass_kernel(PassArgs<R> a) {
+__global__ __launch_bounds__(kPassThreads) void colour_pass_kernel(PassArgs<R> a) {
   int32_t tile = xcd_tile((int32_t)blockIdx.x, a.tile_count);
   if (a.reverse) tile = a.tile_count - 1 - tile;
-  pass_tile<R, MODE, NT>(a, __builtin_amdgcn_readfirstlane(a.tile_base + tile));
+  pass_tile<R, MODE, NT>(a, (uint32_t)__builtin_amdgcn_readfirstlane(a.tile_base + tile));
 }
 
 template <typename R, bool NT>
 void launch_pass_kind(PassMode mode, const PassArgs<R>& a, hipStream_t stream) {
-  const dim3 grid((unsigned)a.tile_count), block(256);
+  const dim3 grid((unsigned)a.tile_count), block(kPassThreads);
   switch (mode) {
     case PassMode::Metropolis:
     case PassMode::MetropolisFull:
