@@ -78,7 +78,7 @@ extern "C" {
                                before the next); HSG_FUSED alone, up to two phases per
                                march in binary32, is the SM4P analogue.  HSG_EINVAL
                                without HSG_FUSED */
-#define HSG_PLANE_LAUNCH 32 /* one launch per z slab of tiles -- per z plane for L >= 64 --
+#define HSG_PLANE_LAUNCH 32 /* one launch per z slab of tiles -- per z plane for L >= 24 --
                                instead of one per pass: 2L launches per phase, the CA
                                analogue's launch count.  Not with HSG_FUSED */
 #define HSG_PHASE_LAUNCH 128 /* each over-relaxation phase -- its colour-0 and colour-1
@@ -325,6 +325,22 @@ int hsg_batch_tiles(const hsg_chain *host_chains, int32_t n_chains, const int32_
 int hsg_batch_pass_sweep(const hsg_batch *b, const int32_t *tiles_dev, int32_t n_tiles,
                          int32_t tile_sites, int32_t max_n_or, int32_t renorm, int32_t n_sweeps,
                          void *stream);
+
+/* hsg_batch_sweep in the launches of hsg_batch_pass_sweep, for batches of few or large
+ * chains, which one workgroup per chain would leave most of the GPU idle for: the same
+ * spins, and energies summed in a fixed order (the same bits on every run).  tiles_dev
+ * lists the tiles of every chain of the batch, chain by chain (a device copy of the table
+ * hsg_batch_tiles writes for active = 0, 1, ..., n_chains - 1); first_tile_dev (device
+ * [n_chains + 1]) gives the number of chain c's first tile, and n_tiles for c = n_chains.
+ * partials_dev (device [n_tiles] doubles) holds the tiles' energy changes: zero before
+ * the first call, zero again after each; calls that share it, or the batch, are ordered
+ * by the caller.  max_n_or is the largest n_or of the chains, any_mc whether one has
+ * k_hits > 0, renorm whether one has renorm_every > 0.  b->remaining may be NULL.
+ * Launches only, so the call can be captured in a HIP graph. */
+int hsg_batch_tile_sweep(const hsg_batch *b, const int32_t *tiles_dev,
+                         const int32_t *first_tile_dev, int32_t n_tiles, int32_t tile_sites,
+                         double *partials_dev, int32_t any_mc, int32_t max_n_or, int32_t renorm,
+                         int32_t n_sweeps, void *stream);
 
 /* Parallel tempering over temperature ladders of chains of a batch. */
 typedef struct hsg_pt {

@@ -59,9 +59,12 @@ def _bind():
     L.hsg_pt_overlap.argtypes = [PP, BP, P, I32, P, P]
     L.hsg_batch_overlap_fourier.argtypes = [BP, P, I32, P, P]
     L.hsg_pt_overlap_fourier.argtypes = [PP, BP, P, I32, P, P]
+    L.hsg_batch_tiles.argtypes = [P, I32, P, I32, I32, P, I32, ctypes.POINTER(I32)]
+    L.hsg_batch_tile_sweep.argtypes = [BP, P, P, I32, I32, P, I32, I32, I32, I32, P]
     for name in ("hsg_batch_check", "hsg_batch_init", "hsg_batch_sweep",
                  "hsg_batch_energy", "hsg_batch_overlap", "hsg_pt_exchange", "hsg_pt_overlap",
-                 "hsg_batch_overlap_fourier", "hsg_pt_overlap_fourier"):
+                 "hsg_batch_overlap_fourier", "hsg_pt_overlap_fourier", "hsg_batch_tiles",
+                 "hsg_batch_tile_sweep"):
         getattr(L, name).restype = ctypes.c_int
     _bound = True
 
@@ -87,6 +90,28 @@ def lpt_order(Ls, groups) -> np.ndarray:
     Ls = np.asarray(Ls)
     groups = np.asarray(groups)
     return np.lexsort((np.arange(Ls.size), groups, -Ls.astype(np.int64) ** 3)).astype(np.int32)
+
+
+TILE_SITES = 256
+
+
+def tiles_pay(specs) -> bool:
+    """Whether a sweep of these chains runs as launches over tiles of every chain, one per
+    colour pass, rather than as one launch with a workgroup per chain.
+
+    A workgroup alone needs, per sweep of k = 4 hits, 5 us at L = 8, 23 at 16, 42 at 20,
+    66 at 24, 150 at 32 and 1340 at 64, whether it is one of 4 chains or of 256 (a compute
+    unit each); the launches over tiles need 11 us plus 11 ps a site.  So they win for few
+    chains: up to about 200 chains of L = 16 (128: 24 against 17 us, 256: 24 against 27),
+    600 of L = 20 or 24 (L = 24, 512: 92 against 85, 1024: 155 against 164), and of larger
+    ones, which do not stay near their compute unit, up to 2048 (L = 48: 2692 against
+    2554).  Beyond, both forms are bound by the rate of the whole GPU, and the one launch,
+    whose chains of a sample read their couplings together, is the faster (12288 chains of
+    L = 16 .. 48: 57.9 against 60.4 ms for ten sweeps)."""
+    sites = [c.L ** 3 for c in specs]
+    most = max(sites)
+    limit = 2048 if most >= 32 ** 3 else 512 if most >= 20 ** 3 else 192 if most >= 16 ** 3 else 0
+    return sum(sites) <= limit * most
 
 
 class Batch:
@@ -143,6 +168,7 @@ class Batch:
                          self.remaining.data_ptr() if self.remaining is not None else None,
                          self.order.data_ptr(), threads, 0)
         self._export_work: dict[int, torch.Tensor] = {}
+        self._tiles = self._tile_table() if tiles_pay(self.specs) else None
         if init:
             self.init(stream)
 
@@ -157,8 +183,31 @@ class Batch:
     def init(self, stream=None) -> None:
         check(lib().hsg_batch_init(ctypes.byref(self._d), _stream(stream)))
 
+    def _tile_table(self) -> tuple:
+        """Tiles of every chain, each chain's first tile and the tiles' energy partials."""
+        Ls = self.table["L"].astype(np.int64)
+        count = -(-(Ls ** 3 // 2) // TILE_SITES)
+        first = np.concatenate([[0], np.cumsum(count)])
+        n = ctypes.c_int32()
+        tiles = np.zeros(2 * int(first[-1]), dtype=np.int32)
+        active = np.arange(self.n, dtype=np.int32)
+        check(lib().hsg_batch_tiles(self.table.ctypes.data_as(ctypes.c_void_p), self.n,
+                                    active.ctypes.data_as(ctypes.c_void_p), self.n, TILE_SITES,
+                                    tiles.ctypes.data_as(ctypes.c_void_p), int(first[-1]),
+                                    ctypes.byref(n)))
+        return (torch.from_numpy(tiles).to(self.device),
+                torch.from_numpy(first.astype(np.int32)).to(self.device), n.value,
+                torch.zeros(n.value, dtype=torch.float64, device=self.device))
+
     def sweep(self, n_sweeps: int, stream=None) -> None:
-        check(lib().hsg_batch_sweep(ctypes.byref(self._d), int(n_sweeps), _stream(stream)))
+        if self._tiles is None:
+            check(lib().hsg_batch_sweep(ctypes.byref(self._d), int(n_sweeps), _stream(stream)))
+            return
+        tiles, first, n, partials = self._tiles
+        check(lib().hsg_batch_tile_sweep(
+            ctypes.byref(self._d), _ptr(tiles), _ptr(first), n, TILE_SITES, _ptr(partials),
+            int(any(c.k > 0 for c in self.specs)), max(c.n_or for c in self.specs),
+            int(any(c.renorm_every > 0 for c in self.specs)), int(n_sweeps), _stream(stream)))
 
     def energies(self, recompute: bool = False, stream=None) -> torch.Tensor:
         if not recompute:

@@ -118,7 +118,7 @@ bool renorm_due(const hsg_sweep_params* p, uint64_t sweep) {
 }
 
 // Pass-by-pass schedule: one launch per colour pass over the whole lattice, or with
-// HSG_PLANE_LAUNCH one launch per z slab of tiles (one z plane from L = 64 up).  With
+// HSG_PLANE_LAUNCH one launch per z slab of tiles (one z plane from L = 24 up).  With
 // HSG_PHASE_LAUNCH each over-relaxation phase is one launch reading one spin array and
 // writing the other (the lattice's and the work buffer's second one); when a call would
 // run an odd number of them, its last phase (never one that carries a Monte Carlo pass)
@@ -729,6 +729,31 @@ int hsg_batch_pass_sweep(const hsg_batch* b, const int32_t* tiles_dev, int32_t n
           : hsg::launch_batch_pass_sweep<double>(b, tiles_dev, n_tiles, tile_sites, max_n_or,
                                                  renorm, n_sweeps, st),
       "batch pass sweep");
+}
+
+int hsg_batch_tile_sweep(const hsg_batch* b, const int32_t* tiles_dev,
+                         const int32_t* first_tile_dev, int32_t n_tiles, int32_t tile_sites,
+                         double* partials_dev, int32_t any_mc, int32_t max_n_or, int32_t renorm,
+                         int32_t n_sweeps, void* stream) {
+  int rc = check_batch(b);
+  if (rc) return rc;
+  if (!tiles_dev || !first_tile_dev || !partials_dev || n_tiles < b->n_chains || n_sweeps < 0 ||
+      max_n_or < 0 || max_n_or > 0x7FFF)
+    return fail(HSG_EINVAL, "bad tiles, partials, n_sweeps or max_n_or");
+  if (tile_sites < 64 || tile_sites > 1024 || (tile_sites & 63))
+    return fail(HSG_EINVAL, "tile_sites must be a multiple of 64 in [64, 1024]");
+  if (n_sweeps == 0) return HSG_OK;
+  hipStream_t st = as_stream(stream);
+  const int32_t first_phase = any_mc ? 0 : 1;
+  return device_status(
+      b->dtype == HSG_F32
+          ? hsg::launch_batch_tile_sweep<float>(b, tiles_dev, first_tile_dev, n_tiles, tile_sites,
+                                                partials_dev, first_phase, max_n_or, renorm,
+                                                n_sweeps, st)
+          : hsg::launch_batch_tile_sweep<double>(b, tiles_dev, first_tile_dev, n_tiles, tile_sites,
+                                                 partials_dev, first_phase, max_n_or, renorm,
+                                                 n_sweeps, st),
+      "batch tile sweep");
 }
 
 static int check_pt(const hsg_pt* pt) {

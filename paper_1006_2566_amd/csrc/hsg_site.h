@@ -96,6 +96,28 @@ __device__ __forceinline__ SiteOffsets site_offsets(uint32_t L, uint32_t Lh, uin
   return o;
 }
 
+// Tile `tile` (wave-uniform) of a colour's sites: its plane z and thread threadIdx.x's site
+// i of that plane (none when i >= g.plane).
+struct TileSite {
+  uint32_t z, i;
+};
+__device__ __forceinline__ TileSite tile_site(const Geometry& g, uint32_t tile) {
+  const uint32_t tp = (uint32_t)g.tiles_p;
+  uint32_t z = tile;  // tile / tp: the product with floor(2^32 / tp) is at most one short
+  if (tp > 1) {
+    z = __umulhi(tile, g.inv_tp);
+    z += tile - z * tp >= tp ? 1u : 0u;
+  }
+  return TileSite{z, (tile - z * tp) * (uint32_t)kPassThreads + threadIdx.x};
+}
+template <typename R>
+__device__ __forceinline__ SiteOffsets tile_site_offsets(const Geometry& g, const TileSite& s,
+                                                         uint32_t colour) {
+  const uint32_t y = SmallDiv{(uint32_t)g.Lh, g.inv_lh}.div(s.i);
+  return site_offsets<R>((uint32_t)g.L, (uint32_t)g.Lh, colour, s.i + s.z * (uint32_t)g.plane,
+                         s.i - y * (uint32_t)g.Lh, y, s.z);
+}
+
 // Monte Carlo stream of the site: Philox key and the uniform counter words.
 template <typename R>
 struct HitCtx {
@@ -285,31 +307,22 @@ __device__ __forceinline__ void renormalise_spin(const Planes<R>& S, int c, int6
   S.p[3 * c + 2][e] = dev_div(s.z, n);
 }
 
-// sigma_i . h_i of the colour-0 site (xh, y, z) in binary64.  Every bond has exactly
-// one colour-0 end (L even), so H = -(sum of this over the colour-0 sites).
+// sigma_i . h_i of the colour-0 site at o in binary64.  Every bond has exactly one
+// colour-0 end (L even), so H = -(sum of this over the colour-0 sites).
 template <typename R>
-__device__ __forceinline__ double colour0_bond_sum(const R* spins, const R* J, int64_t Nh,
-                                                   int32_t L, int32_t Lh, int32_t xh, int32_t y,
-                                                   int32_t z) {
-  const int32_t p = (y + z) & 1;
-  const int32_t ym = y == 0 ? L - 1 : y - 1, yp = y == L - 1 ? 0 : y + 1;
-  const int32_t zm = z == 0 ? L - 1 : z - 1, zp = z == L - 1 ? 0 : z + 1;
-  const int64_t row = (int64_t)Lh * (y + (int64_t)L * z);
-  const int64_t own = row + xh;
-  const int64_t nb[6] = {row + (p ? (xh + 1 == Lh ? 0 : xh + 1) : xh),
-                         row + (p ? xh : (xh == 0 ? Lh - 1 : xh - 1)),
-                         (int64_t)Lh * (yp + (int64_t)L * z) + xh,
-                         (int64_t)Lh * (ym + (int64_t)L * z) + xh,
-                         (int64_t)Lh * (y + (int64_t)L * zp) + xh,
-                         (int64_t)Lh * (y + (int64_t)L * zm) + xh};
-  const double jb[6] = {(double)J[own],      (double)J[3 * Nh + nb[1]], (double)J[Nh + own],
-                        (double)J[4 * Nh + nb[3]], (double)J[2 * Nh + own],
-                        (double)J[5 * Nh + nb[5]]};
+__device__ __forceinline__ double colour0_bond_sum(const Planes<R>& S, const Planes<R>& J,
+                                                   const SiteOffsets& o) {
+  const double j[6] = {(double)plane_ld<false>(J.p[0], o.own), (double)plane_ld<false>(J.p[3], o.mx),
+                       (double)plane_ld<false>(J.p[1], o.own), (double)plane_ld<false>(J.p[4], o.my),
+                       (double)plane_ld<false>(J.p[2], o.own), (double)plane_ld<false>(J.p[5], o.mz)};
+  const uint32_t nb[6] = {o.px, o.mx, o.py, o.my, o.pz, o.mz};
   double e_site = 0.0;
+#pragma unroll
   for (int k = 0; k < 3; ++k) {
     double hk = 0.0;
-    for (int d = 0; d < 6; ++d) hk = fma(jb[d], (double)spins[(3 + k) * Nh + nb[d]], hk);
-    e_site = fma((double)spins[k * Nh + own], hk, e_site);
+#pragma unroll
+    for (int d = 0; d < 6; ++d) hk = fma(j[d], (double)plane_ld<false>(S.p[3 + k], nb[d]), hk);
+    e_site = fma((double)plane_ld<false>(S.p[k], o.own), hk, e_site);
   }
   return e_site;
 }

@@ -84,24 +84,30 @@ __device__ __forceinline__ int32_t uniform(int32_t v) { return __builtin_amdgcn_
 __device__ __forceinline__ uint32_t uniform(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)v);
 }
-__device__ __forceinline__ uint64_t uniform(uint64_t v) {
-  return (uint64_t)uniform((uint32_t)v) | ((uint64_t)uniform((uint32_t)(v >> 32)) << 32);
-}
-__device__ __forceinline__ int64_t uniform(int64_t v) { return (int64_t)uniform((uint64_t)v); }
 
-// The chain table entry, with every field made uniform (see uniform()).
+// Element i (wave-uniform) of a table that no kernel writes while this one runs: read
+// through the constant address space, so that it is one scalar load.  A tile's table
+// entry, its chain and the chain's state hang on one another; as vector loads these three
+// round trips and the fourteen words moved to scalar registers were half of a short pass.
+template <typename T>
+__device__ __forceinline__ T uniform_ld(const T* table, int32_t i) {
+  typedef const T __attribute__((address_space(4))) * ConstPtr;
+  return ((ConstPtr)(uintptr_t)table)[i];
+}
+
+// The chain table entry, every field scalar.
 __device__ __forceinline__ hsg_chain load_chain(const hsg_chain* chains, int32_t ci) {
-  const hsg_chain c = chains[ci];
   hsg_chain u;
-  u.spin_offset = uniform(c.spin_offset);
-  u.J_offset = uniform(c.J_offset);
-  u.seed = uniform(c.seed);
-  u.J_seed = uniform(c.J_seed);
-  u.L = uniform(c.L);
-  u.k_hits = uniform(c.k_hits);
-  u.n_or = uniform(c.n_or);
-  u.renorm_every = uniform(c.renorm_every);
-  u.flags = uniform(c.flags);
+  const hsg_chain* c = chains + uniform(ci);
+  u.spin_offset = uniform_ld(&c->spin_offset, 0);
+  u.J_offset = uniform_ld(&c->J_offset, 0);
+  u.seed = uniform_ld(&c->seed, 0);
+  u.J_seed = 0;  // read by the initial state only
+  u.L = uniform_ld(&c->L, 0);
+  u.k_hits = uniform_ld(&c->k_hits, 0);
+  u.n_or = uniform_ld(&c->n_or, 0);
+  u.renorm_every = uniform_ld(&c->renorm_every, 0);
+  u.flags = uniform_ld(&c->flags, 0);
   u.reserved = 0;
   return u;
 }
@@ -179,48 +185,76 @@ __global__ __launch_bounds__(256) void batch_init_kernel(const hsg_chain* chains
                  (uint32_t)ch.J_seed, (uint32_t)(ch.J_seed >> 32));
 }
 
+// H of a chain, by one workgroup: the colour's index in 32 bits, divided by products.
 template <typename R>
 __global__ __launch_bounds__(kChainReduceThreads) void batch_energy_kernel(
-    const hsg_chain* chains, const R* spins, const R* J, double* out) {
+    const hsg_chain* chains, R* spins, R* J, double* out) {
   __shared__ double s_red[16];
-  const hsg_chain ch = chains[blockIdx.x];
-  const int32_t L = ch.L, Lh = L / 2;
-  const int64_t Nh = (int64_t)Lh * L * L;
+  const ChainView<R> v = chain_view<R>(load_chain(chains, (int32_t)blockIdx.x), spins, J);
+  const SmallDiv by_lh((uint32_t)v.Lh), by_l((uint32_t)v.L);
   double acc = 0.0;
-  for (int64_t e = threadIdx.x; e < Nh; e += blockDim.x) {
-    const SiteOf st = site_of(e, L);
-    acc += colour0_bond_sum(spins + ch.spin_offset, J + ch.J_offset, Nh, L, Lh, st.xh, st.y, st.z);
-  }
+  for (uint32_t ic = threadIdx.x; ic < (uint32_t)v.Nh; ic += kChainReduceThreads)
+    acc += colour0_bond_sum<R>(v.S, v.J, chain_site<R, 0>(v, ic, by_lh, by_l));
   const double total = block_sum(acc, s_red);
   if (threadIdx.x == 0) out[blockIdx.x] = -total;
 }
 
-// Overlap of two chains of equal L, reduced by one workgroup.
+// Overlap of two chains of equal L, reduced by one workgroup.  A thread takes U sites at a
+// time, their loads in flight together (one compute unit reads a whole pair: the loop is
+// bound by the latency of its loads); the waves' sums are added in order, all 15 at once.
 template <typename R>
 __device__ __forceinline__ void pair_overlap(const hsg_chain& ca, const hsg_chain& cb,
                                              const R* spins, double* out) {
-  __shared__ double s_red[16];
-  const int64_t N = (int64_t)ca.L * ca.L * ca.L, Nh = N / 2;
+  constexpr int kWaves = kChainReduceThreads / 64;
+  constexpr int U = sizeof(R) == 4 ? 4 : 2;
+  __shared__ double part[kWaves][16];
+  const uint32_t Nh = (uint32_t)(ca.L / 2) * (uint32_t)ca.L * (uint32_t)ca.L;
   const R* a = spins + ca.spin_offset;
   const R* b = spins + cb.spin_offset;
   double v[15] = {0.0};
-  for (int64_t e = threadIdx.x; e < N; e += blockDim.x) {
-    const int64_t c = e >= Nh ? 1 : 0;
-    const int64_t base = 3 * c * Nh + (e - c * Nh);
-    double av[3], bv[3];
-    for (int k = 0; k < 3; ++k) {
-      av[k] = (double)a[base + k * Nh];
-      bv[k] = (double)b[base + k * Nh];
-    }
+  auto add = [&](const R* av, const R* bv) {
+    const double x[3] = {(double)av[0], (double)av[1], (double)av[2]};
+    const double y[3] = {(double)bv[0], (double)bv[1], (double)bv[2]};
+#pragma unroll
     for (int m = 0; m < 3; ++m) {
-      for (int n = 0; n < 3; ++n) v[3 * m + n] = fma(av[m], bv[n], v[3 * m + n]);
-      v[9 + m] += av[m];
-      v[12 + m] += bv[m];
+#pragma unroll
+      for (int n = 0; n < 3; ++n) v[3 * m + n] = fma(x[m], y[n], v[3 * m + n]);
+      v[9 + m] += x[m];
+      v[12 + m] += y[m];
+    }
+  };
+  for (int c = 0; c < 2; ++c) {
+    const R* ac = a + 3 * c * Nh;
+    const R* bc = b + 3 * c * Nh;
+    uint32_t e = threadIdx.x;
+    for (; e + (U - 1) * kChainReduceThreads < Nh; e += U * kChainReduceThreads) {
+      R av[U][3], bv[U][3];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          av[u][k] = ac[k * Nh + e + u * kChainReduceThreads];
+          bv[u][k] = bc[k * Nh + e + u * kChainReduceThreads];
+        }
+#pragma unroll
+      for (int u = 0; u < U; ++u) add(av[u], bv[u]);
+    }
+    for (; e < Nh; e += kChainReduceThreads) {
+      const R av[3] = {ac[e], ac[Nh + e], ac[2 * Nh + e]};
+      const R bv[3] = {bc[e], bc[Nh + e], bc[2 * Nh + e]};
+      add(av, bv);
     }
   }
+#pragma unroll
   for (int k = 0; k < 15; ++k) {
-    const double t = block_sum(v[k], s_red);
-    if (threadIdx.x == 0) out[k] = t / (double)N;
+    const double t = wave_sum(v[k]);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6][k] = t;
+  }
+  __syncthreads();
+  if (threadIdx.x < 15) {
+    double t = 0.0;
+    for (int w = 0; w < kWaves; ++w) t += part[w][threadIdx.x];
+    out[threadIdx.x] = t / (2.0 * (double)Nh);
   }
 }
 
@@ -242,17 +276,32 @@ __global__ __launch_bounds__(kChainReduceThreads) void ladder_pairs_overlap_kern
   pair_overlap<R>(chains[a], chains[b], spins, out + 15 * ((int64_t)p * n_temps + t));
 }
 
-// One exchange round per ladder (one thread per ladder; the ladders are short).
-__global__ void pt_exchange_kernel(int32_t n_ladders, int32_t n_temps, int32_t* chain_at_slot,
-                                   const double* beta_of_slot, int32_t* accepted,
-                                   uint32_t seed_lo, uint32_t seed_hi, uint32_t* round_ctr,
-                                   const double* E, double* beta) {
-  const int32_t l = blockIdx.x * blockDim.x + threadIdx.x;
-  const uint32_t round = *round_ctr;  // advanced by bump_round_kernel afterwards
-  if (l >= n_ladders) return;
+// One exchange round: a thread per slot of every ladder.  Round n pairs the slots (t, t+1)
+// with t = n mod 2, t + 2, ...; the pairs of a round share no slot, so the thread of a
+// pair's lower slot decides the swap and sets both temperatures, and a slot without a
+// partner keeps its own.  With `bump` (one workgroup) the round counter is advanced here,
+// after every thread has read it.  (A thread per ladder walked its pairs one dependent
+// load after another: 9.6 us for 24 temperatures.)
+constexpr int kExchangeThreads = 256;
+__global__ __launch_bounds__(kExchangeThreads) void pt_exchange_kernel(
+    int32_t n_ladders, int32_t n_temps, int32_t* chain_at_slot, const double* beta_of_slot,
+    int32_t* accepted, uint32_t seed_lo, uint32_t seed_hi, uint32_t* round_ctr, const double* E,
+    double* beta, int32_t bump) {
+  const int64_t i = blockIdx.x * (int64_t)kExchangeThreads + threadIdx.x;
+  const uint32_t round = *round_ctr;
+  if (bump) {
+    __syncthreads();
+    if (threadIdx.x == 0) *round_ctr = round + 1u;
+  }
+  if (i >= (int64_t)n_ladders * n_temps) return;
+  const int32_t l = (int32_t)(i / n_temps), t = (int32_t)(i - (int64_t)l * n_temps);
+  const int32_t parity = (int32_t)(round & 1u);
   int32_t* slots = chain_at_slot + (int64_t)l * n_temps;
-  for (int32_t t = (int32_t)(round & 1u); t + 1 < n_temps; t += 2) {
-    const int32_t ca = slots[t], cb = slots[t + 1];
+  const bool lower = t >= parity && ((t - parity) & 1) == 0;  // lower slot of a pair, if any
+  if (!lower && t > parity) return;                           // upper slot: its partner's work
+  int32_t ca = slots[t];
+  if (lower && t + 1 < n_temps) {
+    int32_t cb = slots[t + 1];
     const double delta = (beta_of_slot[t] - beta_of_slot[t + 1]) * (E[ca] - E[cb]);
     const Word4 w = philox10((uint32_t)t, round, (uint32_t)l, kTagSwap, seed_lo, seed_hi);
     const double u = unit_uniform<double>(w.w0);
@@ -260,9 +309,13 @@ __global__ void pt_exchange_kernel(int32_t n_ladders, int32_t n_temps, int32_t* 
       slots[t] = cb;
       slots[t + 1] = ca;
       if (accepted) accepted[(int64_t)l * n_temps + t] += 1;
+      const int32_t c = ca;
+      ca = cb;
+      cb = c;
     }
+    beta[cb] = beta_of_slot[t + 1];
   }
-  for (int32_t t = 0; t < n_temps; ++t) beta[slots[t]] = beta_of_slot[t];
+  beta[ca] = beta_of_slot[t];
 }
 
 __global__ void bump_round_kernel(uint32_t* round_ctr) { *round_ctr += 1u; }
@@ -280,8 +333,9 @@ struct MultiPassArgs {
   const double* beta;
   double* E;
   const uint32_t* sweep;
-  const int32_t* remaining;
+  const int32_t* remaining;  // NULL: every chain runs all the call's sweeps
   const int32_t* tiles;
+  double* partials;  // a double per tile that takes its energy changes, or NULL: atomics on E
   int32_t n_tiles;
   int32_t s;  // sweep offset within the call
   int32_t phase;
@@ -294,18 +348,19 @@ __global__ __launch_bounds__(1024) void multi_pass_kernel(MultiPassArgs<R> a) {
   __shared__ double s_red[16];
   int32_t t = xcd_tile((int32_t)blockIdx.x, a.n_tiles);
   if (a.reverse) t = a.n_tiles - 1 - t;
-  const int32_t ci = uniform(a.tiles[2 * t]), ic0 = uniform(a.tiles[2 * t + 1]);
-  if (a.s >= uniform(a.remaining[ci])) return;
+  t = uniform(t);
+  const int32_t ci = uniform_ld(a.tiles, 2 * t), ic0 = uniform_ld(a.tiles, 2 * t + 1);
+  if (a.remaining && a.s >= uniform_ld(a.remaining, ci)) return;
   const hsg_chain ch = load_chain(a.chains, ci);
   if ((a.phase == 0 && ch.k_hits == 0) || a.phase > ch.n_or) return;
   const ChainView<R> v = chain_view<R>(ch, a.spins, a.J);
   const uint32_t ic = (uint32_t)ic0 + threadIdx.x;
   HitCtx<R> hc;
-  hc.beta = (R)a.beta[ci];
+  hc.beta = (R)uniform_ld(a.beta, ci);
   hc.k_hits = ch.k_hits;
   hc.seed_lo = (uint32_t)ch.seed;
   hc.seed_hi = (uint32_t)(ch.seed >> 32);
-  hc.sweep = a.sweep[ci] + (uint32_t)a.s;
+  hc.sweep = uniform_ld(a.sweep, ci) + (uint32_t)a.s;
   hc.phase = (uint32_t)a.phase;
   double dE = 0.0;
   if (ic < (uint32_t)v.Nh) {
@@ -322,7 +377,12 @@ __global__ __launch_bounds__(1024) void multi_pass_kernel(MultiPassArgs<R> a) {
   }
   if (a.phase == 0) {
     const double total = block_sum(dE, s_red);
-    if (threadIdx.x == 0 && total != 0.0) atomicAdd(&a.E[ci], total);
+    if (threadIdx.x == 0 && total != 0.0) {
+      if (a.partials)
+        a.partials[t] += total;
+      else
+        atomicAdd(&a.E[ci], total);
+    }
   }
 }
 
@@ -333,10 +393,11 @@ __global__ __launch_bounds__(1024) void multi_renorm_kernel(const hsg_chain* cha
                                                             const int32_t* remaining,
                                                             const int32_t* tiles, int32_t s) {
   const int32_t t = blockIdx.x;
-  const int32_t ci = tiles[2 * t], ic0 = tiles[2 * t + 1];
-  if (s >= remaining[ci]) return;
-  const hsg_chain ch = chains[ci];
-  if (ch.renorm_every <= 0 || (sweep[ci] + (uint32_t)s + 1u) % (uint32_t)ch.renorm_every != 0u)
+  const int32_t ci = uniform_ld(tiles, 2 * t), ic0 = uniform_ld(tiles, 2 * t + 1);
+  if (remaining && s >= uniform_ld(remaining, ci)) return;
+  const hsg_chain ch = load_chain(chains, ci);
+  if (ch.renorm_every <= 0 ||
+      (uniform_ld(sweep, ci) + (uint32_t)s + 1u) % (uint32_t)ch.renorm_every != 0u)
     return;
   const int64_t Nh = (int64_t)(ch.L / 2) * ch.L * ch.L;
   const Planes<R> S = planes_of<R>(spins + ch.spin_offset, Nh);
@@ -359,6 +420,31 @@ __global__ void multi_finish_kernel(int32_t n_chains, uint32_t* sweep, int32_t* 
   }
 }
 
+// The same with partials: workgroup c also adds the partials of chain c's tiles (a fixed
+// order, then zeroed) to its energy.
+__global__ __launch_bounds__(256) void tile_finish_kernel(const int32_t* first_tile,
+                                                          double* partials, double* E,
+                                                          uint32_t* sweep, int32_t* remaining,
+                                                          int32_t n_sweeps) {
+  __shared__ double s_red[16];
+  const int32_t c = (int32_t)blockIdx.x;
+  const int32_t t1 = first_tile[c + 1];
+  double acc = 0.0;
+  for (int32_t t = first_tile[c] + (int32_t)threadIdx.x; t < t1; t += 256) {
+    acc += partials[t];
+    partials[t] = 0.0;
+  }
+  const double total = block_sum(acc, s_red);
+  if (threadIdx.x == 0) {
+    E[c] += total;
+    const int32_t n = remaining ? min(n_sweeps, remaining[c]) : n_sweeps;
+    if (n > 0) {
+      sweep[c] += (uint32_t)n;
+      if (remaining) remaining[c] -= n;
+    }
+  }
+}
+
 }  // namespace
 
 template <typename R>
@@ -367,7 +453,7 @@ hipError_t launch_batch_init(const hsg_batch* b, hipStream_t st) {
                      b->chains, (R*)b->spins, (R*)b->J);
   hipLaunchKernelGGL(batch_energy_kernel<R>, dim3((unsigned)b->n_chains),
                      dim3(kChainReduceThreads), 0, st,
-                     b->chains, (const R*)b->spins, (const R*)b->J, b->E);
+                     b->chains, (R*)b->spins, (R*)b->J, b->E);
   return hipGetLastError();
 }
 
@@ -394,7 +480,7 @@ template <typename R>
 hipError_t launch_batch_energy(const hsg_batch* b, double* out, hipStream_t st) {
   hipLaunchKernelGGL(batch_energy_kernel<R>, dim3((unsigned)b->n_chains),
                      dim3(kChainReduceThreads), 0, st,
-                     b->chains, (const R*)b->spins, (const R*)b->J, out);
+                     b->chains, (R*)b->spins, (R*)b->J, out);
   return hipGetLastError();
 }
 
@@ -418,18 +504,24 @@ hipError_t launch_pt_overlap(const hsg_pt* pt, const hsg_batch* b, const int32_t
 }
 
 hipError_t launch_pt_exchange(const hsg_pt* pt, const hsg_batch* b, hipStream_t st) {
-  const unsigned blocks = (unsigned)((pt->n_ladders + 63) / 64);
-  hipLaunchKernelGGL(pt_exchange_kernel, dim3(blocks), dim3(64), 0, st, pt->n_ladders, pt->n_temps,
-                     pt->chain_at_slot, pt->beta_of_slot, pt->accepted, (uint32_t)pt->seed,
-                     (uint32_t)(pt->seed >> 32), pt->round, (const double*)b->E, b->beta);
-  hipLaunchKernelGGL(bump_round_kernel, dim3(1), dim3(1), 0, st, pt->round);
+  const int64_t slots = (int64_t)pt->n_ladders * pt->n_temps;
+  const unsigned blocks = (unsigned)((slots + kExchangeThreads - 1) / kExchangeThreads);
+  const int32_t bump = blocks == 1 ? 1 : 0;
+  hipLaunchKernelGGL(pt_exchange_kernel, dim3(blocks), dim3(kExchangeThreads), 0, st,
+                     pt->n_ladders, pt->n_temps, pt->chain_at_slot, pt->beta_of_slot, pt->accepted,
+                     (uint32_t)pt->seed, (uint32_t)(pt->seed >> 32), pt->round,
+                     (const double*)b->E, b->beta, bump);
+  if (!bump) hipLaunchKernelGGL(bump_round_kernel, dim3(1), dim3(1), 0, st, pt->round);
   return hipGetLastError();
 }
 
+// The colour passes of n_sweeps sweeps, a launch each over the tiles, and the
+// renormalisations between them.
 template <typename R>
-hipError_t launch_batch_pass_sweep(const hsg_batch* b, const int32_t* tiles, int32_t n_tiles,
-                                   int32_t tile_sites, int32_t max_n_or, int32_t renorm,
-                                   int32_t n_sweeps, hipStream_t st) {
+static void launch_tile_passes(const hsg_batch* b, const int32_t* tiles, double* partials,
+                               int32_t n_tiles, int32_t tile_sites, int32_t first_phase,
+                               int32_t max_n_or, int32_t renorm, int32_t n_sweeps,
+                               hipStream_t st) {
   MultiPassArgs<R> a;
   a.chains = b->chains;
   a.spins = (R*)b->spins;
@@ -439,30 +531,48 @@ hipError_t launch_batch_pass_sweep(const hsg_batch* b, const int32_t* tiles, int
   a.sweep = b->sweep;
   a.remaining = b->remaining;
   a.tiles = tiles;
+  a.partials = partials;
   a.n_tiles = n_tiles;
+  const dim3 grid((unsigned)n_tiles), block((unsigned)tile_sites);
   int32_t pass = 0;
   for (int32_t s = 0; s < n_sweeps; ++s) {
     a.s = s;
-    for (int32_t phase = 0; phase <= max_n_or; ++phase) {
+    for (int32_t phase = first_phase; phase <= max_n_or; ++phase) {
       a.phase = phase;
       for (int32_t colour = 0; colour < 2; ++colour) {
         a.colour = colour;
         a.reverse = pass++ & 1;
         if (colour == 0)
-          hipLaunchKernelGGL((multi_pass_kernel<R, 0>), dim3((unsigned)n_tiles),
-                             dim3((unsigned)tile_sites), 0, st, a);
+          hipLaunchKernelGGL((multi_pass_kernel<R, 0>), grid, block, 0, st, a);
         else
-          hipLaunchKernelGGL((multi_pass_kernel<R, 1>), dim3((unsigned)n_tiles),
-                             dim3((unsigned)tile_sites), 0, st, a);
+          hipLaunchKernelGGL((multi_pass_kernel<R, 1>), grid, block, 0, st, a);
       }
     }
     if (renorm)
-      hipLaunchKernelGGL(multi_renorm_kernel<R>, dim3((unsigned)n_tiles), dim3((unsigned)tile_sites),
-                         0, st, b->chains, (R*)b->spins, (const uint32_t*)b->sweep,
-                         (const int32_t*)b->remaining, tiles, s);
+      hipLaunchKernelGGL(multi_renorm_kernel<R>, grid, block, 0, st, b->chains, (R*)b->spins,
+                         (const uint32_t*)b->sweep, (const int32_t*)b->remaining, tiles, s);
   }
+}
+
+template <typename R>
+hipError_t launch_batch_pass_sweep(const hsg_batch* b, const int32_t* tiles, int32_t n_tiles,
+                                   int32_t tile_sites, int32_t max_n_or, int32_t renorm,
+                                   int32_t n_sweeps, hipStream_t st) {
+  launch_tile_passes<R>(b, tiles, nullptr, n_tiles, tile_sites, 0, max_n_or, renorm, n_sweeps, st);
   hipLaunchKernelGGL(multi_finish_kernel, dim3((unsigned)((b->n_chains + 255) / 256)), dim3(256), 0,
                      st, b->n_chains, b->sweep, b->remaining, n_sweeps);
+  return hipGetLastError();
+}
+
+template <typename R>
+hipError_t launch_batch_tile_sweep(const hsg_batch* b, const int32_t* tiles,
+                                   const int32_t* first_tile, int32_t n_tiles, int32_t tile_sites,
+                                   double* partials, int32_t first_phase, int32_t max_n_or,
+                                   int32_t renorm, int32_t n_sweeps, hipStream_t st) {
+  launch_tile_passes<R>(b, tiles, partials, n_tiles, tile_sites, first_phase, max_n_or, renorm,
+                        n_sweeps, st);
+  hipLaunchKernelGGL(tile_finish_kernel, dim3((unsigned)b->n_chains), dim3(256), 0, st, first_tile,
+                     partials, b->E, b->sweep, b->remaining, n_sweeps);
   return hipGetLastError();
 }
 
@@ -475,6 +585,9 @@ hipError_t launch_batch_pass_sweep(const hsg_batch* b, const int32_t* tiles, int
   template hipError_t launch_pt_overlap<R>(const hsg_pt*, const hsg_batch*, const int32_t*,   \
                                            int32_t, double*, hipStream_t);                     \
   template hipError_t launch_batch_pass_sweep<R>(const hsg_batch*, const int32_t*, int32_t,   \
+                                                 int32_t, int32_t, int32_t, int32_t, hipStream_t); \
+  template hipError_t launch_batch_tile_sweep<R>(const hsg_batch*, const int32_t*,             \
+                                                 const int32_t*, int32_t, int32_t, double*,     \
                                                  int32_t, int32_t, int32_t, int32_t, hipStream_t);
 HSG_BATCH_INSTANTIATE(float)
 HSG_BATCH_INSTANTIATE(double)

@@ -90,18 +90,16 @@ __device__ __forceinline__ void block_partials(double (&v)[kReduceSlots], int ns
 }
 
 // Energy over the colour-0 sites: every bond has exactly one colour-0 end (L even),
-// so H = -sum over colour-0 sites of sigma_i . h_i, all in binary64.
+// so H = -sum over colour-0 sites of sigma_i . h_i, all in binary64.  Workgroup b takes
+// tiles b, b + gridDim.x, ... of the colour.
+static_assert(kReduceThreads == kPassThreads, "a tile's sites are a workgroup's threads");
 template <typename R>
-__global__ __launch_bounds__(kReduceThreads) void energy_kernel(int32_t L, const R* spins,
-                                                                const R* J, double* partials) {
-  const int32_t Lh = L / 2;
-  const int64_t Nh = (int64_t)Lh * L * L;
+__global__ __launch_bounds__(kReduceThreads) void energy_kernel(Geometry g, Planes<R> S,
+                                                                Planes<R> J, double* partials) {
   double v[kReduceSlots] = {0.0};
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < Nh;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const SiteOf st = site_of(e, L);  // colour 0
-    const double e_site = colour0_bond_sum(spins, J, Nh, L, Lh, st.xh, st.y, st.z);
-    v[0] += e_site;
+  for (uint32_t tile = blockIdx.x; tile < (uint32_t)g.n_blocks; tile += gridDim.x) {
+    const TileSite ts = tile_site(g, tile);
+    if (ts.i < (uint32_t)g.plane) v[0] += colour0_bond_sum<R>(S, J, tile_site_offsets<R>(g, ts, 0));
   }
   block_partials(v, 1, partials);
 }
@@ -129,26 +127,28 @@ __global__ __launch_bounds__(kReduceThreads) void overlap_kernel(int64_t N, cons
   block_partials(v, 15, partials);
 }
 
-// out[k] = scale * sum over blocks of partials[block][k] (fixed order), k < nslots.
-__global__ __launch_bounds__(kReduceThreads) void finish_reduce_kernel(const double* partials,
+// out[k] = scale * sum over blocks of partials[block][k] (fixed order), k < nslots: a wave
+// per slot, every lane's loads in flight together.  (One workgroup slot after slot, two
+// barriers each, took longer than the lattice takes to read at L = 64.)
+constexpr int kFinishThreads = 1024;
+static_assert(kFinishThreads / 64 >= 15, "a wave per slot");
+__global__ __launch_bounds__(kFinishThreads) void finish_reduce_kernel(const double* partials,
                                                                        int32_t nblocks,
                                                                        int32_t nslots,
                                                                        double scale, double* out) {
-  __shared__ double part[kReduceThreads / 64];
-  for (int k = 0; k < nslots; ++k) {
-    double acc = 0.0;
-    for (int32_t i = (int32_t)threadIdx.x; i < nblocks; i += kReduceThreads)
-      acc += partials[(int64_t)i * kReduceSlots + k];
-    const double s = wave_sum(acc);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      double tot = 0.0;
-      for (int w = 0; w < kReduceThreads / 64; ++w) tot += part[w];
-      out[k] = scale * tot;
-    }
-    __syncthreads();
+  const int lane = threadIdx.x & 63, k = threadIdx.x >> 6;
+  if (k >= nslots) return;
+  double v[kReduceBlocks / 64];
+#pragma unroll
+  for (int r = 0; r < kReduceBlocks / 64; ++r) {
+    const int32_t i = lane + 64 * r;
+    v[r] = i < nblocks ? partials[(int64_t)i * kReduceSlots + k] : 0.0;
   }
+  double acc = 0.0;
+#pragma unroll
+  for (int r = 0; r < kReduceBlocks / 64; ++r) acc += v[r];
+  const double s = wave_sum(acc);
+  if (lane == 0) out[k] = scale * s;
 }
 
 __global__ void zero_kernel(double* p, int64_t n) {
@@ -204,10 +204,11 @@ template <typename R>
 hipError_t launch_energy(int32_t L, const void* spins, const void* J, double* partials,
                          double* out, hipStream_t stream) {
   const int64_t Nh = (int64_t)L * L * L / 2;
-  const unsigned nb = reduce_grid(Nh);
-  hipLaunchKernelGGL(energy_kernel<R>, dim3(nb), dim3(kReduceThreads), 0, stream, L,
-                     (const R*)spins, (const R*)J, partials);
-  hipLaunchKernelGGL(finish_reduce_kernel, dim3(1), dim3(kReduceThreads), 0, stream,
+  const Geometry g = pass_geometry(L);
+  const unsigned nb = (unsigned)(g.n_blocks < kReduceBlocks ? g.n_blocks : kReduceBlocks);
+  hipLaunchKernelGGL(energy_kernel<R>, dim3(nb), dim3(kReduceThreads), 0, stream, g,
+                     planes_of<R>((void*)spins, Nh), planes_of<R>((void*)J, Nh), partials);
+  hipLaunchKernelGGL(finish_reduce_kernel, dim3(1), dim3(kFinishThreads), 0, stream,
                      (const double*)partials, (int32_t)nb, 1, -1.0, out);
   return hipGetLastError();
 }
@@ -219,7 +220,7 @@ hipError_t launch_overlap(int32_t L, const void* a, const void* b, double* parti
   const unsigned nb = reduce_grid(N);
   hipLaunchKernelGGL(overlap_kernel<R>, dim3(nb), dim3(kReduceThreads), 0, stream, N,
                      (const R*)a, (const R*)b, partials);
-  hipLaunchKernelGGL(finish_reduce_kernel, dim3(1), dim3(kReduceThreads), 0, stream,
+  hipLaunchKernelGGL(finish_reduce_kernel, dim3(1), dim3(kFinishThreads), 0, stream,
                      (const double*)partials, (int32_t)nb, 15, 1.0 / (double)N, out);
   return hipGetLastError();
 }

@@ -233,15 +233,13 @@ __device__ __forceinline__ void block_totals(const double (&acc)[kFourierSums], 
 // The 65-value record from the 63 totals (shared memory) and 1/N.
 __device__ __forceinline__ void write_record(const double* sums, double inv_n, double* out) {
   if (threadIdx.x < kFourierSums) out[threadIdx.x] = sums[threadIdx.x] * inv_n;
-  if (threadIdx.x == 64) {
-    double q2 = 0.0;
-    for (int k = 0; k < 9; ++k) q2 = fma(sums[k] * inv_n, sums[k] * inv_n, q2);
-    out[63] = q2;
-  }
-  if (threadIdx.x == 128) {
-    double q2 = 0.0;
-    for (int k = 9; k < kFourierSums; ++k) q2 = fma(sums[k] * inv_n, sums[k] * inv_n, q2);
-    out[64] = q2 / 3.0;
+  // q2(0) by wave 1, q2(k_min) by wave 2: a lane per component, then the wave's sum
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (wave == 1 || wave == 2) {
+    const bool mine = wave == 1 ? lane < 9 : lane >= 9 && lane < kFourierSums;
+    const double v = mine ? sums[lane] * inv_n : 0.0;
+    const double q2 = wave_sum(v * v);
+    if (lane == 0) out[62 + wave] = wave == 1 ? q2 : q2 / 3.0;
   }
 }
 
