@@ -99,6 +99,18 @@ extern "C" {
                                nearest this GPU has to the texture path of the TEXT variant.
                                Not with HSG_FUSED */
 
+#define HSG_BRICK 2048     /* small lattices, several colour passes per launch.  L <= 14 (10
+                               in binary64): all sweeps of the call in one launch (of up to
+                               4096), one workgroup holding the lattice.  Up to L =
+                               HSG_BRICK_MAX_L (40 in binary64): a launch per phase, each
+                               workgroup holding some rows of the lattice and those around
+                               them in LDS; uses the second spin array of the work buffer.
+                               Ignored for larger L, and where the work buffer has no second
+                               array; HSG_EINVAL with any flag but HSG_HEAT_BATH and
+                               HSG_SNAKE, and in hsg_sweep_noalloc.  Spins as always; the
+                               binary64 energy changes are summed in another fixed order */
+#define HSG_BRICK_MAX_L 64
+
 typedef struct hsg_lattice {
   int32_t L;         /* even, 2 <= L <= HSG_L_MAX */
   int32_t dtype;     /* HSG_F32 or HSG_F64 */
@@ -119,7 +131,7 @@ typedef struct hsg_sweep_params {
                            divided by its length; 0 = never */
   int32_t flags;        /* OR of HSG_HEAT_BATH, HSG_SNAKE, HSG_FUSED, HSG_MARCH_PHASE,
                            HSG_PLANE_LAUNCH, HSG_STREAM_LOADS, HSG_PHASE_LAUNCH,
-                           HSG_PHASE_MC */
+                           HSG_PHASE_MC, HSG_BRICK */
 } hsg_sweep_params;
 
 /* Sizes of the three device buffers of an L^3 lattice of the given dtype.  Any
@@ -175,7 +187,7 @@ int hsg_sweep_noalloc(hsg_lattice *lat, const hsg_sweep_params *p, int32_t n_swe
 #define HSG_LAUNCH_OR_PHASE 3     /* over-relaxation phase in one launch (HSG_PHASE_LAUNCH) */
 #define HSG_LAUNCH_OR_PHASE_MC 4  /* the same carrying the next colour-0 Monte Carlo pass
                                      (HSG_PHASE_MC) */
-#define HSG_LAUNCH_MARCH 5        /* fused passes (HSG_FUSED) */
+#define HSG_LAUNCH_MARCH 5        /* fused passes (HSG_FUSED, HSG_BRICK) */
 
 /* Measurement form of hsg_sweep: the same sweeps (same arguments, same results), with a
  * pair of HIP events recorded on `stream` around each of the call's first `capacity`

@@ -32,12 +32,14 @@ HSG_PLANE_LAUNCH = 32
 HSG_STREAM_LOADS = 64
 HSG_PHASE_LAUNCH = 128
 HSG_PHASE_MC = 256
+HSG_BRICK = 2048
 # launch kinds reported by hsg_sweep_timed
 LAUNCH_OTHER, LAUNCH_MC_PASS, LAUNCH_OR_PASS, LAUNCH_OR_PHASE, LAUNCH_OR_PHASE_MC, \
     LAUNCH_MARCH = range(6)
 LAUNCH_NAMES = ("other", "mc_pass", "or_pass", "or_phase", "or_phase_mc", "march")
 FUSED_MIN_L, FUSED_MAX_L = 256, 1024
 PHASE_MIN_L, PHASE_MAX_L = 64, 1024
+BRICK_MAX_L, BRICK_MAX_L_F64 = 64, 40
 FOURIER_VALUES = 65
 L_MAX = 1290
 
@@ -54,14 +56,17 @@ def phase_supported(L: int) -> bool:
 
 
 def default_flags(L: int, dtype=None) -> int:
-    """Traversal flags of a sweep that names none: Monte Carlo passes one launch each in
-    alternating z order, over-relaxation phases as one launch each where the lattice
-    gives that launch enough workgroups (L >= 256) -- in binary32 with the next sweep's
-    colour-0 Monte Carlo pass in the same launch -- which measures fastest on MI355X
-    (HSG_FUSED is opt-in).  Spins are the same either way."""
+    """Traversal flags of a sweep that names none: several colour passes per launch on small
+    lattices (L <= 64, in binary64 40); Monte Carlo passes one launch each in alternating z
+    order, over-relaxation phases as one launch each where the lattice gives that launch
+    enough workgroups (L >= 256) -- in binary32 with the next sweep's colour-0 Monte Carlo
+    pass in the same launch -- which measures fastest on MI355X (HSG_FUSED is opt-in).
+    Spins are the same either way."""
+    f64 = dtype is not None and str(dtype) in ("torch.float64", "float64")
+    if L <= (BRICK_MAX_L_F64 if f64 else BRICK_MAX_L):
+        return HSG_SNAKE | HSG_BRICK
     if not (L >= 256 and phase_supported(L)):
         return HSG_SNAKE
-    f64 = dtype is not None and str(dtype) in ("torch.float64", "float64")
     return HSG_SNAKE | (HSG_PHASE_LAUNCH if f64 else HSG_PHASE_MC)
 
 

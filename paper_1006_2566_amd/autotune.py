@@ -19,7 +19,7 @@ from typing import Callable, Iterable
 
 import torch
 
-from . import (HSG_FUSED, HSG_PHASE_LAUNCH, HSG_PHASE_MC, HSG_SNAKE, Lattice, fused_supported,
+from . import (BRICK_MAX_L, BRICK_MAX_L_F64, HSG_BRICK, HSG_FUSED, HSG_PHASE_LAUNCH, HSG_PHASE_MC, HSG_SNAKE, Lattice, fused_supported,
                phase_supported)
 
 CACHE_ENV = "HSG_AUTOTUNE_CACHE"
@@ -93,8 +93,9 @@ def sweep_flags(L: int, dtype: torch.dtype = torch.float32, k: int = 4, n_or: in
                 retune: bool = False, path: str | None = None) -> int:
     """Traversal flags for hsg_sweep on an L^3 lattice: plain order, alternating z
     order (HSG_SNAKE), over-relaxation phases in one launch each (HSG_PHASE_LAUNCH), the
-    same with the next sweep's colour-0 Monte Carlo pass in that launch (HSG_PHASE_MC) or
-    fused passes (HSG_FUSED), where the lattice allows them."""
+    same with the next sweep's colour-0 Monte Carlo pass in that launch (HSG_PHASE_MC),
+    fused passes (HSG_FUSED) or the small lattices' launches of several passes (HSG_BRICK),
+    where the lattice allows them."""
     cands = [0, HSG_SNAKE]
     if n_or > 0 and phase_supported(L):
         cands.append(HSG_SNAKE | HSG_PHASE_LAUNCH)
@@ -102,6 +103,9 @@ def sweep_flags(L: int, dtype: torch.dtype = torch.float32, k: int = 4, n_or: in
             cands.append(HSG_SNAKE | HSG_PHASE_MC)
     if fused_supported(L):
         cands.append(HSG_FUSED)
+    small = L <= (BRICK_MAX_L if dtype == torch.float32 else BRICK_MAX_L_F64)
+    if small and not phase_supported(L):
+        cands.append(HSG_SNAKE | HSG_BRICK)
     key = f"sweep L={L} {str(dtype).replace('torch.', '')} k={k} n_or={n_or} hb={int(heat_bath)}"
     best: dict = {}
 

@@ -96,7 +96,7 @@ int check_params(const hsg_sweep_params* p) {
     return fail(HSG_EINVAL, "k_hits must be < 65536 and n_or < 32768");
   if (p->renorm_every < 0) return fail(HSG_EINVAL, "renorm_every must be >= 0");
   if (p->flags & ~(HSG_HEAT_BATH | HSG_SNAKE | HSG_FUSED | HSG_MARCH_PHASE | HSG_PLANE_LAUNCH |
-                   HSG_STREAM_LOADS | HSG_PHASE_LAUNCH | HSG_PHASE_MC))
+                   HSG_STREAM_LOADS | HSG_PHASE_LAUNCH | HSG_PHASE_MC | HSG_BRICK))
     return fail(HSG_EINVAL, "unknown flags 0x%x", (unsigned)p->flags);
   if ((p->flags & HSG_MARCH_PHASE) && !(p->flags & HSG_FUSED))
     return fail(HSG_EINVAL, "HSG_MARCH_PHASE needs HSG_FUSED");
@@ -104,6 +104,8 @@ int check_params(const hsg_sweep_params* p) {
       (p->flags & (HSG_PLANE_LAUNCH | HSG_STREAM_LOADS | HSG_PHASE_LAUNCH | HSG_PHASE_MC)))
     return fail(HSG_EINVAL, "HSG_PLANE_LAUNCH, HSG_STREAM_LOADS, HSG_PHASE_LAUNCH and HSG_PHASE_MC "
                             "apply to the pass-by-pass schedule, not to HSG_FUSED");
+  if ((p->flags & HSG_BRICK) && (p->flags & ~(HSG_HEAT_BATH | HSG_SNAKE | HSG_BRICK)))
+    return fail(HSG_EINVAL, "HSG_BRICK goes with HSG_HEAT_BATH and HSG_SNAKE only");
   return HSG_OK;
 }
 
@@ -307,6 +309,104 @@ int sweep_fused(hsg_lattice* lat, const hsg_sweep_params* p, int32_t n_sweeps, h
   return HSG_OK;
 }
 
+// HSG_BRICK, tiny_supported: the sweeps of the call in launches of one workgroup.
+constexpr int32_t kTinySweeps = 4096;  // of a launch: some ten milliseconds
+template <typename R>
+int sweep_tiny(hsg_lattice* lat, const hsg_sweep_params* p, int32_t n_sweeps, hipStream_t st) {
+  using namespace hsg;
+  TinyArgs<R> a{};
+  a.spins = (R*)lat->spins;
+  a.J = (const R*)lat->J;
+  a.E = lat->E;
+  a.beta = (R)(1.0 / p->T);
+  a.seed_lo = (uint32_t)lat->seed;
+  a.seed_hi = (uint32_t)(lat->seed >> 32);
+  a.k_hits = p->k_hits;
+  a.n_or = p->n_or;
+  a.renorm_every = p->renorm_every;
+  a.L = lat->L;
+  const PassMode mc = (p->flags & HSG_HEAT_BATH) ? PassMode::HeatBath : PassMode::Metropolis;
+  for (int32_t n = 0; n < n_sweeps; n += a.n_sweeps) {
+    a.sweep = (uint32_t)(lat->sweep + (uint64_t)n);
+    a.n_sweeps = std::min(kTinySweeps, n_sweeps - n);
+    int rc = device_status(
+        recorded(HSG_LAUNCH_MARCH, st, [&] { return launch_tiny<R>(a, mc, st); }), "sweeps");
+    if (rc) return rc;
+  }
+  return HSG_OK;
+}
+
+// HSG_BRICK, larger lattices: a launch per phase (its colour-0 and colour-1 passes), each
+// reading one spin array and writing the other; with an odd number of phases the call's
+// last one runs as two colour passes in place.  Renormalisation is done on the way out of a
+// sweep's last phase.
+template <typename R>
+int sweep_brick(hsg_lattice* lat, const hsg_sweep_params* p, int32_t n_sweeps, hipStream_t st,
+                double* partials) {
+  using namespace hsg;
+  const int32_t first = p->k_hits > 0 ? 0 : 1;       // first phase of a sweep
+  const int32_t per = p->n_or + 1 - first;           // phases of a sweep
+  const int64_t total = (int64_t)n_sweeps * per;
+  const PassMode mc = (p->flags & HSG_HEAT_BATH) ? PassMode::HeatBath : PassMode::Metropolis;
+  R* bufs[2] = {(R*)lat->spins, (R*)((char*)lat->work + fused_offset(lat->L))};
+  int cur = 0;
+  BrickArgs<R> a{};
+  a.J = (const R*)lat->J;
+  a.partials = partials;
+  a.beta = (R)(1.0 / p->T);
+  a.seed_lo = (uint32_t)lat->seed;
+  a.seed_hi = (uint32_t)(lat->seed >> 32);
+  a.k_hits = p->k_hits;
+  a.L = lat->L;
+  const bool last_plain = (total & 1) != 0;
+  for (int64_t g = 0; g < total - (last_plain ? 1 : 0); ++g) {
+    const uint64_t sweep = lat->sweep + (uint64_t)(g / per);
+    const int32_t phase = first + (int32_t)(g % per);
+    a.sweep = (uint32_t)sweep;
+    a.phase = (uint32_t)phase;
+    a.renorm = phase == p->n_or && renorm_due(p, sweep);
+    a.in = bufs[cur];
+    a.out = bufs[1 - cur];
+    int rc = device_status(
+        recorded(HSG_LAUNCH_MARCH, st,
+                 [&] { return launch_brick<R>(a, phase == 0 ? mc : PassMode::OverRelax, st); }),
+        "phase");
+    if (rc) return rc;
+    cur = 1 - cur;
+  }
+  if (last_plain) {
+    const int64_t Nh = (int64_t)lat->L * lat->L * lat->L / 2;
+    const uint64_t sweep = lat->sweep + (uint64_t)n_sweeps - 1;
+    PassArgs<R> b{};
+    b.spins = planes_of<R>(lat->spins, Nh);
+    b.J = planes_of<R>(lat->J, Nh);
+    b.partials = partials;
+    b.beta = a.beta;
+    b.seed_lo = a.seed_lo;
+    b.seed_hi = a.seed_hi;
+    b.sweep = (uint32_t)sweep;
+    b.phase = (uint32_t)p->n_or;
+    b.k_hits = p->k_hits;
+    b.g = pass_geometry(lat->L);
+    b.tile_count = b.g.n_blocks;
+    const PassMode mode = p->n_or == 0 ? mc : PassMode::OverRelax;
+    for (b.colour = 0; b.colour < 2; ++b.colour) {
+      int rc = device_status(
+          recorded(mode == PassMode::OverRelax ? HSG_LAUNCH_OR_PASS : HSG_LAUNCH_MC_PASS, st,
+                   [&] { return launch_colour_pass<R>(mode, b, st); }),
+          "colour pass");
+      if (rc) return rc;
+    }
+    if (renorm_due(p, sweep)) {
+      int rc = device_status(recorded(HSG_LAUNCH_OTHER, st,
+                                      [&] { return launch_renormalise<R>(lat->L, lat->spins, 2, st); }),
+                             "renormalise");
+      if (rc) return rc;
+    }
+  }
+  return HSG_OK;
+}
+
 bool use_fused(const hsg_lattice* lat, const hsg_sweep_params* p) {
   return (p->flags & HSG_FUSED) && hsg::march_supported(lat->L);
 }
@@ -317,14 +417,21 @@ template <typename R>
 int sweep_impl(hsg_lattice* lat, const hsg_sweep_params* p, int32_t n_sweeps, hipStream_t st,
                double* partials) {
   using namespace hsg;
-  int rc = use_fused(lat, p) ? sweep_fused<R>(lat, p, n_sweeps, st)
-                             : sweep_plain<R>(lat, p, n_sweeps, st, partials);
+  if ((p->flags & HSG_BRICK) && tiny_supported(lat->L, (int32_t)sizeof(R)))
+    return sweep_tiny<R>(lat, p, n_sweeps, st);
+  BrickPlan plan;
+  const bool brick = (p->flags & HSG_BRICK) && brick_plan(lat->L, (int32_t)sizeof(R), &plan) &&
+                     lat->work_bytes >= work_bytes_for(lat->L, (int32_t)sizeof(R));
+  int rc = brick ? sweep_brick<R>(lat, p, n_sweeps, st, partials)
+           : use_fused(lat, p) ? sweep_fused<R>(lat, p, n_sweeps, st)
+                               : sweep_plain<R>(lat, p, n_sweeps, st, partials);
   if (rc) return rc;
   if (n_sweeps > 0 && p->k_hits > 0) {
     rc = device_status(recorded(HSG_LAUNCH_OTHER, st,
                                 [&] {
                                   return launch_fold_partials(partials,
-                                                              pass_geometry(lat->L).n_blocks,
+                                                              brick ? pass_geometry(lat->L).n_partials
+                                                                    : pass_geometry(lat->L).n_blocks,
                                                               lat->E, st);
                                 }),
                        "fold");
@@ -337,7 +444,7 @@ int sweep_impl(hsg_lattice* lat, const hsg_sweep_params* p, int32_t n_sweeps, hi
 template <typename R>
 int reset_energy(hsg_lattice* lat, hipStream_t st) {
   using namespace hsg;
-  int rc = device_status(launch_zero(pass_partials(lat->work), pass_geometry(lat->L).n_blocks, st),
+  int rc = device_status(launch_zero(pass_partials(lat->work), pass_geometry(lat->L).n_partials, st),
                          "clear scratch");
   if (rc) return rc;
   return device_status(launch_energy<R>(lat->L, lat->spins, lat->J,
@@ -509,10 +616,10 @@ int hsg_sweep_noalloc(hsg_lattice* lat, const hsg_sweep_params* p, int32_t n_swe
                 HSG_NOALLOC_L_MAX);
   rc = check_params(p);
   if (rc) return rc;
-  if (p->flags & (HSG_FUSED | HSG_MARCH_PHASE | HSG_PHASE_LAUNCH | HSG_PHASE_MC))
+  if (p->flags & (HSG_FUSED | HSG_MARCH_PHASE | HSG_PHASE_LAUNCH | HSG_PHASE_MC | HSG_BRICK))
     return fail(HSG_EINVAL, "hsg_sweep_noalloc runs the pass-by-pass schedule: HSG_FUSED, "
-                            "HSG_MARCH_PHASE, HSG_PHASE_LAUNCH and HSG_PHASE_MC need a second "
-                            "spin array");
+                            "HSG_MARCH_PHASE, HSG_PHASE_LAUNCH, HSG_PHASE_MC and HSG_BRICK need "
+                            "a second spin array");
   if (n_sweeps < 0) return fail(HSG_EINVAL, "n_sweeps must be >= 0");
   if (lat->sweep + (uint64_t)n_sweeps > 0x100000000ull)
     return fail(HSG_EINVAL, "sweep index would pass 2^32");

@@ -19,6 +19,7 @@ struct Geometry {
   int32_t tiles_p;    // tiles of a plane
   int32_t slab;       // planes per launch of HSG_PLANE_LAUNCH
   int32_t n_blocks;   // tiles of a pass: tiles_p * L
+  int32_t n_partials; // energy partials of a lattice: tiles of a pass, or bricks
   uint32_t inv_lh;    // ceil(2^32 / Lh) (0 for Lh = 1): see SmallDiv
   uint32_t inv_tp;    // floor(2^32 / tiles_p) (0 for one tile)
 };
@@ -38,7 +39,7 @@ static_assert(kFourierBlocks <= kReduceBlocks && kReduceSlots <= kFourierSlots,
 
 // Scratch layout of hsg_lattice.work (bytes):
 //   [0, 256)                              reserved
-//   [256, 256 + 8*n_blocks)               per-tile energy-change partials of the passes
+//   [256, 256 + 8*n_partials)             per-tile energy-change partials of the passes
 //   [.., + 8*kReduceRegion)               per-block partials of energy / overlaps
 //   [fused_offset(L), + 3*N*sizeof(R))    second spin array of fused and phase launches
 //                                         (only for L that march_supported or
@@ -48,7 +49,7 @@ size_t fused_offset(int32_t L);    // 256-byte aligned end of the above
 size_t work_bytes_for(int32_t L, int32_t dtype_bytes);  // with it where it applies
 inline double* pass_partials(void* work) { return (double*)((char*)work + 256); }
 inline double* reduce_partials(void* work, int32_t L) {
-  return pass_partials(work) + pass_geometry(L).n_blocks;
+  return pass_partials(work) + pass_geometry(L).n_partials;
 }
 
 // Pointers of the six planes (3 components x 2 colours) of a colour-split array.
@@ -164,6 +165,48 @@ int32_t march_max_stages();
 // n_stages consecutive passes (2, or 4 in binary32) described by a.st.
 template <typename R>
 hipError_t launch_march(const MarchArgs<R>& a, int32_t n_stages, hipStream_t stream);
+
+// Small lattices: several colour passes per launch (kernels_brick.hip).
+constexpr int kBrickMaxL = 64;
+// One workgroup holds a lattice of that size and element size.
+bool tiny_supported(int32_t L, int32_t elem);
+
+template <typename R>
+struct BrickArgs {
+  const R* in;       // colour-split spins before the launch
+  R* out;            // after it (distinct from in)
+  const R* J;
+  double* partials;  // one per workgroup, energy changes of its own sites are added
+  R beta;
+  uint32_t seed_lo, seed_hi;
+  uint32_t sweep, phase;  // Philox counter words
+  int32_t k_hits;
+  int32_t L;
+  int32_t renorm;    // divide every spin by its length after the phase
+  int32_t n[2];      // bricks along y and z: set by launch_brick
+  uint32_t inv[2];
+};
+
+struct BrickPlan {
+  int32_t n[2];
+  int32_t lds;  // which LDS size
+};
+// The bricks of an L^3 lattice; false if there are none.
+bool brick_plan(int32_t L, int32_t elem, BrickPlan* plan);
+template <typename R>
+hipError_t launch_brick(const BrickArgs<R>& a, PassMode mode, hipStream_t stream);
+
+template <typename R>
+struct TinyArgs {
+  R* spins;  // colour-split, updated in place
+  const R* J;
+  double* E;  // tracked energy, advanced
+  R beta;
+  uint32_t seed_lo, seed_hi, sweep;
+  int32_t k_hits, n_or, renorm_every, n_sweeps, L;
+};
+template <typename R>
+hipError_t launch_tiny(const TinyArgs<R>& a, PassMode mc, hipStream_t stream);
 
 // *E += sum of the n partials (fixed order); the partials are then zeroed.
 hipError_t launch_fold_partials(double* partials, int32_t n, double* E, hipStream_t stream);

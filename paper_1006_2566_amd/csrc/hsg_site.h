@@ -127,102 +127,157 @@ struct HitCtx {
   uint32_t seed_lo, seed_hi;
 };
 
-// The update of one site given its spin s and local field h (eq. 2): reflection about
-// h (over-relaxation), or k Metropolis hits / heat-bath draws with h fixed.  s is
-// replaced in place; returns the sum of the accepted energy changes.
+// Draws of a Monte Carlo update that need neither the site's spin nor its field.
 //
 // Uniforms: the site's stream in a phase is the words of the Philox blocks b = 0, 1,
 // ... with counter (sweep, site, phase << 16 | b, tag), in word order.  Metropolis hit
 // j takes uniforms 3j, 3j+1, 3j+2 (polar, azimuth, acceptance), heat-bath draw j takes
 // 2j, 2j+1: four hits share three blocks, two draws one block.  The hits are taken in
-// such groups.  A hit's draws, trial spin and trial energy do not depend on earlier
-// decisions, only its accept/reject step does; with G > 1 a group's trials are formed
-// first (instruction-level parallelism for a wave with few neighbours on its SIMD),
-// then its decisions in order.  Every operation and the order of the energy sum are
-// the same for any G.  A heat-bath draw is always taken and does not depend on the spin
+// such groups (kHits).  A heat-bath draw is always taken and does not depend on the spin
 // it replaces, so of k draws only the last counts and only that one is computed.
-template <typename R, PassMode MODE, int G = 1>
-__device__ __forceinline__ double apply_update(Vec3<R>& s, const Vec3<R>& h, uint32_t site,
-                                               const HitCtx<R>& hc) {
-  double dE_sum = 0.0;
-  if constexpr (MODE == PassMode::OverRelax) {
-    s = reflect(s, h);
-  } else if constexpr (MODE == PassMode::HeatBath) {
-    const uint32_t j = (uint32_t)hc.k_hits - 1u;  // the last draw: uniforms 2j, 2j + 1
-    const Word4 x = philox10(hc.sweep, site, (hc.phase << 16) | (j >> 1), kTagHeatBath,
-                             hc.seed_lo, hc.seed_hi);
-    const uint32_t w0 = (j & 1u) ? x.w2 : x.w0, w1 = (j & 1u) ? x.w3 : x.w1;
-    const Vec3<R> t = heat_bath_point(h, hc.beta, unit_uniform<R>(w0), unit_uniform<R>(w1));
-    const R dE = dot3(s, h) - dot3(t, h);
-    s = t;
-    dE_sum = (double)dE;
+constexpr int kHits = 4;
+template <typename R, PassMode MODE>
+struct Draws {
+  Vec3<R> trial[kHits];  // trial points of a group of Metropolis hits
+  R u[kHits];            // their acceptance uniforms
+};
+template <typename R>
+struct Draws<R, PassMode::OverRelax> {};
+template <typename R>
+struct Draws<R, PassMode::HeatBath> {
+  uint32_t w0, w1;
+};
+
+// The words of Metropolis group b0 / 3 (nh >= 1 hits of it taken).
+template <bool FULL, typename R>
+__device__ __forceinline__ void hit_words(uint32_t (&w)[3 * kHits], uint32_t site, uint32_t b0,
+                                          int32_t nh, const HitCtx<R>& hc) {
+  constexpr int NB = 3;  // Philox blocks per group
+  if (FULL) {
+    // a full group: its NB blocks advanced together (philox10_n)
+    uint32_t c2[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) c2[i] = (hc.phase << 16) | (b0 + (uint32_t)i);
+    Word4 x[NB];
+    philox10_n<NB>(hc.sweep, site, c2, kTagMetropolis, hc.seed_lo, hc.seed_hi, x);
+    // all words complete here (an empty statement that takes them as operands):
+    // without it each block's rounds would be sunk to its first use, behind the
+    // previous hit's decision, one chain at a time again
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+      asm volatile("" : "+v"(x[i].w0), "+v"(x[i].w1), "+v"(x[i].w2), "+v"(x[i].w3));
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      w[4 * i] = x[i].w0;
+      w[4 * i + 1] = x[i].w1;
+      w[4 * i + 2] = x[i].w2;
+      w[4 * i + 3] = x[i].w3;
+    }
   } else {
-    constexpr uint32_t tag = kTagMetropolis;
-    constexpr int U = 3;             // uniforms per hit
-    constexpr int H = 4;             // hits per group
-    constexpr int NB = U * H / 4;    // Philox blocks per group
-    // every group complete (k_hits a multiple of four): no per-group conditions
-    constexpr bool kFull = MODE == PassMode::MetropolisFull;
-    R sh = dot3(s, h);
-    uint32_t b0 = 0;
-    for (int32_t j0 = 0; j0 < hc.k_hits; j0 += H, b0 += NB) {
-      const int32_t nh = hc.k_hits - j0;  // hits left (the group takes min(H, nh))
-      uint32_t w[4 * NB];
-      auto block = [&](int i) {
-        const Word4 x = philox10(hc.sweep, site, (hc.phase << 16) | (b0 + (uint32_t)i), tag,
-                                 hc.seed_lo, hc.seed_hi);
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+      if (i == 0 || 4 * i < 3 * nh) {
+        const Word4 x = philox10(hc.sweep, site, (hc.phase << 16) | (b0 + (uint32_t)i),
+                                 kTagMetropolis, hc.seed_lo, hc.seed_hi);
         w[4 * i] = x.w0;
         w[4 * i + 1] = x.w1;
         w[4 * i + 2] = x.w2;
         w[4 * i + 3] = x.w3;
-      };
-      if (kFull) {
-        // a full group: its NB blocks advanced together (philox10_n)
-        uint32_t c2[NB];
-#pragma unroll
-        for (int i = 0; i < NB; ++i) c2[i] = (hc.phase << 16) | (b0 + (uint32_t)i);
-        Word4 x[NB];
-        philox10_n<NB>(hc.sweep, site, c2, tag, hc.seed_lo, hc.seed_hi, x);
-        // all words complete here (an empty statement that takes them as operands):
-        // without it each block's rounds would be sunk to its first use, behind the
-        // previous hit's decision, one chain at a time again
-#pragma unroll
-        for (int i = 0; i < NB; ++i)
-          asm volatile("" : "+v"(x[i].w0), "+v"(x[i].w1), "+v"(x[i].w2), "+v"(x[i].w3));
-#pragma unroll
-        for (int i = 0; i < NB; ++i) {
-          w[4 * i] = x[i].w0;
-          w[4 * i + 1] = x[i].w1;
-          w[4 * i + 2] = x[i].w2;
-          w[4 * i + 3] = x[i].w3;
-        }
-      } else {
-#pragma unroll
-        for (int i = 0; i < NB; ++i)
-          if (i == 0 || 4 * i < U * nh) block(i);
       }
-      (void)nh;
-      Vec3<R> trial[H];
-      R th[H], u2[H];
+  }
+}
+
+// The first group's draws of a site.
+template <typename R, PassMode MODE>
+__device__ __forceinline__ Draws<R, MODE> first_draws(uint32_t site, const HitCtx<R>& hc) {
+  Draws<R, MODE> d;
+  if constexpr (MODE == PassMode::HeatBath) {
+    const uint32_t j = (uint32_t)hc.k_hits - 1u;  // the last draw: uniforms 2j, 2j + 1
+    const Word4 x = philox10(hc.sweep, site, (hc.phase << 16) | (j >> 1), kTagHeatBath,
+                             hc.seed_lo, hc.seed_hi);
+    d.w0 = (j & 1u) ? x.w2 : x.w0;
+    d.w1 = (j & 1u) ? x.w3 : x.w1;
+  } else if constexpr (MODE != PassMode::OverRelax) {
+    constexpr bool kFull = MODE == PassMode::MetropolisFull;
+    uint32_t w[3 * kHits];
+    hit_words<kFull>(w, site, 0u, hc.k_hits, hc);
+#pragma unroll
+    for (int g = 0; g < kHits; ++g)
+      if (kFull || g < hc.k_hits) {
+        d.trial[g] = sphere_point_words<R>(w[3 * g], w[3 * g + 1]);
+        d.u[g] = unit_uniform<R>(w[3 * g + 2]);
+      }
+  }
+  return d;
+}
+
+// One Metropolis decision: sh = s.h of the current spin.
+template <typename R>
+__device__ __forceinline__ void decide_hit(Vec3<R>& s, R& sh, double& dE_sum, const Vec3<R>& trial,
+                                           R th, R u, R beta) {
+  const R dE = sh - th;
+  // both conditions formed for every trial: a wave has lanes that need the second
+  // one in almost every hit, and a branch around it cost more than it skipped
+  const bool accept = (dE <= (R)0) | (u < accept_prob(-beta * dE));
+  if (accept) {
+    s = trial;
+    sh = th;
+    dE_sum += (double)dE;
+  }
+}
+
+// The update of one site given its spin s and local field h (eq. 2): reflection about
+// h (over-relaxation), or k Metropolis hits / heat-bath draws with h fixed.  s is
+// replaced in place; returns the sum of the accepted energy changes.
+//
+// A hit's draws, trial spin and trial energy do not depend on earlier decisions, only its
+// accept/reject step does; with G > 1 a group's trials are formed first (instruction-level
+// parallelism for a wave with few neighbours on its SIMD), then its decisions in order;
+// with `first` the first group's draws were made before the field was known.  Every
+// operation and the order of the energy sum are the same for any of these.
+template <typename R, PassMode MODE, int G = 1>
+__device__ __forceinline__ double apply_update(Vec3<R>& s, const Vec3<R>& h, uint32_t site,
+                                               const HitCtx<R>& hc,
+                                               const Draws<R, MODE>* first = nullptr) {
+  double dE_sum = 0.0;
+  if constexpr (MODE == PassMode::OverRelax) {
+    s = reflect(s, h);
+  } else if constexpr (MODE == PassMode::HeatBath) {
+    const Draws<R, MODE> d = first ? *first : first_draws<R, MODE>(site, hc);
+    const Vec3<R> t = heat_bath_point(h, hc.beta, unit_uniform<R>(d.w0), unit_uniform<R>(d.w1));
+    const R dE = dot3(s, h) - dot3(t, h);
+    s = t;
+    dE_sum = (double)dE;
+  } else {
+    // every group complete (k_hits a multiple of four): no per-group conditions
+    constexpr bool kFull = MODE == PassMode::MetropolisFull;
+    R sh = dot3(s, h);
+    int32_t j0 = 0;
+    uint32_t b0 = 0;
+    if (first) {
+#pragma unroll
+      for (int g = 0; g < kHits; ++g)
+        if (kFull || g < hc.k_hits)
+          decide_hit(s, sh, dE_sum, first->trial[g], dot3(first->trial[g], h), first->u[g],
+                     hc.beta);
+      j0 = kHits;
+      b0 = 3;
+    }
+    for (; j0 < hc.k_hits; j0 += kHits, b0 += 3) {
+      const int32_t nh = hc.k_hits - j0;  // hits left (the group takes min(kHits, nh))
+      uint32_t w[3 * kHits];
+      hit_words<kFull>(w, site, b0, nh, hc);
+      Vec3<R> trial[kHits];
+      R th[kHits], u[kHits];
       auto draw = [&](int g) {
-        trial[g] = sphere_point_words<R>(w[U * g], w[U * g + 1]);
-        u2[g] = unit_uniform<R>(w[U * g + 2]);
+        trial[g] = sphere_point_words<R>(w[3 * g], w[3 * g + 1]);
+        u[g] = unit_uniform<R>(w[3 * g + 2]);
         th[g] = dot3(trial[g], h);
       };
-      auto decide = [&](int g) {
-        const R dE = sh - th[g];
-        // both conditions formed for every trial: a wave has lanes that need the second
-        // one in almost every hit, and a branch around it cost more than it skipped
-        const bool accept = (dE <= (R)0) | (u2[g] < accept_prob(-hc.beta * dE));
-        if (accept) {
-          s = trial[g];
-          sh = th[g];
-          dE_sum += (double)dE;
-        }
-      };
+      auto decide = [&](int g) { decide_hit(s, sh, dE_sum, trial[g], th[g], u[g], hc.beta); };
       if constexpr (G == 1) {
 #pragma unroll
-        for (int g = 0; g < H; ++g) {
+        for (int g = 0; g < kHits; ++g) {
           if (kFull || g < nh) {
             draw(g);
             decide(g);
@@ -230,10 +285,10 @@ __device__ __forceinline__ double apply_update(Vec3<R>& s, const Vec3<R>& h, uin
         }
       } else {
 #pragma unroll
-        for (int g = 0; g < H; ++g)
+        for (int g = 0; g < kHits; ++g)
           if (kFull || g < nh) draw(g);
 #pragma unroll
-        for (int g = 0; g < H; ++g)
+        for (int g = 0; g < kHits; ++g)
           if (kFull || g < nh) decide(g);
       }
     }

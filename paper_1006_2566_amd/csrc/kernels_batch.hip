@@ -379,7 +379,7 @@ __global__ __launch_bounds__(1024) void multi_pass_kernel(MultiPassArgs<R> a) {
     const double total = block_sum(dE, s_red);
     if (threadIdx.x == 0 && total != 0.0) {
       if (a.partials)
-        a.partials[t] += total;
+        atomicAdd(&a.partials[t], total);  // its only writer
       else
         atomicAdd(&a.E[ci], total);
     }

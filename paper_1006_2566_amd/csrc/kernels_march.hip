@@ -427,3 +427,5 @@ template hipError_t launch_march<float>(const MarchArgs<float>&, int32_t, hipStr
 template hipError_t launch_march<double>(const MarchArgs<double>&, int32_t, hipStream_t);
 
 }  // namespace hsg
+
+#include "kernels_brick.h"  // the small lattices' launches of several passes

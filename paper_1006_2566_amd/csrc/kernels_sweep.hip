@@ -25,19 +25,22 @@ Geometry pass_geometry(int32_t L) {
   g.tiles_p = (g.plane + kPassThreads - 1) / kPassThreads;
   g.slab = std::max(1, std::min(L, kPassThreads / std::max(64, g.plane)));
   g.n_blocks = g.tiles_p * L;
+  g.n_partials = std::max(g.n_blocks, L <= kBrickMaxL ? (L / 2) * (L / 2) : 0);
   g.inv_lh = g.Lh > 1 ? 0xFFFFFFFFu / (uint32_t)g.Lh + 1u : 0u;
   g.inv_tp = g.tiles_p > 1 ? (uint32_t)(0x100000000ull / (uint32_t)g.tiles_p) : 0u;
   return g;
 }
 
 size_t work_bytes_for(int32_t L) {
-  return 256 + sizeof(double) * ((size_t)pass_geometry(L).n_blocks + (size_t)kReduceRegion);
+  return 256 + sizeof(double) * ((size_t)pass_geometry(L).n_partials + (size_t)kReduceRegion);
 }
 
 size_t fused_offset(int32_t L) { return (work_bytes_for(L) + 255) & ~(size_t)255; }
 
 size_t work_bytes_for(int32_t L, int32_t dtype_bytes) {
-  if (!march_supported(L) && !phase_supported(L)) return work_bytes_for(L);
+  BrickPlan plan;
+  if (!march_supported(L) && !phase_supported(L) && !brick_plan(L, dtype_bytes, &plan))
+    return work_bytes_for(L);
   return fused_offset(L) + (size_t)3 * L * L * L * (size_t)dtype_bytes;
 }
 
@@ -59,7 +62,8 @@ __device__ __forceinline__ void pass_tile(const PassArgs<R>& a, uint32_t tile) {
     if ((threadIdx.x & 63) == 0) wave_part[threadIdx.x >> 6] = v;
     __syncthreads();
     if (threadIdx.x == 0)
-      a.partials[tile] += ((wave_part[0] + wave_part[1]) + (wave_part[2] + wave_part[3]));
+      atomicAdd(&a.partials[tile],  // its only writer: the sum without waiting for a load
+                ((wave_part[0] + wave_part[1]) + (wave_part[2] + wave_part[3])));
   }
 }
 
