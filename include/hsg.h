@@ -84,16 +84,17 @@ extern "C" {
 #define HSG_PHASE_LAUNCH 128 /* each over-relaxation phase -- its colour-0 and colour-1
                                passes -- runs as one launch that marches through z with a
                                window of planes in LDS, reading and writing the spins once
-                               (L a multiple of 64, 64 <= L <= 1024; else ignored: the
-                               launch indexes with 32-bit offsets up to 3 L^3).  Uses the second
-                               spin array of the work buffer.  Not with HSG_FUSED */
+                               (any even L from 98 to 1024, whose offsets fit 32 bits, and
+                               L = 64; else ignored).  Uses the second spin array of the
+                               work buffer: without one HSG_EINVAL where L is a multiple of
+                               64, ignored elsewhere.  Not with HSG_FUSED */
 #define HSG_PHASE_MC 256   /* as HSG_PHASE_LAUNCH, and when a sweep of the call is followed
                                by another (k_hits > 0), the launch of its last
                                over-relaxation phase also runs the next sweep's colour-0
                                Monte Carlo pass on each workgroup's own sites, after the
-                               phase (renormalisation between them when due).  The Monte
-                               Carlo arithmetic, which is never recomputed, hides the
-                               phase's memory traffic.  Not with HSG_FUSED */
+                               phase (renormalisation between them when due): the lattice
+                               is read and written once for the three passes.  Not with
+                               HSG_FUSED */
 #define HSG_STREAM_LOADS 64 /* couplings and the other colour's spins, which a pass only
                                reads, are loaded with the non-temporal cache hint: the
                                nearest this GPU has to the texture path of the TEXT variant.

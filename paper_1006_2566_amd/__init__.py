@@ -38,7 +38,7 @@ LAUNCH_OTHER, LAUNCH_MC_PASS, LAUNCH_OR_PASS, LAUNCH_OR_PHASE, LAUNCH_OR_PHASE_M
     LAUNCH_MARCH = range(6)
 LAUNCH_NAMES = ("other", "mc_pass", "or_pass", "or_phase", "or_phase_mc", "march")
 FUSED_MIN_L, FUSED_MAX_L = 256, 1024
-PHASE_MIN_L, PHASE_MAX_L = 64, 1024
+PHASE_MIN_L, PHASE_MAX_L = 98, 1024
 BRICK_MAX_L, BRICK_MAX_L_F64 = 64, 40
 FOURIER_VALUES = 65
 L_MAX = 1290
@@ -50,24 +50,60 @@ def fused_supported(L: int) -> bool:
 
 
 def phase_supported(L: int) -> bool:
-    """Whether HSG_PHASE_LAUNCH takes effect for an L^3 lattice (L a multiple of 64 with
-    64 <= L <= 1024: the launch's 32-bit element offsets reach 3 L^3)."""
-    return PHASE_MIN_L <= L <= PHASE_MAX_L and L % 64 == 0
+    """Whether HSG_PHASE_LAUNCH takes effect for an L^3 lattice (even L from 98 to 1024,
+    whose offsets fit 32 bits, and L = 64)."""
+    return L <= PHASE_MAX_L and ((L >= PHASE_MIN_L and L % 2 == 0) or L == 64)
 
 
 def default_flags(L: int, dtype=None) -> int:
-    """Traversal flags of a sweep that names none: several colour passes per launch on small
+    """Traversal flags by the lattice alone: several colour passes per launch on small
     lattices (L <= 64, in binary64 40); Monte Carlo passes one launch each in alternating z
-    order, over-relaxation phases as one launch each where the lattice gives that launch
-    enough workgroups (L >= 256) -- in binary32 with the next sweep's colour-0 Monte Carlo
-    pass in the same launch -- which measures fastest on MI355X (HSG_FUSED is opt-in).
-    Spins are the same either way."""
+    order, and for multiples of 64 from 256 up over-relaxation phases as one launch each --
+    in binary32 with the next sweep's colour-0 Monte Carlo pass in the same launch.
+    Spins are the same either way.  A sweep that names no flags also looks at its hits
+    (call_flags)."""
     f64 = dtype is not None and str(dtype) in ("torch.float64", "float64")
     if L <= (BRICK_MAX_L_F64 if f64 else BRICK_MAX_L):
         return HSG_SNAKE | HSG_BRICK
-    if not (L >= 256 and phase_supported(L)):
+    if not (L >= 256 and L % 64 == 0 and phase_supported(L)):
         return HSG_SNAKE
     return HSG_SNAKE | (HSG_PHASE_LAUNCH if f64 else HSG_PHASE_MC)
+
+
+# Bytes of spins and couplings, 6 L^3 values, that colour passes in place find in the 256 MB
+# memory-side cache, but launches that also read or write a second spin array (9 L^3) do not.
+PHASE_CACHE_BYTES = (204_000_000, 272_000_000)
+
+
+def call_flags(L: int, dtype=None, k: int = 1, heat_bath: bool = False) -> int:
+    """Traversal flags of a sweep of k hits that names none: over default_flags, every even
+    L from 98 to 1024 runs its over-relaxation phases as one launch each, with the next
+    sweep's colour-0 Monte Carlo pass where that pass is short.  us a sweep on MI355X (one
+    over-relaxation phase; colour passes / a launch per phase / with the Monte Carlo pass):
+
+      binary32  L = 98 k = 1  28.4 / 26.1 / 26.8     130 k = 1  47.3 / 43.5 / 43.5
+                    98 k = 8  36.0 / 34.1 / 37.0     186 k = 4   121 /  113 /  107
+                   210 k = 4   169 /  172 /  166     218 k = 4   186 /  196 /  199
+                   250 k = 8   415 /  375 /  394     384 k = 8  1555 / 1328 / 1336
+                   512 k = 4  3312 / 2782 / 2487     512 k = 8  3720 / 3251 / 3061
+      binary64  L =130 k = 1  85.6 / 81.1 / 78.6     130 k = 4  99.9 / 95.1 / 99.4
+                   170 k = 1   171 /  192 /  181     250 k = 4   776 /  693 /  675
+                   250 k = 8   988 /  905 /  915     250 heat bath  756 / 673 / 767
+
+    so binary32 takes the pass along from L = 130 with up to 4 hits or a heat bath, and from
+    256 always; binary64 with 1 or 2 hits from 130, with up to 4 from 180, never a heat bath.
+    Where only the passes' footprint fits the memory-side cache they stay: 206 <= L <= 224,
+    in binary64 162 to 178."""
+    f64 = dtype is not None and str(dtype) in ("torch.float64", "float64")
+    f = default_flags(L, dtype)
+    lo, hi = PHASE_CACHE_BYTES
+    if L < PHASE_MIN_L or not phase_supported(L) or lo < 6 * L ** 3 * (8 if f64 else 4) < hi:
+        return f
+    if f64:
+        carry = not heat_bath and L >= 130 and (k <= 2 or (k <= 4 and L >= 180))
+    else:
+        carry = L >= 256 or (L >= 130 and (heat_bath or k <= 4))
+    return f | (HSG_PHASE_MC if carry else HSG_PHASE_LAUNCH)
 
 
 class HsgError(RuntimeError):
@@ -218,8 +254,8 @@ class Lattice:
     def sweep(self, T: float, k: int = 1, n_or: int = 0, renorm_every: int = 0,
               n_sweeps: int = 1, heat_bath: bool = False, flags: int | None = None,
               stream=None) -> None:
-        """n_sweeps sweeps; flags None = default_flags(L, dtype)."""
-        f = default_flags(self.L, self.dtype) if flags is None else int(flags)
+        """n_sweeps sweeps; flags None = call_flags(L, dtype, k, heat_bath)."""
+        f = call_flags(self.L, self.dtype, k, heat_bath) if flags is None else int(flags)
         p = _SweepParams(float(T), int(k), int(n_or), int(renorm_every),
                          (HSG_HEAT_BATH if heat_bath else 0) | f)
         check(lib().hsg_sweep(ctypes.byref(self._d), ctypes.byref(p), int(n_sweeps),
@@ -231,7 +267,7 @@ class Lattice:
         """As sweep(), with every launch timed by HIP events on the launch stream:
         [(launch kind, ms)] in launch order (hsg_sweep_timed; waits for the stream)."""
         import numpy as np
-        f = default_flags(self.L, self.dtype) if flags is None else int(flags)
+        f = call_flags(self.L, self.dtype, k, heat_bath) if flags is None else int(flags)
         p = _SweepParams(float(T), int(k), int(n_or), int(renorm_every),
                          (HSG_HEAT_BATH if heat_bath else 0) | f)
         kinds = np.zeros(capacity, dtype=np.int32)

@@ -19,8 +19,8 @@ from typing import Callable, Iterable
 
 import torch
 
-from . import (BRICK_MAX_L, BRICK_MAX_L_F64, HSG_BRICK, HSG_FUSED, HSG_PHASE_LAUNCH, HSG_PHASE_MC, HSG_SNAKE, Lattice, fused_supported,
-               phase_supported)
+from . import (BRICK_MAX_L, BRICK_MAX_L_F64, HSG_BRICK, HSG_FUSED, HSG_PHASE_LAUNCH, HSG_PHASE_MC,
+               HSG_SNAKE, Lattice, fused_supported, phase_supported)
 
 CACHE_ENV = "HSG_AUTOTUNE_CACHE"
 

@@ -126,8 +126,7 @@ bool renorm_due(const hsg_sweep_params* p, uint64_t sweep) {
 // run an odd number of them, its last phase (never one that carries a Monte Carlo pass)
 // runs as two colour passes in place instead, so the spins end in the lattice's own
 // array without a copy (two passes cost less than a phase launch plus a copy of the
-// lattice).  With HSG_PHASE_MC
-// the launch of a sweep's last over-relaxation phase also runs the colour-0 Monte Carlo
+// lattice).  With HSG_PHASE_MC the launch of a sweep's last over-relaxation phase also runs the colour-0 Monte Carlo
 // pass of the next sweep of the call (and the renormalisation between them when due);
 // that sweep then starts with its colour-1 pass.
 template <typename R>
@@ -137,8 +136,9 @@ int sweep_plain(hsg_lattice* lat, const hsg_sweep_params* p, int32_t n_sweeps, h
   const Geometry g = pass_geometry(lat->L);
   const int64_t Nh = (int64_t)lat->L * lat->L * lat->L / 2;
   PassArgs<R> a{};
-  const bool phase_launch =
-      (p->flags & (HSG_PHASE_LAUNCH | HSG_PHASE_MC)) && phase_supported(lat->L);
+  const bool phase_launch = (p->flags & (HSG_PHASE_LAUNCH | HSG_PHASE_MC)) &&
+                            phase_supported(lat->L) &&
+                            lat->work_bytes >= work_bytes_for(lat->L, (int32_t)sizeof(R));
   R* bufs[2] = {(R*)lat->spins,
                 phase_launch ? (R*)((char*)lat->work + fused_offset(lat->L)) : nullptr};
   int cur = 0;  // buffer holding the current spins (phase launches flip it)
@@ -163,7 +163,6 @@ int sweep_plain(hsg_lattice* lat, const hsg_sweep_params* p, int32_t n_sweeps, h
   a.g = g;
   a.nt = (p->flags & HSG_STREAM_LOADS) ? 1 : 0;
   const PassMode mc = (p->flags & HSG_HEAT_BATH) ? PassMode::HeatBath : PassMode::Metropolis;
-  ph.mc_mode = (int32_t)mc;
   ph.partials = partials;
   const bool snake = (p->flags & HSG_SNAKE) != 0;
   const bool by_slab = (p->flags & HSG_PLANE_LAUNCH) != 0;
@@ -182,14 +181,11 @@ int sweep_plain(hsg_lattice* lat, const hsg_sweep_params* p, int32_t n_sweeps, h
         const bool then_mc = phase_mc && phase == p->n_or && n + 1 < n_sweeps;
         ph.in = bufs[cur];
         ph.out = bufs[1 - cur];
-        ph.sweep = (uint32_t)sweep;
-        ph.phase = (uint32_t)phase;
-        ph.then_mc = then_mc ? 1 : 0;
         ph.mc_sweep = (uint32_t)(sweep + 1);
         ph.renorm = then_mc && renorm_due(p, sweep) ? 1 : 0;
         int rc = device_status(
             recorded(then_mc ? HSG_LAUNCH_OR_PHASE_MC : HSG_LAUNCH_OR_PHASE, st,
-                     [&] { return launch_phase<R>(ph, st); }),
+                     [&] { return launch_phase<R>(ph, then_mc ? mc : PassMode::OverRelax, st); }),
             "phase launch");
         if (rc) return rc;
         cur = 1 - cur;
@@ -557,7 +553,7 @@ static int sweep_checked(hsg_lattice* lat, const hsg_sweep_params* p, int32_t n_
   if (use_fused(lat, p) && lat->work_bytes < hsg::work_bytes_for(lat->L, (int32_t)elem))
     return fail(HSG_EINVAL, "HSG_FUSED needs a work buffer of %zu bytes (has %zu)",
                 hsg::work_bytes_for(lat->L, (int32_t)elem), lat->work_bytes);
-  if ((p->flags & (HSG_PHASE_LAUNCH | HSG_PHASE_MC)) && hsg::phase_supported(lat->L) &&
+  if ((p->flags & (HSG_PHASE_LAUNCH | HSG_PHASE_MC)) && hsg::phase_always(lat->L) &&
       p->n_or > 0 && lat->work_bytes < hsg::work_bytes_for(lat->L, (int32_t)elem))
     return fail(HSG_EINVAL, "HSG_PHASE_LAUNCH and HSG_PHASE_MC need a work buffer of %zu bytes "
                             "(has %zu)",

@@ -41,9 +41,9 @@ static_assert(kFourierBlocks <= kReduceBlocks && kReduceSlots <= kFourierSlots,
 //   [0, 256)                              reserved
 //   [256, 256 + 8*n_partials)             per-tile energy-change partials of the passes
 //   [.., + 8*kReduceRegion)               per-block partials of energy / overlaps
-//   [fused_offset(L), + 3*N*sizeof(R))    second spin array of fused and phase launches
-//                                         (only for L that march_supported or
-//                                         phase_supported accepts)
+//   [fused_offset(L), + 3*N*sizeof(R))    second spin array of the launches of several
+//                                         passes (only for L that march_supported,
+//                                         phase_supported or brick_plan accepts)
 size_t work_bytes_for(int32_t L);  // without the second spin array
 size_t fused_offset(int32_t L);    // 256-byte aligned end of the above
 size_t work_bytes_for(int32_t L, int32_t dtype_bytes);  // with it where it applies
@@ -120,15 +120,11 @@ struct MarchArgs {
   MarchStage st[kMarchMaxStages];
 };
 
-// An over-relaxation phase (colour-0 pass then colour-1 pass) in one launch, optionally
-// followed by the next sweep's colour-0 Monte Carlo pass (kernels_phase.hip).  Tile
-// shape timed on MI355X at L = 256 against 128-1024 threads, 4-32 rows and 16-64 planes.
-constexpr int kPhaseThreads = 512;
-constexpr int kPTY = 16;  // tile rows
-constexpr int kPZ = 32;   // planes per workgroup
-constexpr int kPhaseMinL = 64;
-// Element offsets of the phase launch reach 3 N (six planes of N/2 from one base) and are
-// 32-bit: L = 1024 keeps them below 2^32.
+// An over-relaxation phase (colour-0 pass then colour-1 pass) in one launch, alone or
+// followed by the next sweep's colour-0 Monte Carlo pass (kernels_phase.hip).
+// 32-bit byte offsets into a component of a colour (N/2 values of up to 8 bytes) hold up to
+// L = 1024.
+constexpr int kPhaseMinL = 98;
 constexpr int kPhaseMaxL = 1024;
 
 template <typename R>
@@ -136,27 +132,27 @@ struct PhaseArgs {
   const R* in;  // colour-split spins before the phase
   R* out;       // after it (distinct from in)
   const R* J;   // colour-split couplings
-  R beta;       // inverse temperature of the Monte Carlo pass
-  uint32_t seed_lo, seed_hi;
-  uint32_t sweep, phase;  // Philox counter words of the phase (over-relaxation draws none)
-  int32_t k_hits;
   int32_t L;
-  // With then_mc: after the phase, the colour-0 pass of the Monte Carlo phase of sweep
-  // mc_sweep (mode mc_mode, a PassMode other than OverRelax).  With renorm, every spin
-  // is divided by its length between the two (colour 1 right after its over-relaxation
-  // step, colour 0 right before its Monte Carlo update).  The energy changes of a
+  int32_t n[3];  // tiles along x (colour columns), y and z: set by launch_phase
+  uint32_t inv[3];
+  // The colour-0 pass of the Monte Carlo phase of sweep mc_sweep, after the phase.  With
+  // renorm, every spin is divided by its length between the two.  The energy changes of a
   // workgroup's sites are added to partials[blockIdx.x].
-  int32_t then_mc;
-  int32_t mc_mode;
+  R beta;
+  uint32_t seed_lo, seed_hi;
   uint32_t mc_sweep;
+  int32_t k_hits;
   int32_t renorm;
   double* partials;
 };
 
+// Lattices that HSG_PHASE_LAUNCH and HSG_PHASE_MC apply to; among them those that need a
+// work buffer for it (the others run pass by pass without one).
 bool phase_supported(int32_t L);
-int32_t phase_blocks(int32_t L);
+bool phase_always(int32_t L);
+// mc: the mode of the pass that follows the phase, PassMode::OverRelax for the phase alone.
 template <typename R>
-hipError_t launch_phase(const PhaseArgs<R>& a, hipStream_t stream);
+hipError_t launch_phase(const PhaseArgs<R>& a, PassMode mc, hipStream_t stream);
 
 bool march_supported(int32_t L);
 int32_t march_blocks(int32_t L);
