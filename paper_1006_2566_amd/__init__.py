@@ -81,28 +81,36 @@ def call_flags(L: int, dtype=None, k: int = 1, heat_bath: bool = False) -> int:
     sweep's colour-0 Monte Carlo pass where that pass is short.  us a sweep on MI355X (one
     over-relaxation phase; colour passes / a launch per phase / with the Monte Carlo pass):
 
-      binary32  L = 98 k = 1  28.4 / 26.1 / 26.8     130 k = 1  47.3 / 43.5 / 43.5
-                    98 k = 8  36.0 / 34.1 / 37.0     186 k = 4   121 /  113 /  107
-                   210 k = 4   169 /  172 /  166     218 k = 4   186 /  196 /  199
-                   250 k = 8   415 /  375 /  394     384 k = 8  1555 / 1328 / 1336
-                   512 k = 4  3312 / 2782 / 2487     512 k = 8  3720 / 3251 / 3061
-      binary64  L =130 k = 1  85.6 / 81.1 / 78.6     130 k = 4  99.9 / 95.1 / 99.4
-                   170 k = 1   171 /  192 /  181     250 k = 4   776 /  693 /  675
-                   250 k = 8   988 /  905 /  915     250 heat bath  756 / 673 / 767
+      binary32  L = 98 k = 1  28.4 / 26.5 / 25.3     98 k = 2  29.4 / 27.3 / 27.6
+                   122 k = 2  42.6 / 40.6 / 39.9    178 k = 1   101 / 89.4 / 79.2
+                   146 k = 3  65.4 / 61.9 / 59.9    178 k = 4   108 / 98.2 /  102
+                   146 heat bath 64.6 / 61.9 / 59.6 194 heat bath 132 / 121 / 123
+                   210 k = 1   161 /  167 /  143    218 k = 1   177 /  189 /  175
+                   218 k = 4   186 /  194 /  198    242 k = 4   330 /  294 /  275
+                   242 k = 8   377 /  340 /  367    258 k = 8   462 /  414 /  398
+                   512 k = 4  3281 / 2753 / 2412    512 k = 8  3701 / 3224 / 2994
+      binary64  L =122 k = 1  74.0 / 67.7 / 68.2    130 k = 1  86.0 / 81.1 / 78.1
+                   146 k = 2   117 /  108 /  119    178 k = 1   211 /  229 /  214
+                   182 k = 4   269 /  260 /  256    320 k = 8  2111 / 1845 / 1923
+                   448 k = 8  5959 / 5601 / 5333    320 heat bath 1656 / 1386 / 1689
 
-    so binary32 takes the pass along from L = 130 with up to 4 hits or a heat bath, and from
-    256 always; binary64 with 1 or 2 hits from 130, with up to 4 from 180, never a heat bath.
-    Where only the passes' footprint fits the memory-side cache they stay: 206 <= L <= 224,
-    in binary64 162 to 178."""
+    so binary32 takes the pass along with one hit, from L = 114 with two, from 128 with three
+    or a heat bath, from 226 with four and from 256 always; binary64 with one hit from 126, with up to four
+    from 180, with more from 448, never a heat bath.  Where only the passes' footprint fits
+    the memory-side cache (206 <= L <= 224, in binary64 162 to 178) they stay, but for one hit
+    in binary32."""
     f64 = dtype is not None and str(dtype) in ("torch.float64", "float64")
     f = default_flags(L, dtype)
-    lo, hi = PHASE_CACHE_BYTES
-    if L < PHASE_MIN_L or not phase_supported(L) or lo < 6 * L ** 3 * (8 if f64 else 4) < hi:
+    if L < PHASE_MIN_L or not phase_supported(L):
         return f
     if f64:
-        carry = not heat_bath and L >= 130 and (k <= 2 or (k <= 4 and L >= 180))
+        carry = not heat_bath and (L >= 448 or (L >= 126 and k <= 1) or (L >= 180 and k <= 4))
     else:
-        carry = L >= 256 or (L >= 130 and (heat_bath or k <= 4))
+        carry = (L >= (128 if heat_bath or k == 3 else 226 if k == 4 else 256) or
+                 (not heat_bath and (k <= 1 or (k == 2 and L >= 114))))
+    lo, hi = PHASE_CACHE_BYTES
+    if lo < 6 * L ** 3 * (8 if f64 else 4) < hi and (f64 or heat_bath or k != 1):
+        return f
     return f | (HSG_PHASE_MC if carry else HSG_PHASE_LAUNCH)
 
 

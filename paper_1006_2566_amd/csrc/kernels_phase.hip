@@ -37,11 +37,12 @@
 // 132, 512 1649 / 1068 (36 bytes a site at 4.5 TB/s, 0.89 of a copy: bound by HBM from L =
 // 230 up, by the caches' far side below 204); binary64 L = 128 39.3 / 30.9, 256 403 / 291.
 // With the Monte Carlo pass, its three passes one by one / this, binary32 k = 4: L = 192 97
-// / 78, 256 277 / 177, 512 2490 / 1587.  At L = 256 that issues 72M vector instructions, 48M
-// of them C's, which take 117 of the 177 us; with k = 1 (45M) it is 171 us, bound by the
-// loads of a step and its barrier.  Tiles of 64 x 16 sites with loads behind conditions and
-// three barriers a step, which this replaced, took 161 and 215 us at L = 256, 1327 and 1830
-// at 512.
+// / 78, 256 277 / 177, 512 2490 / 1510; k = 1: 192 88 / 55, 256 274 / 146, 512 2460 / 1394.
+// At L = 256 and k = 4 that issues 72M vector instructions, 48M of them C's, which take 117
+// of the 177 us; only the waves of the tile's own rows, half of them there, have a C.  At
+// 512 (three rounds of 11 rows) the clock falls to 1.6 GHz under the load.  Tiles of 64 x 16
+// sites with loads behind conditions and three barriers a step, which this replaced, took
+// 161 and 215 us at L = 256, 1327 and 1830 at 512.
 #include <algorithm>
 #include <type_traits>
 
@@ -69,10 +70,14 @@ struct RowSize {
   static constexpr int D = MC ? 1 : 2;  // steps ahead of which a step's values are loaded
 };
 
-// MODE: of the Monte Carlo pass behind the phase, OverRelax for the phase alone.
-template <typename R, PassMode MODE>
+// MODE: of the Monte Carlo pass behind the phase, OverRelax for the phase alone.  WAVES: a wave
+// takes a row of the tile (by_wave below).
+template <typename R, PassMode MODE, bool WAVES>
 __device__ __forceinline__ void row_march(const PhaseArgs<R>& a) {
   constexpr bool MC = MODE != PassMode::OverRelax;
+  // hits whose trials are formed together: a group's registers cost more than they gain
+  // where it may be incomplete (L = 256, one hit: 189 us, and 146 one by one)
+  [[maybe_unused]] constexpr int kGroup = MODE == PassMode::MetropolisFull ? 4 : 1;
   constexpr int H = MC ? 1 : 0;  // rows (and columns) B goes beyond the tile
   using Size = RowSize<R, MC>;
   constexpr int N0 = Size::A, N1 = Size::C1, D = Size::D;
@@ -97,7 +102,7 @@ __device__ __forceinline__ void row_march(const PhaseArgs<R>& a) {
   const int32_t hx = a.n[0] > 1 ? 1 : 0;
   const int32_t w0 = nx + 2 * hx, w1 = nx + 4 * hx;
   const int32_t wb = nx + 2 * hx * H;
-  const int32_t n1 = (ny + 4 + 2 * H) * w1, n0 = (ny + 2 + 2 * H) * w0, nb = (ny + 2 * H) * wb;
+  [[maybe_unused]] const int32_t n1 = (ny + 4 + 2 * H) * w1;
 
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
@@ -112,9 +117,34 @@ __device__ __forceinline__ void row_march(const PhaseArgs<R>& a) {
   // Threads and slots past the last site load the last site's: loads without a condition are
   // what lets the wait for one step's values leave the next steps' in flight (with a branch
   // around any of them the compiler has to wait for all).
-  const bool hasA = tid < n0, hasB = tid < nb;
-  const int32_t sA = min(tid, n0 - 1), sB = min(tid, nb - 1);
-  const int32_t rA = quot(sA, w0), jA = sA - rA * w0, rB = quot(sB, wb), jB = sB - rB * wb;
+  // item i of a window of n rows of w columns, h of them halo on either side: its place, or
+  // the last one's for threads past the last
+  struct Place {
+    int32_t r, j;
+    bool has;
+  };
+  auto item = [&](int32_t i, int32_t n, int32_t w, int32_t h) {
+    Place p;
+    if constexpr (!WAVES) {
+      const int32_t s = min(i, n * w - 1);
+      p.has = i < n * w;
+      p.r = quot(s, w);
+      p.j = s - p.r * w;
+    } else if ((i >> 6) < n) {  // the tile's 64 columns
+      p = Place{i >> 6, h + (i & 63), true};
+    } else {  // 2 h halo columns (h = 1 or 2) of a row after the other
+      const int32_t e = i - 64 * n, s = min(e, 2 * h * n - 1), c = s & (2 * h - 1);
+      p.has = e < 2 * h * n;
+      p.r = s >> h;
+      p.j = c < h ? c : 64 + c;
+    }
+    return p;
+  };
+  const Place itA = item(tid, ny + 2 + 2 * H, w0, hx), itB = item(tid, ny + 2 * H, wb, hx * H);
+  const bool hasA = itA.has, hasB = itB.has;
+  const int32_t rA = itA.r, jA = itA.j, rB = itB.r, jB = itB.j;
+  // in the planes of their results
+  const int32_t oA = WAVES ? rA * w0 + jA : tid, oB = WAVES ? rB * wb + jB : tid;
   const int32_t xA = wrap(x0 - hx + jA, Lh), xB = wrap(x0 - hx * H + jB, Lh);
   const int32_t yA = wrap(y0 - 1 - H + rA, L), yB = wrap(y0 - H + rB, L);
   const bool ownA = hasA && rA > H && rA <= ny + H && jA >= hx && jA < hx + nx;
@@ -141,11 +171,13 @@ __device__ __forceinline__ void row_march(const PhaseArgs<R>& a) {
   const uint32_t dA = (uint32_t)(xA > 0 ? -1 : Lh - 1) * E, dB = (uint32_t)(xB > 0 ? -1 : Lh - 1) * E;
   const uint32_t gax[2] = {ga + (pA ? 0u : dA), ga + (pA ? dA : 0u)};
   const uint32_t gbx[2] = {gb + (pB ? 0u : dB), gb + (pB ? dB : 0u)};
-  uint32_t g1[2];  // colour-1 sites of the region: tid and tid + T
+  uint32_t g1[2];  // colour-1 sites of the region: items tid and tid + T
+  [[maybe_unused]] int32_t o1[2];  // with WAVES their places in LDS, or -1
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
-    const int32_t i = min(tid + u * T, n1 - 1), r = quot(i, w1);
-    g1[u] = (uint32_t)(wrap(y0 - 2 - H + r, L) * Lh + wrap(x0 - 2 * hx + i - r * w1, Lh)) * E;
+    const Place it = item(tid + u * T, ny + 4 + 2 * H, w1, 2 * hx);
+    g1[u] = (uint32_t)(wrap(y0 - 2 - H + it.r, L) * Lh + wrap(x0 - 2 * hx + it.j, Lh)) * E;
+    if constexpr (WAVES) o1[u] = it.has ? it.r * w1 + it.j : -1;
   }
 
   // The twelve component arrays and six outputs have fixed (scalar) bases, and a load's
@@ -174,11 +206,13 @@ __device__ __forceinline__ void row_march(const PhaseArgs<R>& a) {
   };
   auto put_c1 = [&](const R (&c1)[2][3], R (&d)[3][N1]) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
-      if (tid + u * T < n1) {
+    for (int u = 0; u < 2; ++u) {
+      const int32_t i = WAVES ? o1[u] : tid + u * T;
+      if (WAVES ? i >= 0 : i < n1) {
 #pragma unroll
-        for (int k = 0; k < 3; ++k) d[k][tid + u * T] = c1[u][k];
+        for (int k = 0; k < 3; ++k) d[k][i] = c1[u][k];
       }
+    }
   };
   // what A of plane q needs (q of step parity U & 1), and colour 1 of plane q + 2
   auto load_a = [&](auto U, RowStep<R>& s, int32_t q) {
@@ -238,14 +272,14 @@ __device__ __forceinline__ void row_march(const PhaseArgs<R>& a) {
     const bool doC = MC && ownA && q - 3 >= z0;
     Vec3<R> sc{};
     if (doC)
-      sc = Vec3<R>{lds0[(U + 1) & 3][0][tid], lds0[(U + 1) & 3][1][tid], lds0[(U + 1) & 3][2][tid]};
+      sc = Vec3<R>{lds0[(U + 1) & 3][0][oA], lds0[(U + 1) & 3][1][oA], lds0[(U + 1) & 3][2][oA]};
     if (hasA) {
       const Vec3<R> h = field(lds1[(U + 1) & 3], lds1[(U + 2) & 3], lds1[U], iA, w1, iA_px[par],
                               iA_mx[par], s.ja);
       const Vec3<R> r = reflect(Vec3<R>{s.s0[0], s.s0[1], s.s0[2]}, h);
-      lds0[U][0][tid] = r.x;
-      lds0[U][1][tid] = r.y;
-      lds0[U][2][tid] = r.z;
+      lds0[U][0][oA] = r.x;
+      lds0[U][1][oA] = r.y;
+      lds0[U][2][oA] = r.z;
       if constexpr (!MC)
         if (ownA && q >= z0 && q < z0 + nz) store(I0{}, ga + zb * (uint32_t)q, r);
     }
@@ -267,9 +301,9 @@ __device__ __forceinline__ void row_march(const PhaseArgs<R>& a) {
       Vec3<R> r = reflect(sb, h);
       if constexpr (MC) {
         if (a.renorm) r = unit_vector(r);
-        ldsB[U][0][tid] = r.x;
-        ldsB[U][1][tid] = r.y;
-        ldsB[U][2][tid] = r.z;
+        ldsB[U][0][oB] = r.x;
+        ldsB[U][1][oB] = r.y;
+        ldsB[U][2][oB] = r.z;
         if (ownB && q > z0 && q <= z0 + nz) store(I3{}, gb + zb * (uint32_t)(q - 1), r);
       } else {
         store(I3{}, gb + zb * (uint32_t)(q - 1), r);
@@ -278,13 +312,13 @@ __device__ __forceinline__ void row_march(const PhaseArgs<R>& a) {
     load_b(std::integral_constant<int, (U + D) & 3>{}, s, next);
     if constexpr (MC) {
       if (doC) {
-        const int32_t ic = tid - w0, p = (pA + par + 1) & 1;
+        const int32_t ic = oA - w0, p = (pA + par + 1) & 1;
         const Vec3<R> h = field(ldsB[(U + 2) & 3], ldsB[(U + 3) & 3], ldsB[(U + 1) & 3], ic, w0,
                                 ic + (p ? lA : 0), ic + (p ? 0 : mA), jc[2]);
         if (a.renorm) sc = unit_vector(sc);
         const int32_t z = q - 3;
         const uint32_t site = (uint32_t)(2 * xA + p) + (uint32_t)L * (uint32_t)(yA + L * z);
-        dE += apply_update<R, MODE, 4>(
+        dE += apply_update<R, MODE, kGroup>(
             sc, h, site, HitCtx<R>{a.beta, a.mc_sweep, 0u, a.k_hits, a.seed_lo, a.seed_hi});
         store(I0{}, ga + zb * (uint32_t)z, sc);
       }
@@ -330,12 +364,17 @@ __device__ __forceinline__ void row_march(const PhaseArgs<R>& a) {
 
 template <typename R>
 __global__ __launch_bounds__((RowSize<R, false>::A)) void phase_kernel(PhaseArgs<R> a) {
-  row_march<R, PassMode::OverRelax>(a);
+  row_march<R, PassMode::OverRelax, false>(a);
 }
 
 template <typename R, PassMode MC>
 __global__ __launch_bounds__((RowSize<R, true>::A)) void phase_mc_kernel(PhaseArgs<R> a) {
-  row_march<R, MC>(a);
+  row_march<R, MC, false>(a);
+}
+
+template <typename R, PassMode MC>
+__global__ __launch_bounds__((RowSize<R, true>::A)) void phase_mc_wave_kernel(PhaseArgs<R> a) {
+  row_march<R, MC, true>(a);
 }
 
 }  // namespace
@@ -350,14 +389,25 @@ namespace {
 
 uint32_t row_inv(int32_t d) { return d > 1 ? 0xFFFFFFFFu / (uint32_t)d + 1u : 0u; }
 
+// Tiles of 64 columns: a wave per row and the halo columns on the waves behind those, so that
+// a load of the tile's columns is two cache lines, not three or four.  us of the launch with
+// four hits (one), items row by row / a wave per row: L = 512 1587 / 1510 (1564 / 1394), 640
+// 3252 / 3110 (3080 / 2892), 1024 14038 / 13751 (14083 / 12668).  With fewer columns lanes
+// are idle: 448, 56 columns, 1056 / 1221.
+bool by_wave(bool mc, int32_t nx, int32_t hx) { return mc && hx && nx == 64; }
+
 // Threads of tiles of that many columns and rows (hx: tiles narrower than the lattice), 0 if
 // the kernel does not hold them.
 template <typename R, bool MC>
 int32_t row_threads(int32_t nx, int32_t ny, int32_t hx) {
   using Size = RowSize<R, MC>;
-  const int32_t H = MC ? 1 : 0, T = ((ny + 2 + 2 * H) * (nx + 2 * hx) + 63) & ~63;
-  const int32_t n1 = (ny + 4 + 2 * H) * (nx + 4 * hx);
-  return T <= Size::A && n1 <= Size::C1 && n1 <= 2 * T ? T : 0;
+  const int32_t H = MC ? 1 : 0, r0 = ny + 2 + 2 * H, r1 = r0 + 2;
+  const int32_t n0 = r0 * (nx + 2 * hx), n1 = r1 * (nx + 4 * hx);
+  const bool waves = by_wave(MC, nx, hx);
+  const int32_t T = (waves ? 64 * r0 + 2 * r0 + 63 : n0 + 63) & ~63;
+  return T <= Size::A && n0 <= Size::A && n1 <= Size::C1 && (waves ? 64 * r1 + 4 * r1 : n1) <= 2 * T
+             ? T
+             : 0;
 }
 
 // The tiles for an L^3 lattice: the smallest of an estimate fitted to 2400 timed plans of 55
@@ -411,13 +461,16 @@ hipError_t launch_rows(PhaseArgs<R> a, hipStream_t st) {
   constexpr bool MC = MODE != PassMode::OverRelax;
   if (!phase_supported(a.L) || !row_plan<R, MC>(a.L, a.n)) return hipErrorInvalidValue;
   const int32_t Lh = a.L / 2, nx = (Lh + a.n[0] - 1) / a.n[0], ny = (a.L + a.n[1] - 1) / a.n[1];
-  const int32_t T = row_threads<R, MC>(nx, ny, a.n[0] > 1);
+  const int32_t hx = a.n[0] > 1 ? 1 : 0, T = row_threads<R, MC>(nx, ny, hx);
   if (!T || (MC && !a.partials)) return hipErrorInvalidValue;
   for (int k = 0; k < 3; ++k) a.inv[k] = row_inv(a.n[k]);
   const dim3 grid((unsigned)(a.n[0] * a.n[1] * a.n[2])), block((unsigned)T);
-  if constexpr (MC)
-    hipLaunchKernelGGL((phase_mc_kernel<R, MODE>), grid, block, 0, st, a);
-  else
+  if constexpr (MC) {
+    if (by_wave(MC, nx, hx))
+      hipLaunchKernelGGL((phase_mc_wave_kernel<R, MODE>), grid, block, 0, st, a);
+    else
+      hipLaunchKernelGGL((phase_mc_kernel<R, MODE>), grid, block, 0, st, a);
+  } else
     hipLaunchKernelGGL((phase_kernel<R>), grid, block, 0, st, a);
   return hipGetLastError();
 }

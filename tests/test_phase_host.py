@@ -20,10 +20,16 @@ def test_flags_of_a_call():
     f64 = torch.float64
     assert hsg.call_flags(64) == hsg.HSG_SNAKE | hsg.HSG_BRICK
     assert hsg.call_flags(96) == hsg.call_flags(1026) == hsg.HSG_SNAKE
-    assert hsg.call_flags(98) == hsg.call_flags(128, k=4) == hsg.call_flags(130, k=5) == one
-    assert hsg.call_flags(130, k=4) == hsg.call_flags(130, k=9, heat_bath=True) == carry
-    assert hsg.call_flags(204) == hsg.call_flags(226) == hsg.call_flags(256, k=8) == carry
-    assert hsg.call_flags(206) == hsg.call_flags(224) == hsg.HSG_SNAKE
-    assert hsg.call_flags(130, f64, k=3) == hsg.call_flags(300, f64, heat_bath=True) == one
-    assert hsg.call_flags(130, f64, k=2) == hsg.call_flags(190, f64, k=4) == carry
-    assert hsg.call_flags(162, f64) == hsg.call_flags(178, f64) == hsg.HSG_SNAKE
+    assert hsg.call_flags(98, k=2) == hsg.call_flags(126, k=3) == hsg.call_flags(204, k=4) == one
+    assert hsg.call_flags(126, k=0, heat_bath=True) == hsg.call_flags(254, k=5) == one
+    assert hsg.call_flags(98) == hsg.call_flags(114, k=2) == hsg.call_flags(218) == carry
+    assert hsg.call_flags(128, k=3) == hsg.call_flags(128, k=9, heat_bath=True) == carry
+    assert hsg.call_flags(226, k=4) == hsg.call_flags(226, heat_bath=True) == carry
+    assert hsg.call_flags(256, k=8) == carry
+    assert hsg.call_flags(206, k=2) == hsg.call_flags(224, k=4) == hsg.HSG_SNAKE
+    assert hsg.call_flags(224, heat_bath=True) == hsg.HSG_SNAKE
+    assert hsg.call_flags(124, f64) == hsg.call_flags(446, f64, k=5) == one
+    assert hsg.call_flags(448, f64, heat_bath=True) == one
+    assert hsg.call_flags(126, f64) == hsg.call_flags(180, f64, k=4) == carry
+    assert hsg.call_flags(448, f64, k=5) == carry | hsg.HSG_PHASE_LAUNCH  # a default there
+    assert hsg.call_flags(162, f64) == hsg.call_flags(178, f64, k=8) == hsg.HSG_SNAKE
