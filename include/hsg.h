@@ -311,6 +311,16 @@ int hsg_batch_energy(const hsg_batch *b, double *out_dev, void *stream);
 int hsg_batch_overlap(const hsg_batch *b, const int32_t *pairs_dev, int32_t n_pairs,
                       double *out_dev, void *stream);
 
+/* hsg_batch_init and hsg_batch_overlap with the sums of a large chain spread over several
+ * workgroups (a part each of its sites).  L_max: at least the largest L of the chains
+ * concerned; parts_dev: device scratch of hsg_batch_parts(L_max) doubles per chain of the
+ * batch, or 15 times as many per pair (n_pairs <= 65535).  Same results up to the order of
+ * the binary64 sums, which depends on a chain's L alone. */
+int32_t hsg_batch_parts(int32_t L);
+int hsg_batch_init_parts(const hsg_batch *b, int32_t L_max, double *parts_dev, void *stream);
+int hsg_batch_overlap_parts(const hsg_batch *b, const int32_t *pairs_dev, int32_t n_pairs,
+                            int32_t L_max, double *parts_dev, double *out_dev, void *stream);
+
 /* Records of hsg_overlap_fourier for chain pairs: pairs_dev [n_pairs][2] of chain
  * indices (device); out_dev [n_pairs][HSG_FOURIER_VALUES] (device).  A pair whose
  * indices are out of range or whose chains differ in L gets a record of NaNs. */

@@ -53,6 +53,9 @@ def _bind():
     L.hsg_batch_check.argtypes = [P, I32, ctypes.c_int64, ctypes.c_int64]
     L.hsg_batch_init.argtypes = [BP, P]
     L.hsg_batch_sweep.argtypes = [BP, I32, P]
+    L.hsg_batch_parts.argtypes, L.hsg_batch_parts.restype = [I32], I32
+    L.hsg_batch_init_parts.argtypes = [BP, I32, P, P]
+    L.hsg_batch_overlap_parts.argtypes = [BP, P, I32, I32, P, P, P]
     L.hsg_batch_energy.argtypes = [BP, P, P]
     L.hsg_batch_overlap.argtypes = [BP, P, I32, P, P]
     L.hsg_pt_exchange.argtypes = [PP, BP, P]
@@ -64,7 +67,7 @@ def _bind():
     for name in ("hsg_batch_check", "hsg_batch_init", "hsg_batch_sweep",
                  "hsg_batch_energy", "hsg_batch_overlap", "hsg_pt_exchange", "hsg_pt_overlap",
                  "hsg_batch_overlap_fourier", "hsg_pt_overlap_fourier", "hsg_batch_tiles",
-                 "hsg_batch_tile_sweep"):
+                 "hsg_batch_tile_sweep", "hsg_batch_init_parts", "hsg_batch_overlap_parts"):
         getattr(L, name).restype = ctypes.c_int
     _bound = True
 

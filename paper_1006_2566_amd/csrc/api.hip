@@ -743,6 +743,40 @@ int hsg_batch_init(const hsg_batch* b, void* stream) {
                        "batch init");
 }
 
+int32_t hsg_batch_parts(int32_t L) {
+  return L >= 2 && L <= HSG_BATCH_L_MAX ? hsg::batch_parts(L) : 0;
+}
+
+int hsg_batch_init_parts(const hsg_batch* b, int32_t L_max, double* parts_dev, void* stream) {
+  int rc = check_batch(b);
+  if (rc) return rc;
+  const int32_t parts = hsg_batch_parts(L_max);
+  if (!parts_dev || parts == 0) return fail(HSG_EINVAL, "bad L_max or parts buffer");
+  hipStream_t st = as_stream(stream);
+  return device_status(b->dtype == HSG_F32
+                           ? hsg::launch_batch_init_parts<float>(b, parts, parts_dev, st)
+                           : hsg::launch_batch_init_parts<double>(b, parts, parts_dev, st),
+                       "batch init");
+}
+
+int hsg_batch_overlap_parts(const hsg_batch* b, const int32_t* pairs_dev, int32_t n_pairs,
+                            int32_t L_max, double* parts_dev, double* out_dev, void* stream) {
+  int rc = check_batch(b);
+  if (rc) return rc;
+  if (!pairs_dev || !out_dev || n_pairs < 0 || n_pairs > 65535)
+    return fail(HSG_EINVAL, "bad pairs or output");
+  const int32_t parts = hsg_batch_parts(L_max);
+  if (!parts_dev || parts == 0) return fail(HSG_EINVAL, "bad L_max or parts buffer");
+  if (n_pairs == 0) return HSG_OK;
+  hipStream_t st = as_stream(stream);
+  return device_status(b->dtype == HSG_F32
+                           ? hsg::launch_batch_overlap_parts<float>(b, pairs_dev, n_pairs, parts,
+                                                                    parts_dev, out_dev, st)
+                           : hsg::launch_batch_overlap_parts<double>(b, pairs_dev, n_pairs, parts,
+                                                                     parts_dev, out_dev, st),
+                       "batch overlap");
+}
+
 int hsg_batch_sweep(const hsg_batch* b, int32_t n_sweeps, void* stream) {
   int rc = check_batch(b);
   if (rc) return rc;

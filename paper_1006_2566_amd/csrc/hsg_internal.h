@@ -240,6 +240,14 @@ template <typename R>
 hipError_t launch_batch_init(const hsg_batch* b, hipStream_t st);
 template <typename R>
 hipError_t launch_batch_sweep(const hsg_batch* b, int32_t n_sweeps, hipStream_t st);
+int32_t batch_parts(int32_t L);
+template <typename R>
+hipError_t launch_batch_init_parts(const hsg_batch* b, int32_t parts, double* scratch,
+                                   hipStream_t st);
+template <typename R>
+hipError_t launch_batch_overlap_parts(const hsg_batch* b, const int32_t* pairs, int32_t n_pairs,
+                                      int32_t parts, double* scratch, double* out,
+                                      hipStream_t st);
 template <typename R>
 hipError_t launch_batch_energy(const hsg_batch* b, double* out, hipStream_t st);
 template <typename R>

@@ -199,16 +199,23 @@ __global__ __launch_bounds__(kChainReduceThreads) void batch_energy_kernel(
   if (threadIdx.x == 0) out[blockIdx.x] = -total;
 }
 
-// Overlap of two chains of equal L, reduced by one workgroup.  A thread takes U sites at a
-// time, their loads in flight together (one compute unit reads a whole pair: the loop is
-// bound by the latency of its loads); the waves' sums are added in order, all 15 at once.
+__host__ __device__ inline uint32_t half_sites(int32_t L) {
+  return (uint32_t)(L / 2) * (uint32_t)L * (uint32_t)L;
+}
+
+// Overlap of two chains of equal L over the sites [e0, e1) of either colour, reduced by one
+// workgroup; its 15 sums divided by `norm` go to out.  A thread takes U sites at a time,
+// their loads in flight together (one compute unit reads them all: the loop is bound by the
+// latency of its loads, and for large chains by what it can load, 170 GB/s); the waves' sums
+// are added in order, all 15 at once.
 template <typename R>
 __device__ __forceinline__ void pair_overlap(const hsg_chain& ca, const hsg_chain& cb,
-                                             const R* spins, double* out) {
+                                             const R* spins, uint32_t e0, uint32_t e1,
+                                             double norm, double* out) {
   constexpr int kWaves = kChainReduceThreads / 64;
   constexpr int U = sizeof(R) == 4 ? 4 : 2;
   __shared__ double part[kWaves][16];
-  const uint32_t Nh = (uint32_t)(ca.L / 2) * (uint32_t)ca.L * (uint32_t)ca.L;
+  const uint32_t Nh = half_sites(ca.L);
   const R* a = spins + ca.spin_offset;
   const R* b = spins + cb.spin_offset;
   double v[15] = {0.0};
@@ -226,8 +233,8 @@ __device__ __forceinline__ void pair_overlap(const hsg_chain& ca, const hsg_chai
   for (int c = 0; c < 2; ++c) {
     const R* ac = a + 3 * c * Nh;
     const R* bc = b + 3 * c * Nh;
-    uint32_t e = threadIdx.x;
-    for (; e + (U - 1) * kChainReduceThreads < Nh; e += U * kChainReduceThreads) {
+    uint32_t e = e0 + threadIdx.x;
+    for (; e + (U - 1) * kChainReduceThreads < e1; e += U * kChainReduceThreads) {
       R av[U][3], bv[U][3];
 #pragma unroll
       for (int u = 0; u < U; ++u)
@@ -239,7 +246,7 @@ __device__ __forceinline__ void pair_overlap(const hsg_chain& ca, const hsg_chai
 #pragma unroll
       for (int u = 0; u < U; ++u) add(av[u], bv[u]);
     }
-    for (; e < Nh; e += kChainReduceThreads) {
+    for (; e < e1; e += kChainReduceThreads) {
       const R av[3] = {ac[e], ac[Nh + e], ac[2 * Nh + e]};
       const R bv[3] = {bc[e], bc[Nh + e], bc[2 * Nh + e]};
       add(av, bv);
@@ -254,8 +261,15 @@ __device__ __forceinline__ void pair_overlap(const hsg_chain& ca, const hsg_chai
   if (threadIdx.x < 15) {
     double t = 0.0;
     for (int w = 0; w < kWaves; ++w) t += part[w][threadIdx.x];
-    out[threadIdx.x] = t / (2.0 * (double)Nh);
+    out[threadIdx.x] = t / norm;
   }
+}
+
+template <typename R>
+__device__ __forceinline__ void pair_overlap(const hsg_chain& ca, const hsg_chain& cb,
+                                             const R* spins, double* out) {
+  const uint32_t Nh = half_sites(ca.L);
+  pair_overlap<R>(ca, cb, spins, 0u, Nh, 2.0 * (double)Nh, out);
 }
 
 template <typename R>
@@ -263,6 +277,71 @@ __global__ __launch_bounds__(kChainReduceThreads) void chain_pairs_overlap_kerne
     const hsg_chain* chains, const R* spins, const int32_t* pairs, double* out) {
   const int32_t p = blockIdx.x;
   pair_overlap<R>(chains[pairs[2 * p]], chains[pairs[2 * p + 1]], spins, out + 15 * (int64_t)p);
+}
+
+// The same and H of a chain in parts of kPartSites sites of a colour, a workgroup each, whose
+// sums are then added in order: a chain's result depends on nothing but the chain.  A
+// workgroup alone took 255 us for the overlaps of a few chains of up to L = 96 and 755 for
+// the energies of 48 (bound by what its compute unit can load); 54 to a chain take 16 and 84.
+constexpr uint32_t kPartSites = 8192;
+__host__ __device__ inline int32_t chain_parts(int32_t L) {
+  return (int32_t)((half_sites(L) + kPartSites - 1u) / kPartSites);
+}
+template <typename R>
+__global__ __launch_bounds__(kChainReduceThreads) void chain_pairs_part_kernel(
+    const hsg_chain* chains, const R* spins, const int32_t* pairs, double* parts) {
+  const int32_t p = (int32_t)blockIdx.y, part = (int32_t)blockIdx.x;
+  const hsg_chain& ca = chains[pairs[2 * p]];
+  const uint32_t Nh = half_sites(ca.L), e0 = (uint32_t)part * kPartSites;
+  if (e0 >= Nh) return;
+  pair_overlap<R>(ca, chains[pairs[2 * p + 1]], spins, e0, min(e0 + kPartSites, Nh), 1.0,
+                  parts + 15 * ((int64_t)p * gridDim.x + part));
+}
+constexpr int kSumThreads = 256;  // 16 partial sums of a record's 15 values, then theirs
+__global__ __launch_bounds__(kSumThreads) void chain_pairs_sum_kernel(
+    const hsg_chain* chains, const int32_t* pairs, const double* parts, int32_t stride,
+    double* out) {
+  __shared__ double part[16][16];
+  const int32_t p = (int32_t)blockIdx.x, i = (int32_t)threadIdx.x & 15,
+                g = (int32_t)threadIdx.x >> 4;
+  const int32_t L = chains[pairs[2 * p]].L, n = min(chain_parts(L), stride);
+  double t = 0.0;
+  if (i < 15)
+    for (int32_t k = g; k < n; k += 16) t += parts[15 * ((int64_t)p * stride + k) + i];
+  part[g][i] = t;
+  __syncthreads();
+  if (threadIdx.x < 15) {
+    t = 0.0;
+    for (int k = 0; k < 16; ++k) t += part[k][threadIdx.x];
+    out[15 * (int64_t)p + threadIdx.x] = t / (2.0 * (double)half_sites(L));
+  }
+}
+template <typename R>
+__global__ __launch_bounds__(kChainReduceThreads) void batch_energy_part_kernel(
+    const hsg_chain* chains, R* spins, R* J, double* parts) {
+  __shared__ double s_red[16];
+  const int32_t c = (int32_t)blockIdx.y, part = (int32_t)blockIdx.x;
+  const ChainView<R> v = chain_view<R>(load_chain(chains, c), spins, J);
+  const uint32_t e0 = (uint32_t)part * kPartSites, e1 = min(e0 + kPartSites, (uint32_t)v.Nh);
+  if (e0 >= e1) return;
+  const SmallDiv by_lh((uint32_t)v.Lh), by_l((uint32_t)v.L);
+  double acc = 0.0;
+  for (uint32_t ic = e0 + threadIdx.x; ic < e1; ic += kChainReduceThreads)
+    acc += colour0_bond_sum<R>(v.S, v.J, chain_site<R, 0>(v, ic, by_lh, by_l));
+  const double total = block_sum(acc, s_red);
+  if (threadIdx.x == 0) parts[(int64_t)c * gridDim.x + part] = total;
+}
+__global__ __launch_bounds__(kSumThreads) void batch_energy_sum_kernel(const hsg_chain* chains,
+                                                                       const double* parts,
+                                                                       int32_t stride,
+                                                                       double* out) {
+  __shared__ double s_red[16];
+  const int32_t c = (int32_t)blockIdx.x, n = min(chain_parts(chains[c].L), stride);
+  double t = 0.0;
+  for (int32_t k = (int32_t)threadIdx.x; k < n; k += kSumThreads)
+    t += parts[(int64_t)c * stride + k];
+  const double total = block_sum(t, s_red);
+  if (threadIdx.x == 0) out[c] = -total;
 }
 
 template <typename R>
@@ -457,6 +536,32 @@ hipError_t launch_batch_init(const hsg_batch* b, hipStream_t st) {
   return hipGetLastError();
 }
 
+int32_t batch_parts(int32_t L) { return chain_parts(L); }
+
+template <typename R>
+hipError_t launch_batch_init_parts(const hsg_batch* b, int32_t parts, double* scratch,
+                                   hipStream_t st) {
+  hipLaunchKernelGGL(batch_init_kernel<R>, dim3(64, (unsigned)b->n_chains), dim3(256), 0, st,
+                     b->chains, (R*)b->spins, (R*)b->J);
+  hipLaunchKernelGGL(batch_energy_part_kernel<R>, dim3((unsigned)parts, (unsigned)b->n_chains),
+                     dim3(kChainReduceThreads), 0, st, b->chains, (R*)b->spins, (R*)b->J, scratch);
+  hipLaunchKernelGGL(batch_energy_sum_kernel, dim3((unsigned)b->n_chains), dim3(kSumThreads), 0,
+                     st, b->chains, (const double*)scratch, parts, b->E);
+  return hipGetLastError();
+}
+
+template <typename R>
+hipError_t launch_batch_overlap_parts(const hsg_batch* b, const int32_t* pairs, int32_t n_pairs,
+                                      int32_t parts, double* scratch, double* out,
+                                      hipStream_t st) {
+  hipLaunchKernelGGL(chain_pairs_part_kernel<R>, dim3((unsigned)parts, (unsigned)n_pairs),
+                     dim3(kChainReduceThreads), 0, st, b->chains, (const R*)b->spins, pairs,
+                     scratch);
+  hipLaunchKernelGGL(chain_pairs_sum_kernel, dim3((unsigned)n_pairs), dim3(kSumThreads), 0, st,
+                     b->chains, pairs, (const double*)scratch, parts, out);
+  return hipGetLastError();
+}
+
 template <typename R>
 hipError_t launch_batch_sweep(const hsg_batch* b, int32_t n_sweeps, hipStream_t st) {
   BatchArgs<R> a;
@@ -578,7 +683,11 @@ hipError_t launch_batch_tile_sweep(const hsg_batch* b, const int32_t* tiles,
 
 #define HSG_BATCH_INSTANTIATE(R)                                                              \
   template hipError_t launch_batch_init<R>(const hsg_batch*, hipStream_t);                    \
-  template hipError_t launch_batch_sweep<R>(const hsg_batch*, int32_t, hipStream_t); \
+  template hipError_t launch_batch_init_parts<R>(const hsg_batch*, int32_t, double*,          \
+                                                 hipStream_t);                                 \
+  template hipError_t launch_batch_overlap_parts<R>(const hsg_batch*, const int32_t*, int32_t, \
+                                                    int32_t, double*, double*, hipStream_t);   \
+  template hipError_t launch_batch_sweep<R>(const hsg_batch*, int32_t, hipStream_t);           \
   template hipError_t launch_batch_energy<R>(const hsg_batch*, double*, hipStream_t);         \
   template hipError_t launch_batch_overlap<R>(const hsg_batch*, const int32_t*, int32_t,      \
                                               double*, hipStream_t);                          \

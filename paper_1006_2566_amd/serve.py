@@ -329,7 +329,13 @@ class Server:
         d = _Batch(n, _dtype_code(self.dtype), chains.data_ptr(), self.spins.data_ptr(),
                    self.J.data_ptr(), beta.data_ptr(), E.data_ptr(), zeros.data_ptr(), None,
                    order.data_ptr(), 256, 0)
-        check(lib().hsg_batch_init(ctypes.byref(d), _stream(None)))
+        L_max = int(max(self.table[s]["L"] for s in slots))
+        parts = lib().hsg_batch_parts(L_max)
+        if parts > 1:
+            scratch = torch.empty(n * parts, dtype=torch.float64, device=dev)
+            check(lib().hsg_batch_init_parts(ctypes.byref(d), L_max, _ptr(scratch), _stream(None)))
+        else:
+            check(lib().hsg_batch_init(ctypes.byref(d), _stream(None)))
         idx = self._to_dev(np.asarray(slots, dtype=np.int64))
         self.E[idx] = E
         self.sweep_ctr.index_fill_(0, idx, 0)  # (a scalar assignment would wait for the stream)
@@ -372,8 +378,15 @@ class Server:
         n = len(done)
         pairs = self._to_dev(np.asarray([[s, s] for s in done], dtype=np.int32))
         m_dev = torch.empty((n, 15), dtype=torch.float64, device=self.device)
-        check(lib().hsg_batch_overlap(ctypes.byref(self._d), _ptr(pairs), n, _ptr(m_dev),
-                                      _stream(None)))
+        L_max = int(max(self.table[s]["L"] for s in done))
+        parts = lib().hsg_batch_parts(L_max)
+        if 1 < parts and n < 65536:
+            scratch = torch.empty(15 * n * parts, dtype=torch.float64, device=self.device)
+            check(lib().hsg_batch_overlap_parts(ctypes.byref(self._d), _ptr(pairs), n, L_max,
+                                                _ptr(scratch), _ptr(m_dev), _stream(None)))
+        else:
+            check(lib().hsg_batch_overlap(ctypes.byref(self._d), _ptr(pairs), n, _ptr(m_dev),
+                                          _stream(None)))
         idx = self._to_dev(np.asarray(done, dtype=np.int64))
         buf, k = self._d2h.take()
         # m (3), E and the sweeps made per lattice
