@@ -90,16 +90,38 @@ __device__ __forceinline__ void block_partials(double (&v)[kReduceSlots], int ns
 }
 
 // Energy over the colour-0 sites: every bond has exactly one colour-0 end (L even),
-// so H = -sum over colour-0 sites of sigma_i . h_i, all in binary64.  Workgroup b takes
-// tiles b, b + gridDim.x, ... of the colour.
+// so H = -sum over colour-0 sites of sigma_i . h_i, all in binary64.  Each XCD takes a
+// contiguous eighth of the tiles, its workgroups one after the other, so that a tile finds
+// its neighbours' rows and planes in the XCD's own L2 (with neighbouring tiles on eight
+// XCDs, L = 256 took 85 us, as it is 79, and L = 512 890 and 715, 4.5 TB/s).
 static_assert(kReduceThreads == kPassThreads, "a tile's sites are a workgroup's threads");
 template <typename R>
 __global__ __launch_bounds__(kReduceThreads) void energy_kernel(Geometry g, Planes<R> S,
                                                                 Planes<R> J, double* partials) {
   double v[kReduceSlots] = {0.0};
-  for (uint32_t tile = blockIdx.x; tile < (uint32_t)g.n_blocks; tile += gridDim.x) {
-    const TileSite ts = tile_site(g, tile);
-    if (ts.i < (uint32_t)g.plane) v[0] += colour0_bond_sum<R>(S, J, tile_site_offsets<R>(g, ts, 0));
+  constexpr int U = 2;  // tiles a thread reads at a time
+  // workgroup b of XCD b mod 8; gridDim.x is a multiple of 8 or a workgroup per tile
+  const uint32_t n = (uint32_t)g.n_blocks, all = gridDim.x;
+  const uint32_t per = all < n ? (n + 7u) / 8u : n, step = all < n ? all / 8u : n;
+  const uint32_t x = all < n ? blockIdx.x & 7u : 0u;
+  const uint32_t local =
+      all < n ? blockIdx.x >> 3 : (uint32_t)xcd_tile((int32_t)blockIdx.x, (int32_t)n);
+  const uint32_t end = min(per, n - min(n, x * per));
+  auto site = [&](uint32_t i, bool& has) {
+    const TileSite ts = tile_site(g, x * per + min(i, end - 1u));
+    has = i < end && ts.i < (uint32_t)g.plane;
+    return tile_site_offsets<R>(g, TileSite{ts.z, (uint32_t)min((int32_t)ts.i, g.plane - 1)}, 0);
+  };
+  for (uint32_t i = local; i < end; i += U * step) {
+    SiteOffsets o[U];
+    bool has[U];
+    double e[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) o[u] = site(i + (uint32_t)u * step, has[u]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) e[u] = colour0_bond_sum<R>(S, J, o[u]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[0] += has[u] ? e[u] : 0.0;
   }
   block_partials(v, 1, partials);
 }
