@@ -206,11 +206,177 @@ __global__ __launch_bounds__(T) void brick_kernel(BrickArgs<R> a) {
 
 // ---------------------------------------------------------------------- one workgroup
 
-// The lattice's sweeps in one workgroup of T threads.  Thread t owns sites t, t + T, ...
-// (ROUNDS of them) of each colour for the whole launch: their couplings, their neighbours'
-// places and their spins stay in registers; the other colour is read from LDS.
+// The lattice's sweeps in one workgroup, T threads on the sites of colour 0 and T on those of
+// colour 1.  A thread owns sites t, t + T, ... (ROUNDS of them) for the whole launch: their
+// couplings, their neighbours' places and their spins stay in registers; the other colour is
+// read from LDS.  A pass is a chain of dependent steps on one wave per SIMD or two, half of
+// it the draws, which need no spin: the colour that waits makes those of its next Monte
+// Carlo update.  us a sweep of k = 4 and one over-relaxation phase, each thread on both
+// colours / so: L = 8 3.0 / 2.1, 10 3.9 / 3.2, 12 6.5 / 5.8 (binary64 L = 8 4.0 / 3.5); k = 1
+// 2.3 / 1.7, 2.8 / 2.2, 4.5 / 4.2.
 template <typename R, PassMode MC, int T, int ROUNDS>
-__global__ __launch_bounds__(T) void tiny_kernel(TinyArgs<R> a) {
+__global__ __launch_bounds__(2 * T) void tiny_kernel(TinyArgs<R> a) {
+  constexpr int kCap = T * ROUNDS;
+  constexpr bool kMetropolis = MC == PassMode::Metropolis || MC == PassMode::MetropolisFull;
+  constexpr bool kFull = MC == PassMode::MetropolisFull;
+  __shared__ R lds[2][3][kCap];
+  __shared__ double s_red[16];
+  const uint32_t L = (uint32_t)a.L, Lh = L / 2, Nh = Lh * L * L;
+  const int32_t c = __builtin_amdgcn_readfirstlane((int32_t)threadIdx.x) >= T ? 1 : 0;
+  const uint32_t tid = threadIdx.x - (uint32_t)(c * T);
+  SiteBonds<R> jb[ROUNDS];
+  Vec3<R> sp[ROUNDS];
+  uint32_t site[ROUNDS], at[ROUNDS][6];  // neighbours' places in LDS: px, mx, py, my, pz, mz
+  const SmallDiv by_lh(Lh), by_l(L);
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    const uint32_t i = tid + (uint32_t)(r * T);
+    site[r] = 0;
+    if (i >= Nh) continue;
+    const uint32_t row = by_lh.div(i), z = by_l.div(row);
+    const SiteOffsets q = site_offsets<R>(L, Lh, (uint32_t)c, i, i - row * Lh, row - z * L, z);
+    const R* Jo = a.J + 3 * c * Nh;
+    const R* Jn = a.J + 3 * (1 - c) * Nh;
+    jb[r] = SiteBonds<R>{*plane_at(Jo, q.own),          *plane_at(Jn, q.mx),
+                         *plane_at(Jo + Nh, q.own),     *plane_at(Jn + Nh, q.my),
+                         *plane_at(Jo + 2 * Nh, q.own), *plane_at(Jn + 2 * Nh, q.mz)};
+    const R* S = a.spins + 3 * c * Nh;
+    sp[r] = Vec3<R>{S[i], S[Nh + i], S[2 * Nh + i]};
+    site[r] = q.site;
+    const uint32_t nb[6] = {q.px, q.mx, q.py, q.my, q.pz, q.mz};
+#pragma unroll
+    for (int k = 0; k < 6; ++k)
+      at[r][k] = nb[k] * (uint32_t)(sizeof(R) / OffsetUnit<R>::value) +
+                 (uint32_t)((1 - c) * 3 * kCap * (int)sizeof(R));
+  }
+  auto put = [&](int r) {
+    R* own = &lds[c][0][tid + (uint32_t)(r * T)];
+    own[0] = sp[r].x;
+    own[kCap] = sp[r].y;
+    own[2 * kCap] = sp[r].z;
+  };
+  auto each = [&](auto f) {
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r)
+      if (tid + (uint32_t)(r * T) < Nh) f(r);
+  };
+  auto field = [&](int r) {
+    const char* base = (const char*)&lds[0][0][0];
+    R h[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      auto s = [&](int d) { return *(const R*)(base + at[r][d] + k * kCap * (int)sizeof(R)); };
+      R acc = jb[r].px * s(0);
+      acc = dev_fma(jb[r].mx, s(1), acc);
+      acc = dev_fma(jb[r].py, s(2), acc);
+      acc = dev_fma(jb[r].my, s(3), acc);
+      acc = dev_fma(jb[r].pz, s(4), acc);
+      acc = dev_fma(jb[r].mz, s(5), acc);
+      h[k] = acc;
+    }
+    return Vec3<R>{h[0], h[1], h[2]};
+  };
+  // The draws of a sweep's first group of hits at the thread's first site, in two halves
+  // (words; trial points) that each fit behind a pass of the other colour.
+  uint32_t w[3 * kHits];
+  Draws<R, MC> d;
+  const bool mc = MC != PassMode::OverRelax && a.k_hits > 0;
+  auto ctx = [&](uint32_t sweep) {
+    return HitCtx<R>{a.beta, sweep, 0u, a.k_hits, a.seed_lo, a.seed_hi};
+  };
+  auto words = [&](uint32_t sweep) {
+    const HitCtx<R> hc = ctx(sweep);
+    if constexpr (kMetropolis)
+      hit_words<kFull>(w, site[0], 0u, a.k_hits, hc);
+    else
+      d = first_draws<R, MC>(site[0], hc);
+  };
+  auto points = [&] {
+    if constexpr (kMetropolis) {
+#pragma unroll
+      for (int g = 0; g < kHits; ++g)
+        if (kFull || g < a.k_hits) {
+          d.trial[g] = sphere_point_words<R>(w[3 * g], w[3 * g + 1]);
+          d.u[g] = unit_uniform<R>(w[3 * g + 2]);
+        }
+    }
+  };
+  each(put);
+  if (mc) {
+    words(a.sweep);
+    if (c == 0) points();
+  }
+  __syncthreads();
+  const double E0 = threadIdx.x == 0 ? *a.E : 0.0;
+  double dE = 0.0;
+  auto monte_carlo = [&](uint32_t sweep) {
+    each([&](int r) {
+      dE += apply_update<R, MC, kHits>(sp[r], field(r), site[r], ctx(sweep), r == 0 ? &d : nullptr);
+      put(r);
+    });
+  };
+  auto over_relax = [&] {
+    each([&](int r) {
+      sp[r] = reflect(sp[r], field(r));
+      put(r);
+    });
+  };
+  for (int32_t n = 0; n < a.n_sweeps; ++n) {
+    const uint32_t sweep = a.sweep + (uint32_t)n;
+    const bool more = mc && n + 1 < a.n_sweeps;
+    if (mc) {
+      if (c == 0) {
+        monte_carlo(sweep);
+      } else {
+        if (a.n_or == 0 && n > 0) words(sweep);
+        points();
+      }
+      __syncthreads();
+      if (c == 1) {
+        monte_carlo(sweep);
+      } else if (more) {
+        words(sweep + 1u);
+        if (a.n_or == 0) points();
+      }
+      __syncthreads();
+    }
+    for (int32_t phase = 1; phase <= a.n_or; ++phase) {
+      if (c == 0)
+        over_relax();
+      else if (phase == 1 && more)
+        words(sweep + 1u);
+      __syncthreads();
+      if (c == 1)
+        over_relax();
+      else if (phase == 1 && more)
+        points();
+      __syncthreads();
+    }
+    if (a.renorm_every > 0 && (sweep + 1u) % (uint32_t)a.renorm_every == 0u) {
+      each([&](int r) {
+        sp[r] = unit_vector(sp[r]);
+        put(r);
+      });
+      __syncthreads();
+    }
+  }
+  each([&](int r) {
+    const uint32_t i = tid + (uint32_t)(r * T);
+    R* S = a.spins + 3 * c * Nh;
+    S[i] = sp[r].x;
+    S[Nh + i] = sp[r].y;
+    S[2 * Nh + i] = sp[r].z;
+  });
+  if (mc) {
+    const double total = block_sum(dE, s_red);
+    if (threadIdx.x == 0) *a.E = E0 + total;
+  }
+}
+
+// The same with every thread on ROUNDS sites of both colours, for lattices whose 1024 threads
+// would have more sites each than registers, or more waves idle than there is to do for them.
+template <typename R, PassMode MC, int T, int ROUNDS>
+__global__ __launch_bounds__(T) void tiny_both_kernel(TinyArgs<R> a) {
   constexpr int kCap = T * ROUNDS;
   __shared__ R lds[2][3][kCap];
   __shared__ double s_red[16];
@@ -312,17 +478,22 @@ __global__ __launch_bounds__(T) void tiny_kernel(TinyArgs<R> a) {
 template <typename R, PassMode MC>
 hipError_t launch_tiny_as(const TinyArgs<R>& a, hipStream_t st) {
   const int32_t Nh = a.L * a.L * a.L / 2;
+  const dim3 one(1);
   if (Nh <= 256)
-    hipLaunchKernelGGL((tiny_kernel<R, MC, 256, 1>), dim3(1), dim3(256), 0, st, a);
-  else if (Nh <= 512)
-    hipLaunchKernelGGL((tiny_kernel<R, MC, 512, 1>), dim3(1), dim3(512), 0, st, a);
+    hipLaunchKernelGGL((tiny_kernel<R, MC, 256, 1>), one, dim3(512), 0, st, a);
+  // us a sweep of k = 4 (1) by colour / by both: binary32 L = 14, three rounds of sites
+  // against two, 8.5 / 8.4 (6.7 / 5.0); binary64 L = 10, two against one, 7.3 / 6.5 (4.6 / 3.9)
   else if constexpr (sizeof(R) == 4) {
-    if (Nh <= 1024)
-      hipLaunchKernelGGL((tiny_kernel<R, MC, 512, 2>), dim3(1), dim3(512), 0, st, a);
+    if (Nh <= 512)
+      hipLaunchKernelGGL((tiny_kernel<R, MC, 512, 1>), one, dim3(1024), 0, st, a);
+    else if (Nh <= 1024)
+      hipLaunchKernelGGL((tiny_kernel<R, MC, 512, 2>), one, dim3(1024), 0, st, a);
     else if (Nh <= 1408)
-      hipLaunchKernelGGL((tiny_kernel<R, MC, 704, 2>), dim3(1), dim3(704), 0, st, a);
+      hipLaunchKernelGGL((tiny_both_kernel<R, MC, 704, 2>), one, dim3(704), 0, st, a);
     else
       return hipErrorInvalidValue;
+  } else if (Nh <= 512) {
+    hipLaunchKernelGGL((tiny_both_kernel<R, MC, 512, 1>), one, dim3(512), 0, st, a);
   } else {
     return hipErrorInvalidValue;
   }
@@ -401,6 +572,7 @@ hipError_t launch_brick(const BrickArgs<R>& a0, PassMode mode, hipStream_t st) {
 
 template <typename R>
 hipError_t launch_tiny(const TinyArgs<R>& a, PassMode mc, hipStream_t st) {
+  if (a.k_hits == 0) return launch_tiny_as<R, PassMode::OverRelax>(a, st);
   if (mc == PassMode::HeatBath) return launch_tiny_as<R, PassMode::HeatBath>(a, st);
   if (metropolis_mode(a.k_hits) == PassMode::MetropolisFull)
     return launch_tiny_as<R, PassMode::MetropolisFull>(a, st);
