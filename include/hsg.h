@@ -365,6 +365,15 @@ int hsg_batch_tile_sweep(const hsg_batch *b, const int32_t *tiles_dev,
                          double *partials_dev, int32_t any_mc, int32_t max_n_or, int32_t renorm,
                          int32_t n_sweeps, void *stream);
 
+/* The same, all sweeps of the call on one group of chains after the other, for batches
+ * larger than the memory-side cache holds: group g is the tiles [groups[g], groups[g + 1])
+ * (host memory, n_groups + 1 ascending values from 0 to the number of tiles), whole chains.
+ * A chain without tiles is left as it is. */
+int hsg_batch_group_sweep(const hsg_batch *b, const int32_t *tiles_dev,
+                          const int32_t *first_tile_dev, const int32_t *groups, int32_t n_groups,
+                          int32_t tile_sites, double *partials_dev, int32_t any_mc,
+                          int32_t max_n_or, int32_t renorm, int32_t n_sweeps, void *stream);
+
 /* Parallel tempering over temperature ladders of chains of a batch. */
 typedef struct hsg_pt {
   int32_t n_ladders;

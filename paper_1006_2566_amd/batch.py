@@ -64,10 +64,11 @@ def _bind():
     L.hsg_pt_overlap_fourier.argtypes = [PP, BP, P, I32, P, P]
     L.hsg_batch_tiles.argtypes = [P, I32, P, I32, I32, P, I32, ctypes.POINTER(I32)]
     L.hsg_batch_tile_sweep.argtypes = [BP, P, P, I32, I32, P, I32, I32, I32, I32, P]
+    L.hsg_batch_group_sweep.argtypes = [BP, P, P, P, I32, I32, P, I32, I32, I32, I32, P]
     for name in ("hsg_batch_check", "hsg_batch_init", "hsg_batch_sweep",
                  "hsg_batch_energy", "hsg_batch_overlap", "hsg_pt_exchange", "hsg_pt_overlap",
                  "hsg_batch_overlap_fourier", "hsg_pt_overlap_fourier", "hsg_batch_tiles",
-                 "hsg_batch_tile_sweep", "hsg_batch_init_parts", "hsg_batch_overlap_parts"):
+                 "hsg_batch_tile_sweep", "hsg_batch_group_sweep", "hsg_batch_init_parts", "hsg_batch_overlap_parts"):
         getattr(L, name).restype = ctypes.c_int
     _bound = True
 
@@ -115,6 +116,22 @@ def tiles_pay(specs) -> bool:
     most = max(sites)
     limit = 2048 if most >= 32 ** 3 else 512 if most >= 20 ** 3 else 192 if most >= 16 ** 3 else 0
     return sum(sites) <= limit * most
+
+
+# Bytes of spins that chains advanced together may have: with them in the 256 MB memory-side
+# cache (their couplings, shared by the chains of a sample, are a few per cent of that).
+GROUP_SPIN_BYTES = 256_000_000
+
+
+def groups_pay(specs) -> bool:
+    """Whether chains too many for tiles_pay run over tiles all the same, in groups that the
+    memory-side cache holds, every sweep of a call on one group after the other: where most
+    sites are in chains of L >= 32.  Their smaller chains, if they come to no more than the
+    tiles of the others, have a workgroup each.  ms for ten sweeps, a workgroup per chain /
+    in groups: 3072 chains of L = 48 k = 4 39.4 / 35.6, k = 1 36.9 / 26.6; 3072 of L = 32
+    11.1 / 10.8, k = 1 9.9 / 7.9 (L = 24 4.8 / 5.0; 16 1.6 / 1.9); L = 48 by 64, 128, 512 MB
+    37.8, 37.0, 36.7."""
+    return 2 * sum(c.L ** 3 for c in specs if c.L >= 32) > sum(c.L ** 3 for c in specs)
 
 
 class Batch:
@@ -171,7 +188,17 @@ class Batch:
                          self.remaining.data_ptr() if self.remaining is not None else None,
                          self.order.data_ptr(), threads, 0)
         self._export_work: dict[int, torch.Tensor] = {}
-        self._tiles = self._tile_table() if tiles_pay(self.specs) else None
+        self._tiles, self._alone = None, None
+        if tiles_pay(self.specs):
+            self._tiles = self._tile_table()
+        elif groups_pay(self.specs):
+            large = np.flatnonzero(table["L"] >= 32)
+            if int((table["L"][large].astype(np.int64) ** 3 // 2 // TILE_SITES).sum()) < self.n:
+                large = None
+            self._tiles = self._tile_table(large)
+            small = np.asarray(order)[table["L"][np.asarray(order)] < 32]
+            if large is not None and small.size:
+                self._alone = torch.from_numpy(small.astype(np.int32)).to(dev)
         if init:
             self.init(stream)
 
@@ -186,31 +213,46 @@ class Batch:
     def init(self, stream=None) -> None:
         check(lib().hsg_batch_init(ctypes.byref(self._d), _stream(stream)))
 
-    def _tile_table(self) -> tuple:
-        """Tiles of every chain, each chain's first tile and the tiles' energy partials."""
+    def _tile_table(self, chains: np.ndarray | None = None) -> tuple:
+        """Tiles of every chain (or of these, ascending: the others have none), each chain's
+        first tile, the number of tiles, their energy partials and the groups: the first tile
+        of each, and the number of tiles."""
         Ls = self.table["L"].astype(np.int64)
-        count = -(-(Ls ** 3 // 2) // TILE_SITES)
+        active = np.arange(self.n) if chains is None else chains
+        has = np.zeros(self.n, dtype=np.int64)
+        has[active] = 1
+        count = -(-(Ls ** 3 // 2) // TILE_SITES) * has
         first = np.concatenate([[0], np.cumsum(count)])
         n = ctypes.c_int32()
         tiles = np.zeros(2 * int(first[-1]), dtype=np.int32)
-        active = np.arange(self.n, dtype=np.int32)
+        active = np.ascontiguousarray(active, dtype=np.int32)
         check(lib().hsg_batch_tiles(self.table.ctypes.data_as(ctypes.c_void_p), self.n,
-                                    active.ctypes.data_as(ctypes.c_void_p), self.n, TILE_SITES,
+                                    active.ctypes.data_as(ctypes.c_void_p), active.size, TILE_SITES,
                                     tiles.ctypes.data_as(ctypes.c_void_p), int(first[-1]),
                                     ctypes.byref(n)))
+        # groups of about the same number of bytes, the last chain of one where its share ends
+        end = np.cumsum(Ls ** 3 * has) * 3 * self.spins.element_size()
+        n_groups = -(-int(end[-1]) // GROUP_SPIN_BYTES)
+        last = np.searchsorted(end, end[-1] * np.arange(1, n_groups) / n_groups)
+        groups = np.unique(np.concatenate([[0], first[last + 1], first[-1:]])).astype(np.int32)
         return (torch.from_numpy(tiles).to(self.device),
                 torch.from_numpy(first.astype(np.int32)).to(self.device), n.value,
-                torch.zeros(n.value, dtype=torch.float64, device=self.device))
+                torch.zeros(n.value, dtype=torch.float64, device=self.device), groups)
 
     def sweep(self, n_sweeps: int, stream=None) -> None:
         if self._tiles is None:
             check(lib().hsg_batch_sweep(ctypes.byref(self._d), int(n_sweeps), _stream(stream)))
             return
-        tiles, first, n, partials = self._tiles
-        check(lib().hsg_batch_tile_sweep(
-            ctypes.byref(self._d), _ptr(tiles), _ptr(first), n, TILE_SITES, _ptr(partials),
-            int(any(c.k > 0 for c in self.specs)), max(c.n_or for c in self.specs),
-            int(any(c.renorm_every > 0 for c in self.specs)), int(n_sweeps), _stream(stream)))
+        if self._alone is not None:
+            d = _Batch.from_buffer_copy(self._d)
+            d.n_chains, d.order = self._alone.numel(), self._alone.data_ptr()
+            check(lib().hsg_batch_sweep(ctypes.byref(d), int(n_sweeps), _stream(stream)))
+        tiles, first, _, partials, groups = self._tiles
+        check(lib().hsg_batch_group_sweep(
+            ctypes.byref(self._d), _ptr(tiles), _ptr(first), groups.ctypes.data, groups.size - 1,
+            TILE_SITES, _ptr(partials), int(any(c.k > 0 for c in self.specs)),
+            max(c.n_or for c in self.specs), int(any(c.renorm_every > 0 for c in self.specs)),
+            int(n_sweeps), _stream(stream)))
 
     def energies(self, recompute: bool = False, stream=None) -> torch.Tensor:
         if not recompute:

@@ -872,10 +872,22 @@ int hsg_batch_tile_sweep(const hsg_batch* b, const int32_t* tiles_dev,
                          const int32_t* first_tile_dev, int32_t n_tiles, int32_t tile_sites,
                          double* partials_dev, int32_t any_mc, int32_t max_n_or, int32_t renorm,
                          int32_t n_sweeps, void* stream) {
+  const int32_t all[2] = {0, n_tiles};
+  return hsg_batch_group_sweep(b, tiles_dev, first_tile_dev, all, 1, tile_sites, partials_dev,
+                               any_mc, max_n_or, renorm, n_sweeps, stream);
+}
+
+int hsg_batch_group_sweep(const hsg_batch* b, const int32_t* tiles_dev,
+                          const int32_t* first_tile_dev, const int32_t* groups, int32_t n_groups,
+                          int32_t tile_sites, double* partials_dev, int32_t any_mc,
+                          int32_t max_n_or, int32_t renorm, int32_t n_sweeps, void* stream) {
   int rc = check_batch(b);
   if (rc) return rc;
-  if (!tiles_dev || !first_tile_dev || !partials_dev || n_tiles < b->n_chains || n_sweeps < 0 ||
-      max_n_or < 0 || max_n_or > 0x7FFF)
+  if (!groups || n_groups < 1 || groups[0] != 0) return fail(HSG_EINVAL, "bad groups");
+  for (int32_t g = 0; g < n_groups; ++g)
+    if (groups[g + 1] <= groups[g]) return fail(HSG_EINVAL, "groups must ascend");
+  if (!tiles_dev || !first_tile_dev || !partials_dev || groups[n_groups] < b->n_chains ||
+      n_sweeps < 0 || max_n_or < 0 || max_n_or > 0x7FFF)
     return fail(HSG_EINVAL, "bad tiles, partials, n_sweeps or max_n_or");
   if (tile_sites < 64 || tile_sites > 1024 || (tile_sites & 63))
     return fail(HSG_EINVAL, "tile_sites must be a multiple of 64 in [64, 1024]");
@@ -884,12 +896,12 @@ int hsg_batch_tile_sweep(const hsg_batch* b, const int32_t* tiles_dev,
   const int32_t first_phase = any_mc ? 0 : 1;
   return device_status(
       b->dtype == HSG_F32
-          ? hsg::launch_batch_tile_sweep<float>(b, tiles_dev, first_tile_dev, n_tiles, tile_sites,
-                                                partials_dev, first_phase, max_n_or, renorm,
-                                                n_sweeps, st)
-          : hsg::launch_batch_tile_sweep<double>(b, tiles_dev, first_tile_dev, n_tiles, tile_sites,
-                                                 partials_dev, first_phase, max_n_or, renorm,
-                                                 n_sweeps, st),
+          ? hsg::launch_batch_tile_sweep<float>(b, tiles_dev, first_tile_dev, groups, n_groups,
+                                                tile_sites, partials_dev, first_phase, max_n_or,
+                                                renorm, n_sweeps, st)
+          : hsg::launch_batch_tile_sweep<double>(b, tiles_dev, first_tile_dev, groups, n_groups,
+                                                 tile_sites, partials_dev, first_phase, max_n_or,
+                                                 renorm, n_sweeps, st),
       "batch tile sweep");
 }
 

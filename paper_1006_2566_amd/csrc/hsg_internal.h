@@ -270,9 +270,10 @@ hipError_t launch_batch_pass_sweep(const hsg_batch* b, const int32_t* tiles, int
                                    int32_t n_sweeps, hipStream_t st);
 template <typename R>
 hipError_t launch_batch_tile_sweep(const hsg_batch* b, const int32_t* tiles,
-                                   const int32_t* first_tile, int32_t n_tiles, int32_t tile_sites,
-                                   double* partials, int32_t first_phase, int32_t max_n_or,
-                                   int32_t renorm, int32_t n_sweeps, hipStream_t st);
+                                   const int32_t* first_tile, const int32_t* groups,
+                                   int32_t n_groups, int32_t tile_sites, double* partials,
+                                   int32_t first_phase, int32_t max_n_or, int32_t renorm,
+                                   int32_t n_sweeps, hipStream_t st);
 hipError_t launch_copy_double(const double* src, double* dst, hipStream_t stream);
 
 }  // namespace hsg

@@ -508,6 +508,7 @@ __global__ __launch_bounds__(256) void tile_finish_kernel(const int32_t* first_t
   __shared__ double s_red[16];
   const int32_t c = (int32_t)blockIdx.x;
   const int32_t t1 = first_tile[c + 1];
+  if (t1 == first_tile[c]) return;  // not a chain of this call
   double acc = 0.0;
   for (int32_t t = first_tile[c] + (int32_t)threadIdx.x; t < t1; t += 256) {
     acc += partials[t];
@@ -671,11 +672,14 @@ hipError_t launch_batch_pass_sweep(const hsg_batch* b, const int32_t* tiles, int
 
 template <typename R>
 hipError_t launch_batch_tile_sweep(const hsg_batch* b, const int32_t* tiles,
-                                   const int32_t* first_tile, int32_t n_tiles, int32_t tile_sites,
-                                   double* partials, int32_t first_phase, int32_t max_n_or,
-                                   int32_t renorm, int32_t n_sweeps, hipStream_t st) {
-  launch_tile_passes<R>(b, tiles, partials, n_tiles, tile_sites, first_phase, max_n_or, renorm,
-                        n_sweeps, st);
+                                   const int32_t* first_tile, const int32_t* groups,
+                                   int32_t n_groups, int32_t tile_sites, double* partials,
+                                   int32_t first_phase, int32_t max_n_or, int32_t renorm,
+                                   int32_t n_sweeps, hipStream_t st) {
+  for (int32_t g = 0; g < n_groups; ++g)
+    launch_tile_passes<R>(b, tiles + 2 * (int64_t)groups[g], partials + groups[g],
+                          groups[g + 1] - groups[g], tile_sites, first_phase, max_n_or, renorm,
+                          n_sweeps, st);
   hipLaunchKernelGGL(tile_finish_kernel, dim3((unsigned)b->n_chains), dim3(256), 0, st, first_tile,
                      partials, b->E, b->sweep, b->remaining, n_sweeps);
   return hipGetLastError();
@@ -696,8 +700,9 @@ hipError_t launch_batch_tile_sweep(const hsg_batch* b, const int32_t* tiles,
   template hipError_t launch_batch_pass_sweep<R>(const hsg_batch*, const int32_t*, int32_t,   \
                                                  int32_t, int32_t, int32_t, int32_t, hipStream_t); \
   template hipError_t launch_batch_tile_sweep<R>(const hsg_batch*, const int32_t*,             \
-                                                 const int32_t*, int32_t, int32_t, double*,     \
-                                                 int32_t, int32_t, int32_t, int32_t, hipStream_t);
+                                                 const int32_t*, const int32_t*, int32_t,       \
+                                                 int32_t, double*, int32_t, int32_t, int32_t,   \
+                                                 int32_t, hipStream_t);
 HSG_BATCH_INSTANTIATE(float)
 HSG_BATCH_INSTANTIATE(double)
 
