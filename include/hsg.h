@@ -81,10 +81,10 @@ extern "C" {
 #define HSG_PLANE_LAUNCH 32 /* one launch per z slab of tiles -- per z plane for L >= 24 --
                                instead of one per pass: 2L launches per phase, the CA
                                analogue's launch count.  Not with HSG_FUSED */
-#define HSG_PHASE_LAUNCH 128 /* each over-relaxation phase -- its colour-0 and colour-1
-                               passes -- runs as one launch that marches through z with a
-                               window of planes in LDS, reading and writing the spins once
-                               (any even L from 98 to 1024, whose offsets fit 32 bits, and
+#define HSG_PHASE_LAUNCH 128 /* an over-relaxation phase -- its colour-0 and colour-1
+                               passes -- or two in a row run as one launch that marches
+                               through z with a window of planes in LDS, reading and writing
+                               the spins once (any even L from 98 to 1024, whose offsets fit 32 bits, and
                                L = 64; else ignored).  Uses the second spin array of the
                                work buffer: without one HSG_EINVAL where L is a multiple of
                                64, ignored elsewhere.  Not with HSG_FUSED */
@@ -188,7 +188,8 @@ int hsg_sweep_noalloc(hsg_lattice *lat, const hsg_sweep_params *p, int32_t n_swe
 #define HSG_LAUNCH_OR_PHASE 3     /* over-relaxation phase in one launch (HSG_PHASE_LAUNCH) */
 #define HSG_LAUNCH_OR_PHASE_MC 4  /* the same carrying the next colour-0 Monte Carlo pass
                                      (HSG_PHASE_MC) */
-#define HSG_LAUNCH_MARCH 5        /* fused passes (HSG_FUSED, HSG_BRICK) */
+#define HSG_LAUNCH_MARCH 5        /* fused passes (HSG_FUSED, HSG_BRICK), two over-relaxation
+                                     phases in one launch */
 
 /* Measurement form of hsg_sweep: the same sweeps (same arguments, same results), with a
  * pair of HIP events recorded on `stream` around each of the call's first `capacity`

@@ -75,11 +75,12 @@ def default_flags(L: int, dtype=None) -> int:
 PHASE_CACHE_BYTES = (204_000_000, 272_000_000)
 
 
-def call_flags(L: int, dtype=None, k: int = 1, heat_bath: bool = False) -> int:
-    """Traversal flags of a sweep of k hits that names none: over default_flags, every even
-    L from 98 to 1024 runs its over-relaxation phases as one launch each, with the next
-    sweep's colour-0 Monte Carlo pass where that pass is short.  us a sweep on MI355X (one
-    over-relaxation phase; colour passes / a launch per phase / with the Monte Carlo pass):
+def call_flags(L: int, dtype=None, k: int = 1, heat_bath: bool = False, n_or: int = 1) -> int:
+    """Traversal flags of a sweep that names none, by its hits and over-relaxation phases: over
+    default_flags, every even L from 98 to 1024 runs its over-relaxation phases in launches
+    of one or two, the last of a sweep with the next sweep's colour-0 Monte Carlo pass where
+    that pays.  us a sweep on MI355X with one over-relaxation phase, colour passes / a launch
+    per phase / with the Monte Carlo pass:
 
       binary32  L = 98 k = 1  28.4 / 26.5 / 25.3     98 k = 2  29.4 / 27.3 / 27.6
                    122 k = 2  42.6 / 40.6 / 39.9    178 k = 1   101 / 89.4 / 79.2
@@ -95,23 +96,34 @@ def call_flags(L: int, dtype=None, k: int = 1, heat_bath: bool = False) -> int:
                    448 k = 8  5959 / 5601 / 5333    320 heat bath 1656 / 1386 / 1689
 
     so binary32 takes the pass along with one hit, from L = 114 with two, from 128 with three
-    or a heat bath, from 226 with four and from 256 always; binary64 with one hit from 126, with up to four
-    from 180, with more from 448, never a heat bath.  Where only the passes' footprint fits
-    the memory-side cache (206 <= L <= 224, in binary64 162 to 178) they stay, but for one hit
-    in binary32."""
+    or a heat bath, from 226 with four and from 256 always; binary64 with one hit from 126,
+    with up to four from 180, with more from 448, never a heat bath.  Where only the passes'
+    footprint fits the memory-side cache (206 <= L <= 224, in binary64 162 to 178) they stay,
+    but for one hit in binary32.
+
+    With an even number of phases the Monte Carlo pass would break up a pair of them.  Two
+    phases, passes / pairs / with the Monte Carlo pass: binary32 L = 130 k = 4 73.2 / 61.1 /
+    67.3, 162 k = 1 119 / 99.0 / 95.5, 210 k = 4 245 / 227 / 236, 258 k = 1 602 / 448 / 471,
+    320 k = 4 1139 / 906 / 827, 512 k = 8 5338 / 4004 / 4036; binary64 130 k = 1 128 / 110 /
+    115, 258 k = 1 1251 / 971 / 975, 384 k = 4 4292 / 3257 / 3489: it goes along from L = 310
+    with up to four hits or a heat bath, in binary32 only.  An odd number is as one phase,
+    without the exception for the cache (218 k = 4, three phases: 362 / 343 / 340)."""
     f64 = dtype is not None and str(dtype) in ("torch.float64", "float64")
     f = default_flags(L, dtype)
     if L < PHASE_MIN_L or not phase_supported(L):
         return f
-    if f64:
+    if n_or > 0 and n_or % 2 == 0:
+        carry = not f64 and L >= 310 and (heat_bath or k <= 4)
+    elif f64:
         carry = not heat_bath and (L >= 448 or (L >= 126 and k <= 1) or (L >= 180 and k <= 4))
     else:
         carry = (L >= (128 if heat_bath or k == 3 else 226 if k == 4 else 256) or
                  (not heat_bath and (k <= 1 or (k == 2 and L >= 114))))
     lo, hi = PHASE_CACHE_BYTES
-    if lo < 6 * L ** 3 * (8 if f64 else 4) < hi and (f64 or heat_bath or k != 1):
+    if (lo < 6 * L ** 3 * (8 if f64 else 4) < hi and n_or <= 1 and k > 0 and
+            (f64 or heat_bath or k != 1)):
         return f
-    return f | (HSG_PHASE_MC if carry else HSG_PHASE_LAUNCH)
+    return f & ~HSG_PHASE_MC | (HSG_PHASE_MC if carry and k > 0 else HSG_PHASE_LAUNCH)
 
 
 class HsgError(RuntimeError):
@@ -262,8 +274,8 @@ class Lattice:
     def sweep(self, T: float, k: int = 1, n_or: int = 0, renorm_every: int = 0,
               n_sweeps: int = 1, heat_bath: bool = False, flags: int | None = None,
               stream=None) -> None:
-        """n_sweeps sweeps; flags None = call_flags(L, dtype, k, heat_bath)."""
-        f = call_flags(self.L, self.dtype, k, heat_bath) if flags is None else int(flags)
+        """n_sweeps sweeps; flags None = call_flags(L, dtype, k, heat_bath, n_or)."""
+        f = call_flags(self.L, self.dtype, k, heat_bath, n_or) if flags is None else int(flags)
         p = _SweepParams(float(T), int(k), int(n_or), int(renorm_every),
                          (HSG_HEAT_BATH if heat_bath else 0) | f)
         check(lib().hsg_sweep(ctypes.byref(self._d), ctypes.byref(p), int(n_sweeps),
@@ -275,7 +287,7 @@ class Lattice:
         """As sweep(), with every launch timed by HIP events on the launch stream:
         [(launch kind, ms)] in launch order (hsg_sweep_timed; waits for the stream)."""
         import numpy as np
-        f = call_flags(self.L, self.dtype, k, heat_bath) if flags is None else int(flags)
+        f = call_flags(self.L, self.dtype, k, heat_bath, n_or) if flags is None else int(flags)
         p = _SweepParams(float(T), int(k), int(n_or), int(renorm_every),
                          (HSG_HEAT_BATH if heat_bath else 0) | f)
         kinds = np.zeros(capacity, dtype=np.int32)

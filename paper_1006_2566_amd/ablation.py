@@ -14,9 +14,9 @@ sweep flags, and every analogue computes exactly the default schedule's spins:
     CA    HSG_PLANE_LAUNCH                   one launch per z plane (2L per phase)
     SM    HSG_FUSED | HSG_MARCH_PHASE        LDS plane march, one phase (2 passes) per launch
     SM4P  HSG_FUSED                          LDS plane march, up to four passes per launch
-    PH    HSG_SNAKE | HSG_PHASE_LAUNCH       each over-relaxation phase as one launch (a
-                                             lean one-phase LDS march; Metropolis phases
-                                             pass by pass as in GM+S)
+    PH    HSG_SNAKE | HSG_PHASE_LAUNCH       over-relaxation phases in launches of one or
+                                             two (a lean LDS march; Metropolis phases pass
+                                             by pass as in GM+S)
     PH+MC HSG_SNAKE | HSG_PHASE_MC           PH, the launch of each phase also running the
                                              next sweep's colour-0 Metropolis pass
 

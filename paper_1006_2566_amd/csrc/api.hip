@@ -121,14 +121,15 @@ bool renorm_due(const hsg_sweep_params* p, uint64_t sweep) {
 
 // Pass-by-pass schedule: one launch per colour pass over the whole lattice, or with
 // HSG_PLANE_LAUNCH one launch per z slab of tiles (one z plane from L = 24 up).  With
-// HSG_PHASE_LAUNCH each over-relaxation phase is one launch reading one spin array and
-// writing the other (the lattice's and the work buffer's second one); when a call would
-// run an odd number of them, its last phase (never one that carries a Monte Carlo pass)
-// runs as two colour passes in place instead, so the spins end in the lattice's own
-// array without a copy (two passes cost less than a phase launch plus a copy of the
-// lattice).  With HSG_PHASE_MC the launch of a sweep's last over-relaxation phase also runs the colour-0 Monte Carlo
-// pass of the next sweep of the call (and the renormalisation between them when due);
-// that sweep then starts with its colour-1 pass.
+// HSG_PHASE_LAUNCH over-relaxation phases are launches that read one spin array and write
+// the other (the lattice's and the work buffer's second one), two phases to a launch where
+// one follows the other with nothing between them.  With HSG_PHASE_MC the launch of a
+// sweep's last over-relaxation phase, alone, also runs the colour-0 Monte Carlo pass of the
+// next sweep of the call (and the renormalisation between them when due); that sweep then
+// starts with its colour-1 pass.  The spins have to end in the lattice's own array: when a
+// call would take an odd number of such launches, its last phase (which carries no Monte
+// Carlo pass) runs as two colour passes in place instead, or if it shares a launch the two
+// phases run alone (two passes cost less than a phase launch plus a copy of the lattice).
 template <typename R>
 int sweep_plain(hsg_lattice* lat, const hsg_sweep_params* p, int32_t n_sweeps, hipStream_t st,
                 double* partials) {
@@ -143,9 +144,29 @@ int sweep_plain(hsg_lattice* lat, const hsg_sweep_params* p, int32_t n_sweeps, h
                 phase_launch ? (R*)((char*)lat->work + fused_offset(lat->L)) : nullptr};
   int cur = 0;  // buffer holding the current spins (phase launches flip it)
   const bool phase_mc = phase_launch && (p->flags & HSG_PHASE_MC) && p->k_hits > 0;
-  // an odd count of phase launches: the call's last phase runs as colour passes
-  const bool last_as_passes =
-      phase_launch && (((int64_t)n_sweeps * p->n_or) & 1) != 0;
+  const auto carries = [&](int32_t n, int32_t phase) {
+    return phase_mc && phase == p->n_or && n + 1 < n_sweeps;
+  };
+  // whether an over-relaxation phase follows this one directly and may share its launch
+  const auto pairs = [&](int32_t n, int32_t phase) {
+    if (phase < p->n_or) return !carries(n, phase + 1);
+    return p->k_hits == 0 && n + 1 < n_sweeps && !renorm_due(p, lat->sweep + (uint64_t)n);
+  };
+  bool last_as_passes = false;
+  int32_t last_pair = INT32_MAX;  // sweep of the last two phases that share a launch
+  if (phase_launch && p->n_or > 0) {
+    int64_t launches = 0;
+    bool shared = false, second = false;  // the phase shares a launch; as the second of it
+    for (int32_t n = 0; n < n_sweeps; ++n)
+      for (int32_t phase = 1; phase <= p->n_or; ++phase) {
+        second = shared && !second;
+        if (second) continue;
+        shared = pairs(n, phase);
+        ++launches;
+      }
+    last_as_passes = (launches & 1) != 0 && !shared;
+    if ((launches & 1) != 0 && shared) last_pair = n_sweeps - (p->n_or > 1 ? 1 : 2);
+  }
   PhaseArgs<R> ph{};
   ph.J = (const R*)lat->J;
   ph.beta = (R)(1.0 / p->T);
@@ -168,6 +189,7 @@ int sweep_plain(hsg_lattice* lat, const hsg_sweep_params* p, int32_t n_sweeps, h
   const bool by_slab = (p->flags & HSG_PLANE_LAUNCH) != 0;
   const int32_t n_slabs = (g.L + g.slab - 1) / g.slab;
   int32_t pass_count = 0;
+  bool paired = false;    // this over-relaxation phase ran in the last launch
   bool mc0_done = false;  // this sweep's colour-0 Monte Carlo pass ran in the last launch
   for (int32_t n = 0; n < n_sweeps; ++n) {
     const uint64_t sweep = lat->sweep + (uint64_t)n;
@@ -177,15 +199,27 @@ int sweep_plain(hsg_lattice* lat, const hsg_sweep_params* p, int32_t n_sweeps, h
       if (phase == 0 && p->k_hits == 0) continue;
       a.phase = (uint32_t)phase;
       const bool last_phase = n + 1 == n_sweeps && phase == p->n_or;
+      if (paired && phase > 0) {
+        paired = false;
+        pass_count += 2;
+        continue;
+      }
       if (phase_launch && phase > 0 && !(last_as_passes && last_phase)) {
-        const bool then_mc = phase_mc && phase == p->n_or && n + 1 < n_sweeps;
+        const bool then_mc = carries(n, phase);
+        paired = pairs(n, phase) && !(n >= last_pair && phase + 2 > p->n_or);
         ph.in = bufs[cur];
         ph.out = bufs[1 - cur];
         ph.mc_sweep = (uint32_t)(sweep + 1);
         ph.renorm = then_mc && renorm_due(p, sweep) ? 1 : 0;
         int rc = device_status(
-            recorded(then_mc ? HSG_LAUNCH_OR_PHASE_MC : HSG_LAUNCH_OR_PHASE, st,
-                     [&] { return launch_phase<R>(ph, then_mc ? mc : PassMode::OverRelax, st); }),
+            recorded(paired    ? HSG_LAUNCH_MARCH
+                     : then_mc ? HSG_LAUNCH_OR_PHASE_MC
+                               : HSG_LAUNCH_OR_PHASE,
+                     st,
+                     [&] {
+                       return paired ? launch_phase_pair<R>(ph, st)
+                                     : launch_phase<R>(ph, then_mc ? mc : PassMode::OverRelax, st);
+                     }),
             "phase launch");
         if (rc) return rc;
         cur = 1 - cur;

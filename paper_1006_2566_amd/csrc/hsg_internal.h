@@ -153,6 +153,9 @@ bool phase_always(int32_t L);
 // mc: the mode of the pass that follows the phase, PassMode::OverRelax for the phase alone.
 template <typename R>
 hipError_t launch_phase(const PhaseArgs<R>& a, PassMode mc, hipStream_t stream);
+// Two over-relaxation phases.
+template <typename R>
+hipError_t launch_phase_pair(const PhaseArgs<R>& a, hipStream_t stream);
 
 bool march_supported(int32_t L);
 int32_t march_blocks(int32_t L);

@@ -362,6 +362,201 @@ __device__ __forceinline__ void row_march(const PhaseArgs<R>& a) {
   }
 }
 
+// Two over-relaxation phases in one launch: 36 bytes a site for both.  A thread has one place
+// (row r, column j of a window of ny + 8 rows) for the whole march and both colours; with q
+// the plane of a step:
+//
+//   A  phase 1, colour 0, plane q      on the tile and a ring of 3
+//   B  phase 1, colour 1, plane q - 1  ... of 2
+//   C  phase 2, colour 0, plane q - 3  ... of 1
+//   D  phase 2, colour 1, plane q - 4  on the tile
+//
+// A and C, then a barrier, B and D, then a barrier.  C and B replace what they update in
+// LDS, six planes of colour 0 and seven of colour 1 (160 KB); the couplings of A and B wait
+// three steps in registers for C and D.  The rings cost a third to a half of the arithmetic
+// and nz + 10 steps for nz planes, which stays less than the second reading and writing of
+// the lattice: us for two phases, alone / together, binary32 L = 98 23.4 / 23.0, 128 34.7 /
+// 28.0, 150 52 / 44, 208 149 / 130, 256 272 / 256, 320 515 / 435, 512 2130 / 1850; binary64
+// 128 63 / 63, 180 213 / 180, 256 588 / 529, 384 1970 / 1669.  At L = 128 a step takes 1.8
+// us: 44 waves' worth of sites, two barriers and the latency between them on 16 waves.
+template <typename R>
+constexpr int kPairThreads = sizeof(R) == 4 ? 1024 : 512;
+template <typename R>
+__global__ __launch_bounds__(kPairThreads<R>) void phase_pair_kernel(PhaseArgs<R> a) {
+  constexpr int N = kPairThreads<R>, K0 = 6, K1 = 7;
+  constexpr uint32_t E = sizeof(R);
+  __shared__ R l0[K0 * 3 * N], l1[K1 * 3 * N];
+  const int32_t tid = (int32_t)threadIdx.x;
+  const int32_t L = a.L, Lh = L / 2;
+  const int64_t zs = (int64_t)Lh * L, Nh = zs * L;
+  const uint32_t tile = (uint32_t)xcd_tile((int32_t)blockIdx.x, (int32_t)gridDim.x);
+  const SmallDiv dx{(uint32_t)a.n[0], a.inv[0]}, dy{(uint32_t)a.n[1], a.inv[1]},
+      dz{(uint32_t)a.n[2], a.inv[2]};
+  const uint32_t r0 = dx.div(tile), bx = tile - r0 * dx.d, bz = dy.div(r0), by = r0 - bz * dy.d;
+  const int32_t x0 = (int32_t)dx.div(bx * (uint32_t)Lh), y0 = (int32_t)dy.div(by * (uint32_t)L),
+                z0 = (int32_t)dz.div(bz * (uint32_t)L);
+  const int32_t nx = (int32_t)dx.div((bx + 1) * (uint32_t)Lh) - x0,
+                ny = (int32_t)dy.div((by + 1) * (uint32_t)L) - y0,
+                nz = (int32_t)dz.div((bz + 1) * (uint32_t)L) - z0;
+  const int32_t hx = a.n[0] > 1 ? 3 : 0, w = nx + 2 * hx, rows = ny + 8;
+  auto wrap = [](int32_t v, int32_t n) { return v < 0 ? v + n : (v >= n ? v - n : v); };
+  const int32_t s = min(tid, rows * w - 1);
+  const int32_t r = (int32_t)(((float)s + 0.5f) * __builtin_amdgcn_rcpf((float)w)), j = s - r * w;
+  const bool has = tid < rows * w;
+  const int32_t x = wrap(x0 - hx + j, Lh), y = wrap(y0 - 4 + r, L);
+  // whether a stage that leaves out m rows and c columns on either side has the place
+  auto in = [&](int32_t m, int32_t c) {
+    return has && r >= m && r < rows - m && (hx == 0 || (j >= c && j < w - c));
+  };
+  const bool inA = in(1, 1), inB = in(2, 2), inC = in(3, 2), inD = in(4, 3);
+  const int32_t q0 = z0 - 3;
+  const int32_t p = (y + q0) & 1;  // A's x parity at step 0; B's is the same, C's and D's not
+  const int32_t lx = hx || x < Lh - 1 ? 1 : 1 - Lh, mx = hx || x > 0 ? -1 : Lh - 1;
+  // bytes from a plane's start in LDS to the site's place and its neighbours'
+  constexpr int32_t B = (int32_t)E;
+  const int32_t is = s * B, ipy = (s + w) * B, imy = (s - w) * B;
+  const int32_t ipx[2] = {is + (p ? lx : 0) * B, is + (p ? 0 : lx) * B};
+  const int32_t imx[2] = {is + (p ? 0 : mx) * B, is + (p ? mx : 0) * B};
+  const uint32_t g = (uint32_t)(y * Lh + x) * E, gm = (uint32_t)(wrap(y - 1, L) * Lh + x) * E;
+  const uint32_t d = (uint32_t)(x > 0 ? -1 : Lh - 1) * E;
+  const uint32_t gx[2] = {g + (p ? 0u : d), g + (p ? d : 0u)};
+  const char* sp[6];
+  const char* Jp[6];
+  char* out[6];
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    sp[k] = (const char*)(a.in + k * Nh);
+    Jp[k] = (const char*)(a.J + k * Nh);
+    out[k] = (char*)(a.out + k * Nh);
+  }
+  const uint32_t zb = (uint32_t)zs * E;
+  auto at = [](const char* base, uint32_t off) { return *(const R*)(base + off); };
+  R s0[3], c1[3], ja[4][6], jb[4][6];  // couplings of four steps, step t's in set t mod 4
+  // bonds of the site on the plane at byte offset zo, the plane below it at zm
+  auto load_bonds = [&](auto C, auto Par, R (&jj)[6], uint32_t zo, uint32_t zm) {
+    constexpr int o = 3 * decltype(C)::value, n = 3 - o, par = decltype(Par)::value;
+    const uint32_t own = g + zo;
+    jj[0] = at(Jp[o], own);
+    jj[1] = at(Jp[n], gx[par] + zo);
+    jj[2] = at(Jp[o + 1], own);
+    jj[3] = at(Jp[n + 1], gm + zo);
+    jj[4] = at(Jp[o + 2], own);
+    jj[5] = at(Jp[n + 2], g + zm);
+  };
+  auto load_spin = [&](int c, R (&v)[3], uint32_t zo) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) v[k] = at(sp[3 * c + k], g + zo);
+  };
+  auto store = [&](auto C, uint32_t zo, const Vec3<R>& v) {
+    constexpr int o = 3 * decltype(C)::value;
+    *(R*)(out[o] + (g + zo)) = v.x;
+    *(R*)(out[o + 1] + (g + zo)) = v.y;
+    *(R*)(out[o + 2] + (g + zo)) = v.z;
+  };
+  auto field = [&](const char* cur, const char* up, const char* dn, int32_t px, int32_t mxp,
+                   const R (&jj)[6]) {
+    R h[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      auto ld = [&](const char* plane, int32_t i) { return *(const R*)(plane + i + k * N * B); };
+      R acc = jj[0] * ld(cur, px);
+      acc = dev_fma(jj[1], ld(cur, mxp), acc);
+      acc = dev_fma(jj[2], ld(cur, ipy), acc);
+      acc = dev_fma(jj[3], ld(cur, imy), acc);
+      acc = dev_fma(jj[4], ld(up, is), acc);
+      acc = dev_fma(jj[5], ld(dn, is), acc);
+      h[k] = acc;
+    }
+    return Vec3<R>{h[0], h[1], h[2]};
+  };
+  auto get = [&](const char* plane) {
+    const R* v = (const R*)(plane + is);
+    return Vec3<R>{v[0], v[N], v[2 * N]};
+  };
+  auto put = [&](char* plane, const Vec3<R>& v) {
+    R* o = (R*)(plane + is);
+    o[0] = v.x;
+    o[N] = v.y;
+    o[2 * N] = v.z;
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  // Where planes q, q - 1, ... (colour 1: q + 2, q + 1, ...) are in LDS and planes q + 3, q +
+  // 2, ... in the arrays, in bytes: turned by one place a step.  (Indices modulo 6, 7 and L at
+  // each use were 250 scalar instructions a step and wave, more than a compute unit issues
+  // while it issues the vector ones.)
+  int32_t o0[K0], o1[K1];
+#pragma unroll
+  for (int k = 0; k < K0; ++k) o0[k] = k * 3 * N * B;
+#pragma unroll
+  for (int k = 0; k < K1; ++k) o1[k] = k * 3 * N * B;
+  uint32_t zo[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) zo[k] = zb * (uint32_t)wrap(wrap(q0 + 3 - k, L), L);
+  auto P0 = [&](int o) { return (char*)l0 + o0[-o]; };
+  auto P1 = [&](int o) { return (char*)l1 + o1[2 - o]; };
+  const int32_t end = z0 + nz;
+  auto step = [&](auto Uc, int32_t q) {
+    constexpr int U = decltype(Uc)::value, V = (U + 1) & 3, par = U & 1;
+    using Other = std::integral_constant<int, 1 - par>;
+    if (inA) put(P0(0), reflect(Vec3<R>{s0[0], s0[1], s0[2]},
+                                field(P1(0), P1(1), P1(-1), ipx[par], imx[par], ja[U])));
+    if (inC && q >= z0 + 2) {
+      const Vec3<R> v = reflect(get(P0(-3)), field(P1(-3), P1(-2), P1(-4), ipx[1 - par],
+                                                   imx[1 - par], ja[V]));
+      put(P0(-3), v);
+      if (inD && q >= z0 + 3 && q < end + 3) store(I0{}, zo[6], v);
+    }
+    // for the next step (past the last one: values nobody uses)
+    load_spin(0, s0, zo[2]);
+    load_bonds(I0{}, Other{}, ja[V], zo[2], zo[3]);
+    __syncthreads();
+    if (inB && q >= z0 - 1)
+      put(P1(-1), reflect(get(P1(-1)), field(P0(-1), P0(0), P0(-2), ipx[par], imx[par], jb[U])));
+    if (inD && q >= z0 + 4)
+      store(I1{}, zo[7], reflect(get(P1(-4)), field(P0(-4), P0(-3), P0(-5), ipx[1 - par],
+                                                    imx[1 - par], jb[V])));
+    if (has) put(P1(2), Vec3<R>{c1[0], c1[1], c1[2]});
+    load_spin(1, c1, zo[0]);
+    load_bonds(I1{}, Other{}, jb[V], zo[3], zo[4]);
+    __syncthreads();
+    const int32_t t0 = o0[K0 - 1], t1 = o1[K1 - 1];
+#pragma unroll
+    for (int k = K0 - 1; k > 0; --k) o0[k] = o0[k - 1];
+#pragma unroll
+    for (int k = K1 - 1; k > 0; --k) o1[k] = o1[k - 1];
+    o0[0] = t0;
+    o1[0] = t1;
+#pragma unroll
+    for (int k = 7; k > 0; --k) zo[k] = zo[k - 1];
+    zo[0] = zo[1] + zb;
+    if (zo[0] == zb * (uint32_t)L) zo[0] = 0;
+  };
+  {
+    R c[3][3];  // colour 1 of planes q0 - 1, q0, q0 + 1
+#pragma unroll
+    for (int k = 0; k < 3; ++k) load_spin(1, c[k], zo[4 - k]);
+    load_spin(0, s0, zo[3]);
+    load_bonds(I0{}, I0{}, ja[0], zo[3], zo[4]);
+    load_spin(1, c1, zo[1]);
+    load_bonds(I1{}, I0{}, jb[0], zo[4], zo[5]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      if (has) put(P1(k - 1), Vec3<R>{c[k][0], c[k][1], c[k][2]});
+  }
+  __syncthreads();
+  const int32_t last = end + 3;
+  for (int32_t q = q0; q <= last; q += 4) {
+    step(I0{}, q);
+    if (q + 1 > last) break;
+    step(I1{}, q + 1);
+    if (q + 2 > last) break;
+    step(std::integral_constant<int, 2>{}, q + 2);
+    if (q + 3 > last) break;
+    step(std::integral_constant<int, 3>{}, q + 3);
+  }
+}
+
 template <typename R>
 __global__ __launch_bounds__((RowSize<R, false>::A)) void phase_kernel(PhaseArgs<R> a) {
   row_march<R, PassMode::OverRelax, false>(a);
@@ -410,35 +605,37 @@ int32_t row_threads(int32_t nx, int32_t ny, int32_t hx) {
              : 0;
 }
 
-// The tiles for an L^3 lattice: the smallest of an estimate fitted to 2400 timed plans of 55
-// lattices (its choice is 1 to 1.5% behind the best of them on average, 11% at worst): the
+template <typename R>
+int32_t pair_threads(int32_t nx, int32_t ny, int32_t hx) {
+  const int32_t T = ((ny + 8) * (nx + 6 * hx) + 63) & ~63;
+  return T <= kPairThreads<R> ? T : 0;
+}
+
+// The tiles for an L^3 lattice: the smallest of an estimate fitted to 5000 timed plans of 60
+// lattices (its choice is 1 to 1.5% behind the best of them on average, 15% at worst): the
 // steps of a workgroup, nz and `fill` for the pipeline, times its threads and a fixed part,
-// and the bytes of its planes, more where the tile is cut in x.  `waves` workgroups per
-// compute unit: one is the longest run in z; with the Monte Carlo pass two or three, one
-// after the other, sometimes leave fewer units idle.
-template <typename R, bool MC>
-bool row_plan(int32_t L, int32_t (&n)[3]) {
-  struct Fit {
-    float fill, fixed, bytes, ends, cut, edge;
-  };
-  constexpr bool F32 = sizeof(R) == 4;
-  constexpr Fit f = MC ? (F32 ? Fit{2.0f, 500.0f, 2.0f, 4.0f, 0.0f, 32.0f}
-                              : Fit{4.0f, 200.0f, 1.0f, 0.0f, 0.2f, 8.0f})
-                       : (F32 ? Fit{2.5f, 200.0f, 4.0f, 1.0f, 0.2f, 16.0f}
-                              : Fit{2.5f, 200.0f, 4.0f, 3.0f, 0.0f, 4.0f});
+// and the bytes of its planes, more where the tile is cut in x.  `most` workgroups per
+// compute unit, one after the other: one is the longest run in z; with more stages two or
+// three sometimes leave fewer units idle.
+struct PlanFit {
+  float fill, fixed, bytes, ends, cut, edge;
+  int32_t most, narrow;  // narrow: the fewest columns of a tile that does not have them all
+};
+template <class Threads>
+bool row_plan(const PlanFit& f, int32_t L, Threads threads, int32_t (&n)[3]) {
   constexpr int kCUs = 256;
   const int32_t Lh = L / 2;
   float best = 0.0f;
   for (int32_t px = 1; px <= 16; ++px) {
     const int32_t nx = (Lh + px - 1) / px, hx = px > 1 ? 1 : 0;
-    if (px > 1 && nx < (MC ? 14 : 24)) break;
+    if (px > 1 && nx < f.narrow) break;
     for (int32_t ny = 2;; ++ny) {
-      const int32_t T = row_threads<R, MC>(nx, ny, hx);
+      const int32_t T = threads(nx, ny, hx);
       if (!T) break;
       const int32_t ty = (L + ny - 1) / ny;
       if ((L + ty - 1) / ty != ny) continue;  // no fewer tiles than with the next smaller ny
-      for (int32_t waves = 1; waves <= (MC ? 3 : 1); ++waves) {
-        const int32_t tz = std::max(1, std::min(L / 3, waves * kCUs / (ty * px)));
+      for (int32_t k = 1; k <= f.most; ++k) {
+        const int32_t tz = std::max(1, std::min(L / 3, k * kCUs / (ty * px)));
         const int32_t nz = (L + tz - 1) / tz, rounds = (tz * ty * px + kCUs - 1) / kCUs;
         const float halo = (float)hx * (f.cut + f.edge / (float)nx);
         const float cost =
@@ -456,17 +653,33 @@ bool row_plan(int32_t L, int32_t (&n)[3]) {
   return best > 0.0f;
 }
 
+// Tiles of columns, rows and threads of a launch; false if there are none.
+struct TilePlan {
+  int32_t nx, ny, hx, T;
+};
+template <typename R, class Threads>
+bool set_tiles(const PlanFit& f, PhaseArgs<R>& a, Threads threads, TilePlan* t) {
+  if (!phase_supported(a.L) || !row_plan(f, a.L, threads, a.n)) return false;
+  t->nx = (a.L / 2 + a.n[0] - 1) / a.n[0];
+  t->ny = (a.L + a.n[1] - 1) / a.n[1];
+  t->hx = a.n[0] > 1 ? 1 : 0;
+  t->T = threads(t->nx, t->ny, t->hx);
+  for (int k = 0; k < 3; ++k) a.inv[k] = row_inv(a.n[k]);
+  return t->T > 0;
+}
+
 template <typename R, PassMode MODE>
 hipError_t launch_rows(PhaseArgs<R> a, hipStream_t st) {
-  constexpr bool MC = MODE != PassMode::OverRelax;
-  if (!phase_supported(a.L) || !row_plan<R, MC>(a.L, a.n)) return hipErrorInvalidValue;
-  const int32_t Lh = a.L / 2, nx = (Lh + a.n[0] - 1) / a.n[0], ny = (a.L + a.n[1] - 1) / a.n[1];
-  const int32_t hx = a.n[0] > 1 ? 1 : 0, T = row_threads<R, MC>(nx, ny, hx);
-  if (!T || (MC && !a.partials)) return hipErrorInvalidValue;
-  for (int k = 0; k < 3; ++k) a.inv[k] = row_inv(a.n[k]);
-  const dim3 grid((unsigned)(a.n[0] * a.n[1] * a.n[2])), block((unsigned)T);
+  constexpr bool MC = MODE != PassMode::OverRelax, F32 = sizeof(R) == 4;
+  constexpr PlanFit f = MC ? (F32 ? PlanFit{2.0f, 500.0f, 2.0f, 4.0f, 0.0f, 32.0f, 3, 14}
+                                  : PlanFit{4.0f, 200.0f, 1.0f, 0.0f, 0.2f, 8.0f, 3, 14})
+                           : (F32 ? PlanFit{2.5f, 200.0f, 4.0f, 1.0f, 0.2f, 16.0f, 1, 24}
+                                  : PlanFit{2.5f, 200.0f, 4.0f, 3.0f, 0.0f, 4.0f, 1, 24});
+  TilePlan t;
+  if (!set_tiles(f, a, row_threads<R, MC>, &t) || (MC && !a.partials)) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)(a.n[0] * a.n[1] * a.n[2])), block((unsigned)t.T);
   if constexpr (MC) {
-    if (by_wave(MC, nx, hx))
+    if (by_wave(MC, t.nx, t.hx))
       hipLaunchKernelGGL((phase_mc_wave_kernel<R, MODE>), grid, block, 0, st, a);
     else
       hipLaunchKernelGGL((phase_mc_kernel<R, MODE>), grid, block, 0, st, a);
@@ -476,6 +689,20 @@ hipError_t launch_rows(PhaseArgs<R> a, hipStream_t st) {
 }
 
 }  // namespace
+
+template <typename R>
+hipError_t launch_phase_pair(const PhaseArgs<R>& a0, hipStream_t st) {
+  constexpr PlanFit f = sizeof(R) == 4 ? PlanFit{12.0f, 2000.0f, 4.0f, 4.0f, 0.0f, 32.0f, 3, 14}
+                                       : PlanFit{12.0f, 500.0f, 1.0f, 0.0f, 0.0f, 32.0f, 3, 14};
+  PhaseArgs<R> a = a0;
+  TilePlan t;
+  if (!set_tiles(f, a, pair_threads<R>, &t)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(phase_pair_kernel<R>, dim3((unsigned)(a.n[0] * a.n[1] * a.n[2])),
+                     dim3((unsigned)t.T), 0, st, a);
+  return hipGetLastError();
+}
+template hipError_t launch_phase_pair<float>(const PhaseArgs<float>&, hipStream_t);
+template hipError_t launch_phase_pair<double>(const PhaseArgs<double>&, hipStream_t);
 
 template <typename R>
 hipError_t launch_phase(const PhaseArgs<R>& a, PassMode mc, hipStream_t st) {

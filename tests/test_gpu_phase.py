@@ -12,7 +12,7 @@ F32, F64 = torch.float32, torch.float64
 # k, n_or, heat bath, renormalise every, sweeps: odd and even numbers of phases, groups of
 # four hits complete and incomplete, no Monte Carlo phase
 SCHEDULES = [(4, 1, False, 2, 3), (1, 2, False, 1, 2), (6, 1, False, 0, 2), (1, 1, True, 1, 4),
-             (0, 3, False, 2, 2)]
+             (0, 3, False, 2, 2), (2, 4, False, 0, 1), (1, 5, True, 2, 3), (0, 1, False, 3, 7)]
 
 
 @pytest.fixture(scope="module")
@@ -67,6 +67,24 @@ def test_a_wave_per_row(hsg):
             lat.sweep(T=0.45, k=k, n_or=1, renorm_every=2, n_sweeps=3, heat_bath=hb, flags=flags)
         assert torch.equal(a.spins, b.spins)
         assert abs(a.E.item() - b.E.item()) <= 1e-12 * abs(a.E.item())
+
+
+# launches that a call's over-relaxation phases run in: two phases (5), one (3), with the next
+# Monte Carlo pass (4), two passes (2, 2); an even number of the first three
+@pytest.mark.parametrize("k,n_or,R,n,flags,kinds", [
+    (0, 1, 0, 4, "PHASE_LAUNCH", [5, 5]), (0, 1, 0, 2, "PHASE_LAUNCH", [3, 3]),
+    (0, 1, 0, 3, "PHASE_LAUNCH", [5, 3]), (0, 1, 2, 5, "PHASE_LAUNCH", [5, 0, 5, 0, 2, 2]),
+    (0, 1, 1, 2, "PHASE_LAUNCH", [3, 0, 3, 0]), (0, 2, 1, 3, "PHASE_LAUNCH", [5, 0, 5, 0, 3, 3, 0]),
+    (0, 3, 0, 2, "PHASE_LAUNCH", [5, 5, 3, 3]), (1, 2, 0, 2, "PHASE_LAUNCH", [1, 1, 5, 1, 1, 5, 0]),
+    (1, 3, 0, 1, "PHASE_LAUNCH", [1, 1, 5, 3, 0]), (1, 4, 0, 1, "PHASE_LAUNCH", [1, 1, 5, 5, 0]),
+    (1, 2, 0, 2, "PHASE_MC", [1, 1, 3, 4, 1, 3, 3, 0]),
+    (1, 3, 0, 2, "PHASE_MC", [1, 1, 5, 4, 1, 5, 3, 0]), (1, 2, 0, 1, "PHASE_MC", [1, 1, 3, 3, 0])])
+def test_launches_of_a_call(hsg, k, n_or, R, n, flags, kinds):
+    a, b = [hsg.Lattice(100, F32, seed=9) for _ in range(2)]
+    kw = dict(T=0.5, k=k, n_or=n_or, renorm_every=R, n_sweeps=n)
+    a.sweep(flags=0, **kw)
+    assert [kd for kd, _ in b.sweep_timed(flags=getattr(hsg, "HSG_" + flags), **kw)] == kinds
+    same(a, b)
 
 
 def test_captured_in_a_graph(hsg):

@@ -33,3 +33,14 @@ def test_flags_of_a_call():
     assert hsg.call_flags(126, f64) == hsg.call_flags(180, f64, k=4) == carry
     assert hsg.call_flags(448, f64, k=5) == carry | hsg.HSG_PHASE_LAUNCH  # a default there
     assert hsg.call_flags(162, f64) == hsg.call_flags(178, f64, k=8) == hsg.HSG_SNAKE
+
+
+def test_flags_of_a_call_with_more_phases():
+    one, carry = hsg.HSG_SNAKE | hsg.HSG_PHASE_LAUNCH, hsg.HSG_SNAKE | hsg.HSG_PHASE_MC
+    f64 = torch.float64
+    assert hsg.call_flags(130, n_or=2) == hsg.call_flags(256, k=4, n_or=2) == one
+    assert hsg.call_flags(210, k=4, n_or=2) == hsg.call_flags(448, k=8, n_or=4) == one
+    assert hsg.call_flags(310, k=4, n_or=2) == hsg.call_flags(310, heat_bath=True, n_or=2) == carry
+    assert hsg.call_flags(400, f64, n_or=2) == hsg.call_flags(170, f64, k=4, n_or=3) == one
+    assert hsg.call_flags(210, n_or=3) == hsg.call_flags(190, f64, k=4, n_or=3) == carry
+    assert hsg.call_flags(210, k=0) == one and hsg.call_flags(210, k=2) == hsg.HSG_SNAKE
