@@ -9,6 +9,7 @@ from __future__ import annotations
 import ctypes
 import dataclasses
 import math
+from collections import Counter
 
 import numpy as np
 import torch
@@ -68,7 +69,8 @@ def _bind():
     for name in ("hsg_batch_check", "hsg_batch_init", "hsg_batch_sweep",
                  "hsg_batch_energy", "hsg_batch_overlap", "hsg_pt_exchange", "hsg_pt_overlap",
                  "hsg_batch_overlap_fourier", "hsg_pt_overlap_fourier", "hsg_batch_tiles",
-                 "hsg_batch_tile_sweep", "hsg_batch_group_sweep", "hsg_batch_init_parts", "hsg_batch_overlap_parts"):
+                 "hsg_batch_tile_sweep", "hsg_batch_group_sweep", "hsg_batch_init_parts",
+                 "hsg_batch_overlap_parts"):
         getattr(L, name).restype = ctypes.c_int
     _bound = True
 
@@ -112,10 +114,10 @@ def tiles_pay(specs) -> bool:
     2554).  Beyond, both forms are bound by the rate of the whole GPU, and the one launch,
     whose chains of a sample read their couplings together, is the faster (12288 chains of
     L = 16 .. 48: 57.9 against 60.4 ms for ten sweeps)."""
-    sites = [c.L ** 3 for c in specs]
-    most = max(sites)
-    limit = 2048 if most >= 32 ** 3 else 512 if most >= 20 ** 3 else 192 if most >= 16 ** 3 else 0
-    return sum(sites) <= limit * most
+    number = Counter(c.L for c in specs)
+    L = max(number)
+    limit = 2048 if L >= 32 else 512 if L >= 20 else 192 if L >= 16 else 0
+    return sum(n * l ** 3 for l, n in number.items()) <= limit * L ** 3
 
 
 # Bytes of spins that chains advanced together may have: with them in the 256 MB memory-side
@@ -131,7 +133,8 @@ def groups_pay(specs) -> bool:
     in groups: 3072 chains of L = 48 k = 4 39.4 / 35.6, k = 1 36.9 / 26.6; 3072 of L = 32
     11.1 / 10.8, k = 1 9.9 / 7.9 (L = 24 4.8 / 5.0; 16 1.6 / 1.9); L = 48 by 64, 128, 512 MB
     37.8, 37.0, 36.7."""
-    return 2 * sum(c.L ** 3 for c in specs if c.L >= 32) > sum(c.L ** 3 for c in specs)
+    number = Counter(c.L for c in specs)
+    return sum((1 if l >= 32 else -1) * n * l ** 3 for l, n in number.items()) > 0
 
 
 class Batch:
@@ -188,6 +191,8 @@ class Batch:
                          self.remaining.data_ptr() if self.remaining is not None else None,
                          self.order.data_ptr(), threads, 0)
         self._export_work: dict[int, torch.Tensor] = {}
+        self._any = (int((table["k_hits"] > 0).any()), int(table["n_or"].max(initial=0)),
+                     int((table["renorm_every"] > 0).any()))
         self._tiles, self._alone = None, None
         if tiles_pay(self.specs):
             self._tiles = self._tile_table()
@@ -218,26 +223,29 @@ class Batch:
         first tile, the number of tiles, their energy partials and the groups: the first tile
         of each, and the number of tiles."""
         Ls = self.table["L"].astype(np.int64)
-        active = np.arange(self.n) if chains is None else chains
         has = np.zeros(self.n, dtype=np.int64)
-        has[active] = 1
+        has[slice(None) if chains is None else chains] = 1
         count = -(-(Ls ** 3 // 2) // TILE_SITES) * has
         first = np.concatenate([[0], np.cumsum(count)])
-        n = ctypes.c_int32()
-        tiles = np.zeros(2 * int(first[-1]), dtype=np.int32)
-        active = np.ascontiguousarray(active, dtype=np.int32)
-        check(lib().hsg_batch_tiles(self.table.ctypes.data_as(ctypes.c_void_p), self.n,
-                                    active.ctypes.data_as(ctypes.c_void_p), active.size, TILE_SITES,
-                                    tiles.ctypes.data_as(ctypes.c_void_p), int(first[-1]),
-                                    ctypes.byref(n)))
         # groups of about the same number of bytes, the last chain of one where its share ends
         end = np.cumsum(Ls ** 3 * has) * 3 * self.spins.element_size()
         n_groups = -(-int(end[-1]) // GROUP_SPIN_BYTES)
         last = np.searchsorted(end, end[-1] * np.arange(1, n_groups) / n_groups)
         groups = np.unique(np.concatenate([[0], first[last + 1], first[-1:]])).astype(np.int32)
-        return (torch.from_numpy(tiles).to(self.device),
-                torch.from_numpy(first.astype(np.int32)).to(self.device), n.value,
-                torch.zeros(n.value, dtype=torch.float64, device=self.device), groups)
+        # (chain, first site) of each tile, made where they are read: a million of them for
+        # 12288 chains, 4 ms to make on the host and as long to send
+        n, dev = int(first[-1]), self.device
+        first = torch.from_numpy(first.astype(np.int32)).to(dev)
+        tiles = torch.empty(n, 2, dtype=torch.int32, device=dev)
+        torch.arange(n, dtype=torch.int32, out=tiles[:, 1])
+        tiles[:, 0] = torch.repeat_interleave(
+            torch.from_numpy(count.astype(np.int32)).to(dev), output_size=n)
+        tiles[:, 1] -= first[tiles[:, 0]]
+        tiles[:, 1] *= TILE_SITES
+        partials = torch.zeros(n, dtype=torch.float64, device=dev)
+        if dev.type == "cuda":  # sweeps may run on another stream
+            torch.cuda.current_stream(dev).synchronize()
+        return tiles, first, n, partials, groups
 
     def sweep(self, n_sweeps: int, stream=None) -> None:
         if self._tiles is None:
@@ -250,9 +258,7 @@ class Batch:
         tiles, first, _, partials, groups = self._tiles
         check(lib().hsg_batch_group_sweep(
             ctypes.byref(self._d), _ptr(tiles), _ptr(first), groups.ctypes.data, groups.size - 1,
-            TILE_SITES, _ptr(partials), int(any(c.k > 0 for c in self.specs)),
-            max(c.n_or for c in self.specs), int(any(c.renorm_every > 0 for c in self.specs)),
-            int(n_sweeps), _stream(stream)))
+            TILE_SITES, _ptr(partials), *self._any, int(n_sweeps), _stream(stream)))
 
     def energies(self, recompute: bool = False, stream=None) -> torch.Tensor:
         if not recompute:
