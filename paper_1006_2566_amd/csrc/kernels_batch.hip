@@ -279,22 +279,25 @@ __global__ __launch_bounds__(kChainReduceThreads) void chain_pairs_overlap_kerne
   pair_overlap<R>(chains[pairs[2 * p]], chains[pairs[2 * p + 1]], spins, out + 15 * (int64_t)p);
 }
 
-// The same and H of a chain in parts of kPartSites sites of a colour, a workgroup each, whose
+// The same and H of a chain in parts of 8192 sites of a colour, a workgroup each, whose
 // sums are then added in order: a chain's result depends on nothing but the chain.  A
 // workgroup alone took 255 us for the overlaps of a few chains of up to L = 96 and 755 for
 // the energies of 48 (bound by what its compute unit can load); 54 to a chain take 16 and 84.
-constexpr uint32_t kPartSites = 8192;
+// Up to L = 48 a chain is one part: it is read in 10 to 20 us, and served lattices of L <= 32
+// lost more to the second launch than the parts gave (20 of them, 8 to 32 sweeps each: 1152 us
+// in parts, 1093 without).
+__host__ __device__ inline uint32_t part_sites(int32_t L) { return L <= 48 ? 55296u : 8192u; }
 __host__ __device__ inline int32_t chain_parts(int32_t L) {
-  return (int32_t)((half_sites(L) + kPartSites - 1u) / kPartSites);
+  return (int32_t)((half_sites(L) + part_sites(L) - 1u) / part_sites(L));
 }
 template <typename R>
 __global__ __launch_bounds__(kChainReduceThreads) void chain_pairs_part_kernel(
     const hsg_chain* chains, const R* spins, const int32_t* pairs, double* parts) {
   const int32_t p = (int32_t)blockIdx.y, part = (int32_t)blockIdx.x;
   const hsg_chain& ca = chains[pairs[2 * p]];
-  const uint32_t Nh = half_sites(ca.L), e0 = (uint32_t)part * kPartSites;
+  const uint32_t Nh = half_sites(ca.L), n = part_sites(ca.L), e0 = (uint32_t)part * n;
   if (e0 >= Nh) return;
-  pair_overlap<R>(ca, chains[pairs[2 * p + 1]], spins, e0, min(e0 + kPartSites, Nh), 1.0,
+  pair_overlap<R>(ca, chains[pairs[2 * p + 1]], spins, e0, min(e0 + n, Nh), 1.0,
                   parts + 15 * ((int64_t)p * gridDim.x + part));
 }
 constexpr int kSumThreads = 256;  // 16 partial sums of a record's 15 values, then theirs
@@ -322,7 +325,7 @@ __global__ __launch_bounds__(kChainReduceThreads) void batch_energy_part_kernel(
   __shared__ double s_red[16];
   const int32_t c = (int32_t)blockIdx.y, part = (int32_t)blockIdx.x;
   const ChainView<R> v = chain_view<R>(load_chain(chains, c), spins, J);
-  const uint32_t e0 = (uint32_t)part * kPartSites, e1 = min(e0 + kPartSites, (uint32_t)v.Nh);
+  const uint32_t n = part_sites(v.L), e0 = (uint32_t)part * n, e1 = min(e0 + n, (uint32_t)v.Nh);
   if (e0 >= e1) return;
   const SmallDiv by_lh((uint32_t)v.Lh), by_l((uint32_t)v.L);
   double acc = 0.0;

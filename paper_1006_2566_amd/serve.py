@@ -329,7 +329,7 @@ class Server:
         d = _Batch(n, _dtype_code(self.dtype), chains.data_ptr(), self.spins.data_ptr(),
                    self.J.data_ptr(), beta.data_ptr(), E.data_ptr(), zeros.data_ptr(), None,
                    order.data_ptr(), 256, 0)
-        L_max = int(max(self.table[s]["L"] for s in slots))
+        L_max = max(self.active[s][0].L for s in slots)
         parts = lib().hsg_batch_parts(L_max)
         if parts > 1:
             scratch = torch.empty(n * parts, dtype=torch.float64, device=dev)
@@ -378,7 +378,7 @@ class Server:
         n = len(done)
         pairs = self._to_dev(np.asarray([[s, s] for s in done], dtype=np.int32))
         m_dev = torch.empty((n, 15), dtype=torch.float64, device=self.device)
-        L_max = int(max(self.table[s]["L"] for s in done))
+        L_max = max(self.active[s][0].L for s in done)
         parts = lib().hsg_batch_parts(L_max)
         if 1 < parts and n < 65536:
             scratch = torch.empty(15 * n * parts, dtype=torch.float64, device=self.device)

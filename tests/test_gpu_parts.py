@@ -10,9 +10,9 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 
-# one part, the last site of a part and the first of the next, many parts, chains of other
+# one part, the largest chain of one and the smallest of several, many parts, chains of other
 # sizes than the largest
-@pytest.mark.parametrize("dtype,Ls", [(torch.float32, (2, 24, 26, 96)), (torch.float64, (32, 20, 8)),
+@pytest.mark.parametrize("dtype,Ls", [(torch.float32, (2, 48, 50, 96)), (torch.float64, (32, 20, 8)),
                                       (torch.float32, (16,)), (torch.float32, (128, 4))])
 def test_parts_equal_one_workgroup(dtype, Ls):
     if not torch.cuda.is_available():
@@ -24,7 +24,7 @@ def test_parts_equal_one_workgroup(dtype, Ls):
     b = hb.Batch(specs, dtype=dtype)
     lib, st = hsg.lib(), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
     n, parts = len(specs), lib.hsg_batch_parts(max(Ls))
-    assert parts == -(-max(Ls) ** 3 // 2 // 8192)
+    assert parts == (1 if max(Ls) <= 48 else -(-max(Ls) ** 3 // 2 // 8192))
     E, spins = b.E.clone(), b.spins.clone()
     scratch = torch.full((15 * n * parts,), float("nan"), dtype=torch.float64, device="cuda")
     P = lambda t: ctypes.c_void_p(t.data_ptr())  # noqa: E731
