@@ -93,11 +93,12 @@ def call_flags(L: int, dtype=None, k: int = 1, heat_bath: bool = False, n_or: in
       binary64  L =122 k = 1  74.0 / 67.7 / 68.2    130 k = 1  86.0 / 81.1 / 78.1
                    146 k = 2   117 /  108 /  119    178 k = 1   211 /  229 /  214
                    182 k = 4   269 /  260 /  256    320 k = 8  2111 / 1845 / 1923
-                   448 k = 8  5959 / 5601 / 5333    320 heat bath 1656 / 1386 / 1689
+                   448 k = 8  5891 / 5165 / 5153    512 k = 8  9040 / 7930 / 8050
+                   512 k = 4  7170 / 6090 / 5660    320 heat bath 1656 / 1386 / 1689
 
     so binary32 takes the pass along with one hit, from L = 114 with two, from 128 with three
     or a heat bath, from 226 with four and from 256 always; binary64 with one hit from 126,
-    with up to four from 180, with more from 448, never a heat bath.  Where only the passes'
+    with up to four from 180, never with more or a heat bath.  Where only the passes'
     footprint fits the memory-side cache (206 <= L <= 224, in binary64 162 to 178) they stay,
     but for one hit in binary32.
 
@@ -115,7 +116,7 @@ def call_flags(L: int, dtype=None, k: int = 1, heat_bath: bool = False, n_or: in
     if n_or > 0 and n_or % 2 == 0:
         carry = not f64 and L >= 310 and (heat_bath or k <= 4)
     elif f64:
-        carry = not heat_bath and (L >= 448 or (L >= 126 and k <= 1) or (L >= 180 and k <= 4))
+        carry = not heat_bath and ((L >= 126 and k <= 1) or (L >= 180 and k <= 4))
     else:
         carry = (L >= (128 if heat_bath or k == 3 else 226 if k == 4 else 256) or
                  (not heat_bath and (k <= 1 or (k == 2 and L >= 114))))

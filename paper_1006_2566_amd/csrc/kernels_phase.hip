@@ -616,13 +616,15 @@ int32_t pair_threads(int32_t nx, int32_t ny, int32_t hx) {
 // steps of a workgroup, nz and `fill` for the pipeline, times its threads and a fixed part,
 // and the bytes of its planes, more where the tile is cut in x.  `most` workgroups per
 // compute unit, one after the other: one is the longest run in z; with more stages two or
-// three sometimes leave fewer units idle.
+// three sometimes leave fewer units idle, and up to eight where a plane has more tiles than
+// there are units.  `ragged`: what a cut that is not on a cache line costs, as columns.
 struct PlanFit {
   float fill, fixed, bytes, ends, cut, edge;
   int32_t most, narrow;  // narrow: the fewest columns of a tile that does not have them all
+  float ragged = 0.0f;
 };
 template <class Threads>
-bool row_plan(const PlanFit& f, int32_t L, Threads threads, int32_t (&n)[3]) {
+bool row_plan(const PlanFit& f, int32_t L, int32_t line, Threads threads, int32_t (&n)[3]) {
   constexpr int kCUs = 256;
   const int32_t Lh = L / 2;
   float best = 0.0f;
@@ -637,7 +639,8 @@ bool row_plan(const PlanFit& f, int32_t L, Threads threads, int32_t (&n)[3]) {
       for (int32_t k = 1; k <= f.most; ++k) {
         const int32_t tz = std::max(1, std::min(L / 3, k * kCUs / (ty * px)));
         const int32_t nz = (L + tz - 1) / tz, rounds = (tz * ty * px + kCUs - 1) / kCUs;
-        const float halo = (float)hx * (f.cut + f.edge / (float)nx);
+        const float edge = f.edge + (nx % line || Lh % px ? f.ragged : 0.0f);
+        const float halo = (float)hx * (f.cut + edge / (float)nx);
         const float cost =
             (float)rounds * (((float)nz + f.fill) * ((float)T + f.fixed) +
                              f.bytes * (float)(nx * ny) * ((float)nz + f.ends) * (1.0f + halo));
@@ -659,7 +662,8 @@ struct TilePlan {
 };
 template <typename R, class Threads>
 bool set_tiles(const PlanFit& f, PhaseArgs<R>& a, Threads threads, TilePlan* t) {
-  if (!phase_supported(a.L) || !row_plan(f, a.L, threads, a.n)) return false;
+  if (!phase_supported(a.L) || !row_plan(f, a.L, 128 / (int)sizeof(R), threads, a.n))
+    return false;
   t->nx = (a.L / 2 + a.n[0] - 1) / a.n[0];
   t->ny = (a.L + a.n[1] - 1) / a.n[1];
   t->hx = a.n[0] > 1 ? 1 : 0;
@@ -671,10 +675,18 @@ bool set_tiles(const PlanFit& f, PhaseArgs<R>& a, Threads threads, TilePlan* t) 
 template <typename R, PassMode MODE>
 hipError_t launch_rows(PhaseArgs<R> a, hipStream_t st) {
   constexpr bool MC = MODE != PassMode::OverRelax, F32 = sizeof(R) == 4;
-  constexpr PlanFit f = MC ? (F32 ? PlanFit{2.0f, 500.0f, 2.0f, 4.0f, 0.0f, 32.0f, 3, 14}
-                                  : PlanFit{4.0f, 200.0f, 1.0f, 0.0f, 0.2f, 8.0f, 3, 14})
-                           : (F32 ? PlanFit{2.5f, 200.0f, 4.0f, 1.0f, 0.2f, 16.0f, 1, 24}
-                                  : PlanFit{2.5f, 200.0f, 4.0f, 3.0f, 0.0f, 4.0f, 1, 24});
+  // The phase alone, us before / now that runs in z are also cut to fill the last round of
+  // workgroups and x is cut on cache lines: binary64 L = 288 465 / 431, 448 1877 / 1540, 512
+  // 2526 / 2350, 544 5307 / 3051, 576 4220 / 3330; binary32 416 701 / 623, 544 1740 / 1426,
+  // 576 2049 / 1595, 700 3581 / 3121, 900 7894 / 6977, 1024 13586 / 10847.  Binary32 up to L =
+  // 400, whose planes have fewer tiles than there are units, keeps the first estimate (352:
+  // 363 and 389).
+  const bool tall = a.L > 400;
+  const PlanFit f = MC ? (F32 ? PlanFit{2.0f, 500.0f, 2.0f, 4.0f, 0.0f, 32.0f, 3, 14}
+                              : PlanFit{4.0f, 200.0f, 1.0f, 0.0f, 0.2f, 8.0f, 3, 14})
+                       : (!F32   ? PlanFit{5.0f, 200.0f, 2.0f, 1.0f, 0.1f, 8.0f, 8, 24, 2.0f}
+                          : tall ? PlanFit{10.0f, 1000.0f, 8.0f, 1.0f, 0.0f, 16.0f, 8, 24, 12.0f}
+                                 : PlanFit{2.5f, 200.0f, 4.0f, 1.0f, 0.2f, 16.0f, 1, 24});
   TilePlan t;
   if (!set_tiles(f, a, row_threads<R, MC>, &t) || (MC && !a.partials)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(a.n[0] * a.n[1] * a.n[2])), block((unsigned)t.T);

@@ -32,10 +32,10 @@ def same(a, b):
 
 # The smallest lattice and its neighbour, rows a multiple of a wave and not, runs of unequal
 # length, tiles of whole rows with rows left over, tiles cut in x (evenly and not) into two
-# and more, more workgroups than compute units
+# and more, more workgroups than compute units, and runs in z that fill their last round
 @pytest.mark.parametrize("L,dtype", [(L, F32) for L in (64, 98, 100, 126, 128, 150, 178, 202, 226,
-                                                        254, 300, 302, 354)]
-                         + [(L, F64) for L in (64, 98, 110, 128, 150, 170, 222, 260)])
+                                                        254, 300, 302, 354, 402, 544)]
+                         + [(L, F64) for L in (64, 98, 110, 128, 150, 170, 222, 260, 404, 448)])
 def test_phase_launches_equal_passes(hsg, L, dtype):
     lats = [hsg.Lattice(L, dtype, seed=5 + L) for _ in range(3)]
     for k, n_or, hb, R, n in SCHEDULES:

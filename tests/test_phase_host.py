@@ -31,7 +31,7 @@ def test_flags_of_a_call():
     assert hsg.call_flags(124, f64) == hsg.call_flags(446, f64, k=5) == one
     assert hsg.call_flags(448, f64, heat_bath=True) == one
     assert hsg.call_flags(126, f64) == hsg.call_flags(180, f64, k=4) == carry
-    assert hsg.call_flags(448, f64, k=5) == carry | hsg.HSG_PHASE_LAUNCH  # a default there
+    assert hsg.call_flags(448, f64, k=5) == one
     assert hsg.call_flags(162, f64) == hsg.call_flags(178, f64, k=8) == hsg.HSG_SNAKE
 
 
