@@ -336,6 +336,12 @@ int hsg_batch_tiles(const hsg_chain *host_chains, int32_t n_chains, const int32_
                     int32_t n_active, int32_t tile_sites, int32_t *tiles_out, int32_t capacity,
                     int32_t *n_tiles);
 
+/* The same table written on the device for every chain c of n_chains, from the number of
+ * its first tile, first_tile_dev[c] (device [n_chains + 1], ascending; a chain without tiles
+ * has the next one's): tiles_dev [n_tiles][2], and zeroes to partials_dev [n_tiles]. */
+int hsg_batch_tile_table(const int32_t *first_tile_dev, int32_t n_chains, int32_t tile_sites,
+                         int32_t *tiles_dev, double *partials_dev, void *stream);
+
 /* Up to n_sweeps sweeps of the chains that own tiles, as a sequence of launches: one
  * per colour pass, each covering the tiles of every listed chain (so lattices too large
  * for one workgroup still fill the GPU, and lattices of every size share launches),

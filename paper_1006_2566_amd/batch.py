@@ -64,13 +64,14 @@ def _bind():
     L.hsg_batch_overlap_fourier.argtypes = [BP, P, I32, P, P]
     L.hsg_pt_overlap_fourier.argtypes = [PP, BP, P, I32, P, P]
     L.hsg_batch_tiles.argtypes = [P, I32, P, I32, I32, P, I32, ctypes.POINTER(I32)]
+    L.hsg_batch_tile_table.argtypes = [P, I32, I32, P, P, P]
     L.hsg_batch_tile_sweep.argtypes = [BP, P, P, I32, I32, P, I32, I32, I32, I32, P]
     L.hsg_batch_group_sweep.argtypes = [BP, P, P, P, I32, I32, P, I32, I32, I32, I32, P]
     for name in ("hsg_batch_check", "hsg_batch_init", "hsg_batch_sweep",
                  "hsg_batch_energy", "hsg_batch_overlap", "hsg_pt_exchange", "hsg_pt_overlap",
                  "hsg_batch_overlap_fourier", "hsg_pt_overlap_fourier", "hsg_batch_tiles",
-                 "hsg_batch_tile_sweep", "hsg_batch_group_sweep", "hsg_batch_init_parts",
-                 "hsg_batch_overlap_parts"):
+                 "hsg_batch_tile_table", "hsg_batch_tile_sweep", "hsg_batch_group_sweep",
+                 "hsg_batch_init_parts", "hsg_batch_overlap_parts"):
         getattr(L, name).restype = ctypes.c_int
     _bound = True
 
@@ -232,19 +233,13 @@ class Batch:
         n_groups = -(-int(end[-1]) // GROUP_SPIN_BYTES)
         last = np.searchsorted(end, end[-1] * np.arange(1, n_groups) / n_groups)
         groups = np.unique(np.concatenate([[0], first[last + 1], first[-1:]])).astype(np.int32)
-        # (chain, first site) of each tile, made where they are read: a million of them for
-        # 12288 chains, 4 ms to make on the host and as long to send
         n, dev = int(first[-1]), self.device
         first = torch.from_numpy(first.astype(np.int32)).to(dev)
         tiles = torch.empty(n, 2, dtype=torch.int32, device=dev)
-        torch.arange(n, dtype=torch.int32, out=tiles[:, 1])
-        tiles[:, 0] = torch.repeat_interleave(
-            torch.from_numpy(count.astype(np.int32)).to(dev), output_size=n)
-        tiles[:, 1] -= first[tiles[:, 0]]
-        tiles[:, 1] *= TILE_SITES
-        partials = torch.zeros(n, dtype=torch.float64, device=dev)
-        if dev.type == "cuda":  # sweeps may run on another stream
-            torch.cuda.current_stream(dev).synchronize()
+        partials = torch.empty(n, dtype=torch.float64, device=dev)
+        check(lib().hsg_batch_tile_table(_ptr(first), self.n, TILE_SITES, _ptr(tiles),
+                                         _ptr(partials), _stream(None)))
+        torch.cuda.current_stream().synchronize()  # sweeps may run on another stream
         return tiles, first, n, partials, groups
 
     def sweep(self, n_sweeps: int, stream=None) -> None:

@@ -881,6 +881,18 @@ int hsg_batch_tiles(const hsg_chain* c, int32_t n_chains, const int32_t* active,
   return HSG_OK;
 }
 
+int hsg_batch_tile_table(const int32_t* first_tile_dev, int32_t n_chains, int32_t tile_sites,
+                         int32_t* tiles_dev, double* partials_dev, void* stream) {
+  if (!first_tile_dev || !tiles_dev || !partials_dev || n_chains < 1 ||
+      ((uintptr_t)tiles_dev & 7))
+    return fail(HSG_EINVAL, "bad arguments to hsg_batch_tile_table");
+  if (tile_sites < 64 || tile_sites > 1024 || (tile_sites & 63))
+    return fail(HSG_EINVAL, "tile_sites must be a multiple of 64 in [64, 1024]");
+  return device_status(hsg::launch_tile_table(first_tile_dev, n_chains, tile_sites, tiles_dev,
+                                              partials_dev, as_stream(stream)),
+                       "batch tile table");
+}
+
 int hsg_batch_pass_sweep(const hsg_batch* b, const int32_t* tiles_dev, int32_t n_tiles,
                          int32_t tile_sites, int32_t max_n_or, int32_t renorm, int32_t n_sweeps,
                          void* stream) {

@@ -271,6 +271,8 @@ template <typename R>
 hipError_t launch_batch_pass_sweep(const hsg_batch* b, const int32_t* tiles, int32_t n_tiles,
                                    int32_t tile_sites, int32_t max_n_or, int32_t renorm,
                                    int32_t n_sweeps, hipStream_t st);
+hipError_t launch_tile_table(const int32_t* first_tile, int32_t n_chains, int32_t tile_sites,
+                             int32_t* tiles, double* partials, hipStream_t st);
 template <typename R>
 hipError_t launch_batch_tile_sweep(const hsg_batch* b, const int32_t* tiles,
                                    const int32_t* first_tile, const int32_t* groups,

@@ -33,6 +33,14 @@ def test_rejected_arguments():
         assert call(**bad) == -1, bad
 
 
+def test_rejected_table():
+    hb._bind()
+    f = lib().hsg_batch_tile_table
+    for bad in ((None, 2, 256, 8, 8), (8, 0, 256, 8, 8), (8, 2, 100, 8, 8), (8, 2, 2048, 8, 8),
+                (8, 2, 256, None, 8), (8, 2, 256, 12, 8), (8, 2, 256, 8, None)):
+        assert f(*bad, None) == -1, bad
+
+
 @pytest.mark.parametrize("L,n,pays", [
     (8, 1, False), (8, 5000, False), (12, 48, False), (16, 192, True), (16, 193, False),
     (20, 512, True), (20, 513, False), (24, 512, True), (24, 4096, False), (32, 1, True),

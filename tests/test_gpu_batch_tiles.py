@@ -4,6 +4,8 @@ counters and budgets, also captured in a graph; and the parallel exchange round 
 the rule walked slot by slot."""
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -44,6 +46,20 @@ def test_tiles_equal_workgroup_per_chain(hb, Ls, dtype):
         # sums of the same binary64 terms: N additions of rounding 2^-53 of the sum of |terms|
         assert torch.allclose(a.E, b.E, rtol=1e-12, atol=1e-12)
     assert int(b._tiles[3].count_nonzero()) == 0  # the partials are left at zero
+
+
+@pytest.mark.parametrize("chains", [None, [0, 3, 5], [1], [6]])
+def test_table_equals_the_hosts(hb, chains):
+    b = hb.Batch(specs(hb, (2, 8, 22, 34, 6, 64, 16)))
+    active = np.arange(b.n, dtype=np.int32) if chains is None else np.array(chains, dtype=np.int32)
+    tiles, first, n, partials, _ = b._tile_table(None if chains is None else active)
+    out, m = np.zeros((n, 2), dtype=np.int32), ctypes.c_int32()
+    hb.check(hb.lib().hsg_batch_tiles(b.table.ctypes.data, b.n, active.ctypes.data, active.size,
+                                      hb.TILE_SITES, out.ctypes.data, n, ctypes.byref(m)))
+    assert m.value == n == first[-1] and partials.count_nonzero() == 0
+    np.testing.assert_array_equal(tiles.cpu().numpy(), out)
+    for c, t in enumerate(first[:-1].tolist()):
+        assert c not in active or tiles[t].tolist() == [c, 0]
 
 
 def test_budgets_and_graph_replay(hb):
