@@ -226,7 +226,11 @@ class Lattice:
         self.spins = torch.empty(n, dtype=dtype, device=self.device)
         self.J = torch.empty(n, dtype=dtype, device=self.device)
         self.E = torch.zeros(1, dtype=torch.float64, device=self.device)
-        self.work = torch.zeros(work_b, dtype=torch.uint8, device=self.device)
+        self.work = torch.empty(work_b, dtype=torch.uint8, device=self.device)
+        # partial sums, zero between calls; a second spin array behind them (from L = 64 up the
+        # larger of the two) is written before it is read, and takes 1.3 GB at L = 382 binary64
+        spare = work_b - spin_b
+        self.work[:spare if L >= 64 and spare > 0 else work_b].zero_()
         self._d = _Lattice(L, _dtype_code(dtype), seed & (2 ** 64 - 1), 0, self.spins.data_ptr(),
                            self.J.data_ptr(), self.E.data_ptr(), self.work.data_ptr(), work_b)
         if init == "random":
