@@ -135,6 +135,14 @@ typedef struct hsg_sweep_params {
                            HSG_PHASE_MC, HSG_BRICK */
 } hsg_sweep_params;
 
+/* How the launches of HSG_PHASE_LAUNCH and HSG_PHASE_MC cut a lattice: n_passes 2 for an
+ * over-relaxation phase, 3 for one with the Monte Carlo pass, 4 for two phases.  tiles[3]:
+ * the number of tiles of L/2 columns, L rows and L planes, whose t-th of n begins at t E / n
+ * (rounded down) of the extent E; threads of a workgroup; wave_rows: whether a wave takes a
+ * row of a tile.  HSG_EINVAL where there is no such launch. */
+int hsg_phase_tiles(int32_t L, int32_t dtype, int32_t n_passes, int32_t *tiles,
+                    int32_t *threads, int32_t *wave_rows);
+
 /* Sizes of the three device buffers of an L^3 lattice of the given dtype.  Any
  * output pointer may be NULL.  HSG_EINVAL for odd L, L < 2, L > HSG_L_MAX or an
  * unknown dtype. */

@@ -543,6 +543,20 @@ int hsg_export(const hsg_lattice* lat, void* canon_spins, void* canon_J, void* s
                        "export");
 }
 
+int hsg_phase_tiles(int32_t L, int32_t dtype, int32_t n_passes, int32_t* tiles,
+                    int32_t* threads, int32_t* wave_rows) {
+  int rc = check_dims(L, dtype);
+  if (rc) return rc;
+  if (!tiles || !threads || !wave_rows) return fail(HSG_EINVAL, "hsg_phase_tiles: NULL output");
+  hsg::PhasePlan plan;
+  if (!hsg::phase_plan(L, dtype == HSG_F32 ? 4 : 8, n_passes, &plan))
+    return fail(HSG_EINVAL, "no launch of %d passes at L = %d", (int)n_passes, (int)L);
+  std::copy(plan.n, plan.n + 3, tiles);
+  *threads = plan.threads;
+  *wave_rows = plan.waves ? 1 : 0;
+  return HSG_OK;
+}
+
 static int sweep_checked(hsg_lattice* lat, const hsg_sweep_params* p, int32_t n_sweeps,
                          void* stream);
 

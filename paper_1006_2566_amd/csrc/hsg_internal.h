@@ -133,7 +133,7 @@ struct PhaseArgs {
   R* out;       // after it (distinct from in)
   const R* J;   // colour-split couplings
   int32_t L;
-  int32_t n[3];  // tiles along x (colour columns), y and z: set by launch_phase
+  int32_t n[3];  // tiles along x (colour columns), y and z: set by the launchers
   uint32_t inv[3];
   // The colour-0 pass of the Monte Carlo phase of sweep mc_sweep, after the phase.  With
   // renorm, every spin is divided by its length between the two.  The energy changes of a
@@ -150,6 +150,14 @@ struct PhaseArgs {
 // work buffer for it (the others run pass by pass without one).
 bool phase_supported(int32_t L);
 bool phase_always(int32_t L);
+// How a launch of two passes (a phase), three (with the Monte Carlo pass) or four (two phases)
+// cuts the lattice; false if there is none.
+struct PhasePlan {
+  int32_t n[3];     // tiles along x (colour columns), y and z
+  int32_t threads;  // of a workgroup
+  bool waves;       // a wave per row of a tile
+};
+bool phase_plan(int32_t L, int32_t elem, int32_t passes, PhasePlan* plan);
 // mc: the mode of the pass that follows the phase, PassMode::OverRelax for the phase alone.
 template <typename R>
 hipError_t launch_phase(const PhaseArgs<R>& a, PassMode mc, hipStream_t stream);

@@ -71,7 +71,7 @@ struct RowSize {
 };
 
 // MODE: of the Monte Carlo pass behind the phase, OverRelax for the phase alone.  WAVES: a wave
-// takes a row of the tile (by_wave below).
+// takes a row of the tile (kByWave below).
 template <typename R, PassMode MODE, bool WAVES>
 __device__ __forceinline__ void row_march(const PhaseArgs<R>& a) {
   constexpr bool MC = MODE != PassMode::OverRelax;
@@ -584,29 +584,33 @@ namespace {
 
 uint32_t row_inv(int32_t d) { return d > 1 ? 0xFFFFFFFFu / (uint32_t)d + 1u : 0u; }
 
-// Tiles of 64 columns: a wave per row and the halo columns on the waves behind those, so that
-// a load of the tile's columns is two cache lines, not three or four.  us of the launch with
-// four hits (one), items row by row / a wave per row: L = 512 1587 / 1510 (1564 / 1394), 640
-// 3252 / 3110 (3080 / 2892), 1024 14038 / 13751 (14083 / 12668).  With fewer columns lanes
-// are idle: 448, 56 columns, 1056 / 1221.
-bool by_wave(bool mc, int32_t nx, int32_t hx) { return mc && hx && nx == 64; }
-
-// Threads of tiles of that many columns and rows (hx: tiles narrower than the lattice), 0 if
-// the kernel does not hold them.
+// Tiles of 64 columns, all of them (the kernel deals 64 columns and the halo's to a row): a
+// wave per row and the halo columns on the waves behind those, so that a load of the tile's
+// columns is two cache lines, not three or four.  us of the launch with four hits (one), items
+// row by row / a wave per row: L = 512 1587 / 1510 (1564 / 1394), 1024 14038 / 13751 (14083 /
+// 12668).  With fewer columns lanes are idle: 448, 56 columns, 1056 / 1221.  The estimate
+// below does not weigh the form, so these two lattices are the only ones cut so.
 template <typename R, bool MC>
-int32_t row_threads(int32_t nx, int32_t ny, int32_t hx) {
+constexpr bool kByWave = MC && sizeof(R) == 4;
+
+// Threads of tiles of that many columns and rows (hx: tiles narrower than the lattice; even:
+// all of them nx columns), 0 if the kernel does not hold them.
+template <typename R, bool MC>
+int32_t row_threads(int32_t nx, int32_t ny, int32_t hx, bool even, bool* waves) {
   using Size = RowSize<R, MC>;
   const int32_t H = MC ? 1 : 0, r0 = ny + 2 + 2 * H, r1 = r0 + 2;
   const int32_t n0 = r0 * (nx + 2 * hx), n1 = r1 * (nx + 4 * hx);
-  const bool waves = by_wave(MC, nx, hx);
-  const int32_t T = (waves ? 64 * r0 + 2 * r0 + 63 : n0 + 63) & ~63;
-  return T <= Size::A && n0 <= Size::A && n1 <= Size::C1 && (waves ? 64 * r1 + 4 * r1 : n1) <= 2 * T
+  *waves = kByWave<R, MC> && hx && even && nx == 64;
+  const int32_t T = (*waves ? 64 * r0 + 2 * r0 + 63 : n0 + 63) & ~63;
+  return T <= Size::A && n0 <= Size::A && n1 <= Size::C1 &&
+                 (*waves ? 64 * r1 + 4 * r1 : n1) <= 2 * T
              ? T
              : 0;
 }
 
 template <typename R>
-int32_t pair_threads(int32_t nx, int32_t ny, int32_t hx) {
+int32_t pair_threads(int32_t nx, int32_t ny, int32_t hx, bool, bool* waves) {
+  *waves = false;
   const int32_t T = ((ny + 8) * (nx + 6 * hx) + 63) & ~63;
   return T <= kPairThreads<R> ? T : 0;
 }
@@ -631,8 +635,9 @@ bool row_plan(const PlanFit& f, int32_t L, int32_t line, Threads threads, int32_
   for (int32_t px = 1; px <= 16; ++px) {
     const int32_t nx = (Lh + px - 1) / px, hx = px > 1 ? 1 : 0;
     if (px > 1 && nx < f.narrow) break;
+    bool waves;
     for (int32_t ny = 2;; ++ny) {
-      const int32_t T = threads(nx, ny, hx);
+      const int32_t T = threads(nx, ny, hx, Lh % px == 0, &waves);
       if (!T) break;
       const int32_t ty = (L + ny - 1) / ny;
       if ((L + ty - 1) / ty != ny) continue;  // no fewer tiles than with the next smaller ny
@@ -656,61 +661,81 @@ bool row_plan(const PlanFit& f, int32_t L, int32_t line, Threads threads, int32_
   return best > 0.0f;
 }
 
-// Tiles of columns, rows and threads of a launch; false if there are none.
-struct TilePlan {
-  int32_t nx, ny, hx, T;
-};
-template <typename R, class Threads>
-bool set_tiles(const PlanFit& f, PhaseArgs<R>& a, Threads threads, TilePlan* t) {
-  if (!phase_supported(a.L) || !row_plan(f, a.L, 128 / (int)sizeof(R), threads, a.n))
-    return false;
-  t->nx = (a.L / 2 + a.n[0] - 1) / a.n[0];
-  t->ny = (a.L + a.n[1] - 1) / a.n[1];
-  t->hx = a.n[0] > 1 ? 1 : 0;
-  t->T = threads(t->nx, t->ny, t->hx);
-  for (int k = 0; k < 3; ++k) a.inv[k] = row_inv(a.n[k]);
-  return t->T > 0;
+template <class Threads>
+bool plan_tiles(const PlanFit& f, int32_t L, int32_t elem, Threads threads, PhasePlan* p) {
+  if (!phase_supported(L) || !row_plan(f, L, 128 / elem, threads, p->n)) return false;
+  const int32_t Lh = L / 2, px = p->n[0], py = p->n[1];
+  p->threads = threads((Lh + px - 1) / px, (L + py - 1) / py, px > 1 ? 1 : 0, Lh % px == 0,
+                       &p->waves);
+  return p->threads > 0;
 }
 
-template <typename R, PassMode MODE>
-hipError_t launch_rows(PhaseArgs<R> a, hipStream_t st) {
-  constexpr bool MC = MODE != PassMode::OverRelax, F32 = sizeof(R) == 4;
+template <typename R, bool MC>
+bool plan_rows(int32_t L, PhasePlan* p) {
+  constexpr bool F32 = sizeof(R) == 4;
   // The phase alone, us before / now that runs in z are also cut to fill the last round of
   // workgroups and x is cut on cache lines: binary64 L = 288 465 / 431, 448 1877 / 1540, 512
   // 2526 / 2350, 544 5307 / 3051, 576 4220 / 3330; binary32 416 701 / 623, 544 1740 / 1426,
   // 576 2049 / 1595, 700 3581 / 3121, 900 7894 / 6977, 1024 13586 / 10847.  Binary32 up to L =
   // 400, whose planes have fewer tiles than there are units, keeps the first estimate (352:
   // 363 and 389).
-  const bool tall = a.L > 400;
+  const bool tall = L > 400;
   const PlanFit f = MC ? (F32 ? PlanFit{2.0f, 500.0f, 2.0f, 4.0f, 0.0f, 32.0f, 3, 14}
                               : PlanFit{4.0f, 200.0f, 1.0f, 0.0f, 0.2f, 8.0f, 3, 14})
                        : (!F32   ? PlanFit{5.0f, 200.0f, 2.0f, 1.0f, 0.1f, 8.0f, 8, 24, 2.0f}
                           : tall ? PlanFit{10.0f, 1000.0f, 8.0f, 1.0f, 0.0f, 16.0f, 8, 24, 12.0f}
                                  : PlanFit{2.5f, 200.0f, 4.0f, 1.0f, 0.2f, 16.0f, 1, 24});
-  TilePlan t;
-  if (!set_tiles(f, a, row_threads<R, MC>, &t) || (MC && !a.partials)) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)(a.n[0] * a.n[1] * a.n[2])), block((unsigned)t.T);
-  if constexpr (MC) {
-    if (by_wave(MC, t.nx, t.hx))
-      hipLaunchKernelGGL((phase_mc_wave_kernel<R, MODE>), grid, block, 0, st, a);
-    else
-      hipLaunchKernelGGL((phase_mc_kernel<R, MODE>), grid, block, 0, st, a);
-  } else
+  return plan_tiles(f, L, (int32_t)sizeof(R), row_threads<R, MC>, p);
+}
+
+template <typename R>
+bool plan_pair(int32_t L, PhasePlan* p) {
+  constexpr PlanFit f = sizeof(R) == 4 ? PlanFit{12.0f, 2000.0f, 4.0f, 4.0f, 0.0f, 32.0f, 3, 14}
+                                       : PlanFit{12.0f, 500.0f, 1.0f, 0.0f, 0.0f, 32.0f, 3, 14};
+  return plan_tiles(f, L, (int32_t)sizeof(R), pair_threads<R>, p);
+}
+
+template <typename R>
+dim3 set_tiles(PhaseArgs<R>& a, const PhasePlan& p) {
+  for (int k = 0; k < 3; ++k) {
+    a.n[k] = p.n[k];
+    a.inv[k] = row_inv(p.n[k]);
+  }
+  return dim3((unsigned)(p.n[0] * p.n[1] * p.n[2]));
+}
+
+template <typename R, PassMode MODE>
+hipError_t launch_rows(PhaseArgs<R> a, hipStream_t st) {
+  constexpr bool MC = MODE != PassMode::OverRelax;
+  PhasePlan p;
+  if (!plan_rows<R, MC>(a.L, &p) || (MC && !a.partials)) return hipErrorInvalidValue;
+  const dim3 grid = set_tiles(a, p), block((unsigned)p.threads);
+  if constexpr (!MC)
     hipLaunchKernelGGL((phase_kernel<R>), grid, block, 0, st, a);
+  else if constexpr (!kByWave<R, MC>)
+    hipLaunchKernelGGL((phase_mc_kernel<R, MODE>), grid, block, 0, st, a);
+  else if (p.waves)
+    hipLaunchKernelGGL((phase_mc_wave_kernel<R, MODE>), grid, block, 0, st, a);
+  else
+    hipLaunchKernelGGL((phase_mc_kernel<R, MODE>), grid, block, 0, st, a);
   return hipGetLastError();
 }
 
 }  // namespace
 
+bool phase_plan(int32_t L, int32_t elem, int32_t passes, PhasePlan* p) {
+  if (passes == 2) return elem == 4 ? plan_rows<float, false>(L, p) : plan_rows<double, false>(L, p);
+  if (passes == 3) return elem == 4 ? plan_rows<float, true>(L, p) : plan_rows<double, true>(L, p);
+  return passes == 4 && (elem == 4 ? plan_pair<float>(L, p) : plan_pair<double>(L, p));
+}
+
 template <typename R>
 hipError_t launch_phase_pair(const PhaseArgs<R>& a0, hipStream_t st) {
-  constexpr PlanFit f = sizeof(R) == 4 ? PlanFit{12.0f, 2000.0f, 4.0f, 4.0f, 0.0f, 32.0f, 3, 14}
-                                       : PlanFit{12.0f, 500.0f, 1.0f, 0.0f, 0.0f, 32.0f, 3, 14};
   PhaseArgs<R> a = a0;
-  TilePlan t;
-  if (!set_tiles(f, a, pair_threads<R>, &t)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(phase_pair_kernel<R>, dim3((unsigned)(a.n[0] * a.n[1] * a.n[2])),
-                     dim3((unsigned)t.T), 0, st, a);
+  PhasePlan p;
+  if (!plan_pair<R>(a.L, &p)) return hipErrorInvalidValue;
+  const dim3 grid = set_tiles(a, p);
+  hipLaunchKernelGGL(phase_pair_kernel<R>, grid, dim3((unsigned)p.threads), 0, st, a);
   return hipGetLastError();
 }
 template hipError_t launch_phase_pair<float>(const PhaseArgs<float>&, hipStream_t);
