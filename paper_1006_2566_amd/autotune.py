@@ -128,10 +128,13 @@ def sweep_flags(L: int, dtype: torch.dtype = torch.float32, k: int = 4, n_or: in
 
 def batch_threads(batch, n_sweeps: int = 1, retune: bool = False,
                   path: str | None = None) -> int:
-    """Workgroup size of hsg_batch_sweep for this batch (chain sizes, k, n_or)."""
+    """Workgroup size of hsg_batch_sweep for this batch (chain sizes, k, n_or).  Of a batch
+    that runs over tiles at the default size, the others are timed with a workgroup per
+    chain."""
     from collections import Counter
     hist = sorted(Counter((int(c.L), int(c.k), int(c.n_or)) for c in batch.specs).items())
-    key = f"batch {str(batch.dtype).replace('torch.', '')} {hist}"
+    tiles = " tiles" if batch._tiles is not None else ""
+    key = f"batch {str(batch.dtype).replace('torch.', '')} {hist}{tiles}"
     saved = (batch.threads, batch.sweep_ctr.clone(), batch.E.clone(), batch.spins.clone(),
              batch.remaining.clone() if batch.remaining is not None else None)
 

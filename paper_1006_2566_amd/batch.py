@@ -138,11 +138,17 @@ def groups_pay(specs) -> bool:
     return sum((1 if l >= 32 else -1) * n * l ** 3 for l, n in number.items()) > 0
 
 
+THREADS = 256
+
+
 class Batch:
-    """Chains resident on the GPU, advanced together by ``sweep``."""
+    """Chains resident on the GPU, advanced together by ``sweep``.
+
+    ``threads``: workgroup size of the launch with a workgroup per chain.  Another than the
+    default asks for that launch, whatever the chains."""
 
     def __init__(self, specs: list[ChainSpec], dtype: torch.dtype = torch.float32,
-                 device: str | torch.device = "cuda", threads: int = 256,
+                 device: str | torch.device = "cuda", threads: int = THREADS,
                  order: np.ndarray | None = None, init: bool = True, track_remaining=False,
                  stream=None):
         _bind()
@@ -243,7 +249,7 @@ class Batch:
         return tiles, first, n, partials, groups
 
     def sweep(self, n_sweeps: int, stream=None) -> None:
-        if self._tiles is None:
+        if self._tiles is None or self.threads not in (0, THREADS):
             check(lib().hsg_batch_sweep(ctypes.byref(self._d), int(n_sweeps), _stream(stream)))
             return
         if self._alone is not None:

@@ -1,0 +1,62 @@
+"""Which entry point a batch's sweep calls, without a GPU: a stand-in for the library records
+the calls."""
+from __future__ import annotations
+
+import pytest
+import torch
+
+from paper_1006_2566_amd import batch as hb
+
+
+class Recorder:
+    def __init__(self):
+        self.calls = []
+
+    def __getattr__(self, name):
+        def call(*args):
+            self.calls.append(name)
+            return 0
+        return call
+
+
+class Stream:
+    cuda_stream = 0
+
+    def synchronize(self):
+        pass
+
+
+@pytest.fixture
+def rec(monkeypatch):
+    r = Recorder()
+    hb._bind()
+    monkeypatch.setattr(hb, "lib", lambda: r)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: Stream())
+    return r
+
+
+def chains(L, n, **kw):
+    return [hb.ChainSpec(L=L, seed=i, J_group=1000 * L + i, J_seed=i, **kw) for i in range(n)]
+
+
+def route(rec, batch, n_sweeps=1):
+    rec.calls.clear()
+    batch.sweep(n_sweeps)
+    return [c.replace("hsg_batch_", "") for c in rec.calls]
+
+
+def batch(specs, **kw):
+    return hb.Batch(specs, device="cpu", init=False, **kw)
+
+
+def test_a_workgroup_size_asked_for(rec):
+    b = batch(chains(16, 4))
+    assert route(rec, b) == ["group_sweep"]
+    for threads in (64, 128, 512, 1024):
+        b.threads = threads
+        assert route(rec, b) == ["sweep"]
+        assert route(rec, batch(chains(16, 4), threads=threads)) == ["sweep"]
+    for threads in (0, hb.THREADS):
+        b.threads = threads
+        assert route(rec, b) == ["group_sweep"]
+    assert route(rec, batch(chains(8, 4), threads=256)) == ["sweep"]
