@@ -248,8 +248,25 @@ class Batch:
         torch.cuda.current_stream().synchronize()  # sweeps may run on another stream
         return tiles, first, n, partials, groups
 
-    def sweep(self, n_sweeps: int, stream=None) -> None:
+    def _over_tiles(self, n_sweeps: int) -> bool:
+        """Whether a call of that many sweeps goes over the batch's tiles.
+
+        Launches over tiles are made for every sweep of the call, also where the budgets
+        (``remaining``) end before it, and one that finds nothing to do takes 3.3 us (10 over
+        39 000 tiles); a workgroup per chain ends with its budget.  So a batch with budgets
+        takes the tiles as long as all of a call's launches, idle, cost no more than a sweep
+        of its largest chain by a workgroup, 3 ns a site at k = 1 and 5.5 at 4.  us, 48 chains of L = 32,
+        tiles / workgroups: 10 sweeps with a budget of 10 248 / 2008, with none 76 / 10; 1000
+        sweeps with a budget of 10 6663 / 2011, with none 6870 / 10."""
         if self._tiles is None or self.threads not in (0, THREADS):
+            return False
+        if self.remaining is None:
+            return True
+        launches = 2 * n_sweeps * (self._any[0] + self._any[1]) * (self._tiles[4].size - 1)
+        return 600 * launches <= int(self.table["L"].max()) ** 3
+
+    def sweep(self, n_sweeps: int, stream=None) -> None:
+        if not self._over_tiles(n_sweeps):
             check(lib().hsg_batch_sweep(ctypes.byref(self._d), int(n_sweeps), _stream(stream)))
             return
         if self._alone is not None:

@@ -60,3 +60,22 @@ def test_a_workgroup_size_asked_for(rec):
         b.threads = threads
         assert route(rec, b) == ["group_sweep"]
     assert route(rec, batch(chains(8, 4), threads=256)) == ["sweep"]
+
+
+def test_budgets_that_may_end_before_the_call(rec):
+    """At L = 32 and one phase a sweep, 600 * 2 * 27 <= 32^3 < 600 * 2 * 28."""
+    b = batch(chains(32, 4), track_remaining=True)
+    assert route(rec, b, 27) == ["group_sweep"]
+    assert route(rec, b, 28) == route(rec, b, 10 ** 6) == ["sweep"]
+    b = batch(chains(32, 4, n_or=2), track_remaining=True)
+    assert route(rec, b, 9) == ["group_sweep"] and route(rec, b, 10) == ["sweep"]
+    assert route(rec, batch(chains(32, 4)), 10 ** 6) == ["group_sweep"]
+
+
+def test_budgets_of_a_batch_in_groups(rec, monkeypatch):
+    monkeypatch.setattr(hb, "tiles_pay", lambda specs: False)
+    monkeypatch.setattr(hb, "GROUP_SPIN_BYTES", 2 * 3 * 32 ** 3 * 4)
+    b = batch(chains(32, 8) + chains(16, 3), track_remaining=True)
+    assert b._tiles[4].size - 1 == 4
+    assert route(rec, b, 6) == ["sweep", "group_sweep"]  # the small chains, then the others
+    assert route(rec, b, 7) == ["sweep"]
