@@ -114,11 +114,49 @@ def tiles_pay(specs) -> bool:
     ones, which do not stay near their compute unit, up to 2048 (L = 48: 2692 against
     2554).  Beyond, both forms are bound by the rate of the whole GPU, and the one launch,
     whose chains of a sample read their couplings together, is the faster (12288 chains of
-    L = 16 .. 48: 57.9 against 60.4 ms for ten sweeps)."""
-    number = Counter(c.L for c in specs)
-    L = max(number)
-    limit = 2048 if L >= 32 else 512 if L >= 20 else 192 if L >= 16 else 0
-    return sum(n * l ** 3 for l, n in number.items()) <= limit * L ** 3
+    L = 16 .. 48: 57.9 against 60.4 ms for ten sweeps).
+
+    Over-relaxation phases and single hits, which a workgroup has the less trouble with, move
+    the line (us a sweep, tiles / workgroups: L = 16 k = 1 and two phases, 96 chains 28 / 33,
+    128 35 / 33, 192 43 / 33; k = 4 and three, 128 47 / 50, 160 52 / 50; L = 20 k = 1 and one,
+    384 59 / 64, 448 65 / 65, 512 72 / 66).  And every phase of the batch is two launches of
+    3.5 us, whoever has it: where only small chains have most of them, a workgroup each is
+    faster.  8 chains of L = 8 with k = 1 and n_or phases beside 8 of L = 32 with k = 4: n_or =
+    3 29 / 149, 10 82 / 149, 25 187 / 149, 50 365 / 149."""
+    kinds = _kinds(specs)
+    L = max(L for L, *_ in kinds)
+    n_or = max(o for l, _, o in kinds if l == L)
+    k = min(k for l, k, _ in kinds if l == L)
+    # over-relaxation behind fewer than four hits, two phases or more behind more, or neither
+    at = 0 if n_or and k < 4 else 1 if n_or > 1 else 2
+    limit = (2048 if L >= 32 else 512 if L >= 24 else (416, 480, 512)[at] if L >= 20 else
+             (112, 152, 192)[at] if L >= 16 else 0)
+    return (sum(n * l ** 3 for (l, _, _), n in kinds.items()) <= limit * L ** 3 and
+            max(_alone(*c) for c in kinds) > 7.0 * _phases(kinds))
+
+
+def _kinds(specs) -> Counter:
+    """Number of chains of every L, hits (one where a draw is all that counts) and n_or, of
+    specs or of a batch's table (a tenth of the time)."""
+    if isinstance(specs, Counter):
+        return specs
+    if isinstance(specs, np.ndarray):
+        L, k, n_or = (specs[f].astype(np.int64) for f in ("L", "k_hits", "n_or"))
+        k = np.where(specs["flags"] & HSG_HEAT_BATH, np.minimum(k, 1), k)
+        v, n = np.unique(L << 32 | k << 16 | n_or, return_counts=True)
+        return Counter({(int(x) >> 32, int(x) >> 16 & 0xFFFF, int(x) & 0xFFFF): int(m)
+                        for x, m in zip(v, n)})
+    return Counter([(c.L, 1 if c.heat_bath and c.k else c.k, c.n_or) for c in specs])
+
+
+def _alone(L: int, k: int, n_or: int) -> float:
+    """us a sweep that a workgroup takes for a chain, fitted to L = 8 to 32, k = 1 to 16."""
+    return L ** 3 * ((2.3e-3 + 0.8e-3 * k if k else 0.0) + 2e-3 * n_or)
+
+
+def _phases(kinds) -> int:
+    """Phases of a sweep that launches over all of these chains have."""
+    return int(any(k for _, k, _ in kinds)) + max(n_or for _, _, n_or in kinds)
 
 
 # Bytes of spins that chains advanced together may have: with them in the 256 MB memory-side
@@ -133,9 +171,24 @@ def groups_pay(specs) -> bool:
     tiles of the others, have a workgroup each.  ms for ten sweeps, a workgroup per chain /
     in groups: 3072 chains of L = 48 k = 4 39.4 / 35.6, k = 1 36.9 / 26.6; 3072 of L = 32
     11.1 / 10.8, k = 1 9.9 / 7.9 (L = 24 4.8 / 5.0; 16 1.6 / 1.9); L = 48 by 64, 128, 512 MB
-    37.8, 37.0, 36.7."""
-    number = Counter(c.L for c in specs)
-    return sum((1 if l >= 32 else -1) * n * l ** 3 for l, n in number.items()) > 0
+    37.8, 37.0, 36.7.
+
+    Not where most tiles have nothing to do in most phases: with n_or phases in a share f of
+    3072 chains of L = 32 and k = 4, none in the others, us a sweep, workgroups / groups: n_or
+    = 2 f = 0.01 1181 / 1328, 0.2 1499 / 1453, 0.5 1982 / 1832; 8 and 0.1 1887 / 2571, 0.33 3478
+    / 3503, 0.5 4768 / 4316.  The line is at 0.45 of the tiles' phases (of these 0.34, 0.47,
+    0.67; 0.20, 0.40, 0.56).  Nor where the smaller chains, which go first, are at work for more
+    than a quarter of what all take by workgroups, about 500 at a time."""
+    kinds = _kinds(specs)
+    large = {c: n for c, n in kinds.items() if c[0] >= 32}
+    small = [c for c in kinds if c[0] < 32]
+    sites = sum(n * L ** 3 for (L, _, _), n in large.items())
+    if 2 * sites <= sum(n * L ** 3 for (L, _, _), n in kinds.items()):
+        return False
+    own = sum(n * c[0] ** 3 * _phases([c]) for c, n in large.items())
+    whole = max(max(_alone(*c) for c in kinds), sum(n * _alone(*c) for c, n in kinds.items()) / 500)
+    return (own >= 0.45 * _phases(large) * sites and
+            max((_alone(*c) for c in small), default=0.0) <= 0.25 * whole)
 
 
 THREADS = 256
@@ -198,12 +251,12 @@ class Batch:
                          self.remaining.data_ptr() if self.remaining is not None else None,
                          self.order.data_ptr(), threads, 0)
         self._export_work: dict[int, torch.Tensor] = {}
-        self._any = (int((table["k_hits"] > 0).any()), int(table["n_or"].max(initial=0)),
-                     int((table["renorm_every"] > 0).any()))
         self._tiles, self._alone = None, None
-        if tiles_pay(self.specs):
+        self._largest = int(table["L"].max()) ** 3  # sites
+        kinds = _kinds(table)
+        if tiles_pay(kinds):
             self._tiles = self._tile_table()
-        elif groups_pay(self.specs):
+        elif groups_pay(kinds):
             large = np.flatnonzero(table["L"] >= 32)
             if int((table["L"][large].astype(np.int64) ** 3 // 2 // TILE_SITES).sum()) < self.n:
                 large = None
@@ -228,7 +281,10 @@ class Batch:
     def _tile_table(self, chains: np.ndarray | None = None) -> tuple:
         """Tiles of every chain (or of these, ascending: the others have none), each chain's
         first tile, the number of tiles, their energy partials and the groups: the first tile
-        of each, and the number of tiles."""
+        of each, and the number of tiles.  The phases of a sweep are those chains'."""
+        own = self.table if chains is None else self.table[chains]
+        self._any = (int((own["k_hits"] > 0).any()), int(own["n_or"].max(initial=0)),
+                     int((own["renorm_every"] > 0).any()))
         Ls = self.table["L"].astype(np.int64)
         has = np.zeros(self.n, dtype=np.int64)
         has[slice(None) if chains is None else chains] = 1
@@ -255,15 +311,15 @@ class Batch:
         (``remaining``) end before it, and one that finds nothing to do takes 3.3 us (10 over
         39 000 tiles); a workgroup per chain ends with its budget.  So a batch with budgets
         takes the tiles as long as all of a call's launches, idle, cost no more than a sweep
-        of its largest chain by a workgroup, 3 ns a site at k = 1 and 5.5 at 4.  us, 48 chains of L = 32,
-        tiles / workgroups: 10 sweeps with a budget of 10 248 / 2008, with none 76 / 10; 1000
+        of its largest chain by a workgroup, 3 ns a site at k = 1 and 5.5 at 4.  us, 48 chains of
+        L = 32, tiles / workgroups: 10 sweeps with a budget of 10 248 / 2008, with none 76 / 10; 1000
         sweeps with a budget of 10 6663 / 2011, with none 6870 / 10."""
         if self._tiles is None or self.threads not in (0, THREADS):
             return False
         if self.remaining is None:
             return True
         launches = 2 * n_sweeps * (self._any[0] + self._any[1]) * (self._tiles[4].size - 1)
-        return 600 * launches <= int(self.table["L"].max()) ** 3
+        return 600 * launches <= self._largest
 
     def sweep(self, n_sweeps: int, stream=None) -> None:
         if not self._over_tiles(n_sweeps):
