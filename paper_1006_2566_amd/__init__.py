@@ -70,13 +70,35 @@ def default_flags(L: int, dtype=None) -> int:
     return HSG_SNAKE | (HSG_PHASE_LAUNCH if f64 else HSG_PHASE_MC)
 
 
+def _brick_hits(L: int, f64: bool, n_or: int) -> float:
+    """Most Metropolis hits with which the small lattices' launches are the faster.
+
+    One workgroup has the hits of a whole lattice to do, and a brick those of its ring again,
+    where a pass has the whole chip; every over-relaxation phase saves launches, worth some hits
+    more.  us a sweep with one such phase, colour passes / HSG_BRICK: one workgroup, L = 10 k =
+    64 36.7 / 32.8, 256 104 / 126; 12 and 16 18.2 / 18.1, 64 36.6 / 64.5; 14 and 8 16.0 / 14.2,
+    16 18.3 / 24.8; binary64 10 and 16 22.1 / 19.9, 32 31.9 / 36.8.  Bricks: 24 and 256 130 / 102;
+    44 and 16 19.7 / 18.1, 32 24.9 / 26.2; 48 and 8 17.2 / 16.6, 16 19.1 / 21.6; 64 and 8 20.1 /
+    19.2, 16 23.3 / 25.4, 64 47.2 / 61.8; binary64 14 and 16 23.3 / 21.7, 32 33.2 / 36.7; 36 and 8
+    20.0 / 18.3, 16 24.7 / 24.9, 64 53.9 / 64.6."""
+    if f64:
+        a, b = ((12, 10) if L == 10 else (14, 3) if L == 14 else (10, 3) if L >= 34 else
+                (float("inf"), 0))
+    else:
+        a, b = ((56, 40) if L == 10 else (11, 6) if L == 12 else (5, 4.5) if L == 14 else
+                (12, 0) if L == 46 else (8, 0) if L >= 48 else (28, 6) if L >= 34 else
+                (float("inf"), 0))
+    return a + b * n_or
+
+
 # Bytes of spins and couplings, 6 L^3 values, that colour passes in place find in the 256 MB
 # memory-side cache, but launches that also read or write a second spin array (9 L^3) do not.
 PHASE_CACHE_BYTES = (204_000_000, 272_000_000)
 
 
 def call_flags(L: int, dtype=None, k: int = 1, heat_bath: bool = False, n_or: int = 1) -> int:
-    """Traversal flags of a sweep that names none, by its hits and over-relaxation phases: over
+    """Traversal flags of a sweep that names none, by its hits and over-relaxation phases.
+    Small lattices run pass by pass where the hits are many (_brick_hits).  Over
     default_flags, every even L from 98 to 1024 runs its over-relaxation phases in launches
     of one or two, the last of a sweep with the next sweep's colour-0 Monte Carlo pass where
     that pays.  us a sweep on MI355X with one over-relaxation phase, colour passes / a launch
@@ -111,6 +133,8 @@ def call_flags(L: int, dtype=None, k: int = 1, heat_bath: bool = False, n_or: in
     without the exception for the cache (218 k = 4, three phases: 362 / 343 / 340)."""
     f64 = dtype is not None and str(dtype) in ("torch.float64", "float64")
     f = default_flags(L, dtype)
+    if f & HSG_BRICK and not heat_bath and k > _brick_hits(L, f64, n_or):
+        return f & ~HSG_BRICK
     if L < PHASE_MIN_L or not phase_supported(L):
         return f
     if n_or > 0 and n_or % 2 == 0:
