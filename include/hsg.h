@@ -101,8 +101,9 @@ extern "C" {
                                Not with HSG_FUSED */
 
 #define HSG_BRICK 2048     /* small lattices, several colour passes per launch.  L <= 14 (10
-                               in binary64): all sweeps of the call in one launch (of up to
-                               4096), one workgroup holding the lattice.  Up to L =
+                               in binary64): the sweeps of the call in one launch (of up to
+                               4096, and 8192 phases or groups of four hits), one workgroup
+                               holding the lattice.  Up to L =
                                HSG_BRICK_MAX_L (40 in binary64): a launch per phase, each
                                workgroup holding some rows of the lattice and those around
                                them in LDS; uses the second spin array of the work buffer.

@@ -339,8 +339,10 @@ int sweep_fused(hsg_lattice* lat, const hsg_sweep_params* p, int32_t n_sweeps, h
   return HSG_OK;
 }
 
-// HSG_BRICK, tiny_supported: the sweeps of the call in launches of one workgroup.
-constexpr int32_t kTinySweeps = 4096;  // of a launch: some ten milliseconds
+// HSG_BRICK, tiny_supported: the sweeps of the call in launches of one workgroup.  A phase
+// (four Metropolis hits are one, heat-bath draws together one) takes up to 6 us, so that a
+// launch lasts up to 50 ms, or for one sweep where that is more.
+constexpr int32_t kTinySweeps = 4096, kTinyPhases = 8192;
 template <typename R>
 int sweep_tiny(hsg_lattice* lat, const hsg_sweep_params* p, int32_t n_sweeps, hipStream_t st) {
   using namespace hsg;
@@ -356,9 +358,11 @@ int sweep_tiny(hsg_lattice* lat, const hsg_sweep_params* p, int32_t n_sweeps, hi
   a.renorm_every = p->renorm_every;
   a.L = lat->L;
   const PassMode mc = (p->flags & HSG_HEAT_BATH) ? PassMode::HeatBath : PassMode::Metropolis;
+  const int32_t draws = mc == PassMode::HeatBath ? std::min(p->k_hits, 1) : (p->k_hits + 3) / 4;
+  const int32_t most = std::max(1, std::min(kTinySweeps, kTinyPhases / (draws + p->n_or)));
   for (int32_t n = 0; n < n_sweeps; n += a.n_sweeps) {
     a.sweep = (uint32_t)(lat->sweep + (uint64_t)n);
-    a.n_sweeps = std::min(kTinySweeps, n_sweeps - n);
+    a.n_sweeps = std::min(most, n_sweeps - n);
     int rc = device_status(
         recorded(HSG_LAUNCH_MARCH, st, [&] { return launch_tiny<R>(a, mc, st); }), "sweeps");
     if (rc) return rc;
