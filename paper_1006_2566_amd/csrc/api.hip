@@ -363,6 +363,9 @@ int sweep_tiny(hsg_lattice* lat, const hsg_sweep_params* p, int32_t n_sweeps, hi
   for (int32_t n = 0; n < n_sweeps; n += a.n_sweeps) {
     a.sweep = (uint32_t)(lat->sweep + (uint64_t)n);
     a.n_sweeps = std::min(most, n_sweeps - n);
+    if (p->renorm_every > 0)
+      a.until_renorm = (int32_t)((uint64_t)p->renorm_every -
+                                 (lat->sweep + (uint64_t)n) % (uint64_t)p->renorm_every);
     int rc = device_status(
         recorded(HSG_LAUNCH_MARCH, st, [&] { return launch_tiny<R>(a, mc, st); }), "sweeps");
     if (rc) return rc;

@@ -211,6 +211,7 @@ struct TinyArgs {
   R beta;
   uint32_t seed_lo, seed_hi, sweep;
   int32_t k_hits, n_or, renorm_every, n_sweeps, L;
+  int32_t until_renorm;  // sweeps up to and with the first renormalised one
 };
 template <typename R>
 hipError_t launch_tiny(const TinyArgs<R>& a, PassMode mc, hipStream_t stream);

@@ -321,6 +321,7 @@ __global__ __launch_bounds__(2 * T) void tiny_kernel(TinyArgs<R> a) {
       put(r);
     });
   };
+  int32_t until_renorm = a.until_renorm;
   for (int32_t n = 0; n < a.n_sweeps; ++n) {
     const uint32_t sweep = a.sweep + (uint32_t)n;
     const bool more = mc && n + 1 < a.n_sweeps;
@@ -352,7 +353,8 @@ __global__ __launch_bounds__(2 * T) void tiny_kernel(TinyArgs<R> a) {
         points();
       __syncthreads();
     }
-    if (a.renorm_every > 0 && (sweep + 1u) % (uint32_t)a.renorm_every == 0u) {
+    if (a.renorm_every > 0 && --until_renorm == 0) {
+      until_renorm = a.renorm_every;
       each([&](int r) {
         sp[r] = unit_vector(sp[r]);
         put(r);
@@ -408,6 +410,7 @@ __global__ __launch_bounds__(T) void tiny_both_kernel(TinyArgs<R> a) {
   __syncthreads();
   const double E0 = threadIdx.x == 0 ? *a.E : 0.0;
   double dE = 0.0;
+  int32_t until_renorm = a.until_renorm;
   for (int32_t n = 0; n < a.n_sweeps; ++n) {
     const uint32_t sweep = a.sweep + (uint32_t)n;
     for (int32_t phase = a.k_hits > 0 ? 0 : 1; phase <= a.n_or; ++phase) {
@@ -443,7 +446,8 @@ __global__ __launch_bounds__(T) void tiny_both_kernel(TinyArgs<R> a) {
         __syncthreads();
       }
     }
-    if (a.renorm_every > 0 && (sweep + 1u) % (uint32_t)a.renorm_every == 0u) {
+    if (a.renorm_every > 0 && --until_renorm == 0) {
+      until_renorm = a.renorm_every;
 #pragma unroll
       for (int c = 0; c < 2; ++c)
 #pragma unroll

@@ -30,3 +30,14 @@ def test_launches_of_a_call(hsg, k, n_or, heat_bath, n, launches):
     assert torch.equal(a.spins, b.spins)
     # the energy changes of 64 sites and n sweeps, added in another order
     assert abs(a.E.item() - b.E.item()) <= 1e-12 * n * max(1, k)
+
+
+@pytest.mark.parametrize("L,dtype", [(8, torch.float32), (14, torch.float32), (10, torch.float64)])
+@pytest.mark.parametrize("every", [2, 3, 5])
+def test_renormalisation_at_the_last_sweep_index(hsg, L, dtype, every):
+    """Sweeps 2^32 - 3 to 2^32 - 1; 2^32 is a multiple of 2, not of 3 or 5."""
+    a, b = [hsg.Lattice(L, dtype, seed=3) for _ in range(2)]
+    for lat, flags in ((a, 0), (b, hsg.HSG_BRICK)):
+        lat.sweep_index = 2 ** 32 - 3
+        lat.sweep(T=0.5, k=1, n_or=1, renorm_every=every, n_sweeps=3, flags=flags)
+    assert torch.equal(a.spins, b.spins) and b.sweep_index == 2 ** 32
