@@ -61,7 +61,8 @@ def default_flags(L: int, dtype=None) -> int:
     order, and for multiples of 64 from 256 up over-relaxation phases as one launch each --
     in binary32 with the next sweep's colour-0 Monte Carlo pass in the same launch.
     Spins are the same either way.  A sweep that names no flags also looks at its hits
-    (call_flags)."""
+    (call_flags).  hsg_sweep_noalloc takes neither HSG_BRICK nor the phase launches; HSG_BRICK
+    goes with HSG_HEAT_BATH and HSG_SNAKE alone (Lattice.sweep drops it beside others)."""
     f64 = dtype is not None and str(dtype) in ("torch.float64", "float64")
     if L <= (BRICK_MAX_L_F64 if f64 else BRICK_MAX_L):
         return HSG_SNAKE | HSG_BRICK
@@ -133,7 +134,7 @@ def call_flags(L: int, dtype=None, k: int = 1, heat_bath: bool = False, n_or: in
     without the exception for the cache (218 k = 4, three phases: 362 / 343 / 340)."""
     f64 = dtype is not None and str(dtype) in ("torch.float64", "float64")
     f = default_flags(L, dtype)
-    if f & HSG_BRICK and not heat_bath and k > _brick_hits(L, f64, n_or):
+    if f & HSG_BRICK and k > 5 and not heat_bath and k > _brick_hits(L, f64, n_or):
         return f & ~HSG_BRICK
     if L < PHASE_MIN_L or not phase_supported(L):
         return f
@@ -300,11 +301,18 @@ class Lattice:
         return s, j
 
     # --------------------------------------------------------------- dynamics
+    def _flags(self, flags: int | None, k: int, heat_bath: bool, n_or: int) -> int:
+        if flags is None:
+            return call_flags(self.L, self.dtype, k, heat_bath, n_or)
+        f = int(flags)
+        # default_flags() with a traversal flag added: the traversal that was asked for
+        return f if f & ~(HSG_HEAT_BATH | HSG_SNAKE | HSG_BRICK) == 0 else f & ~HSG_BRICK
+
     def sweep(self, T: float, k: int = 1, n_or: int = 0, renorm_every: int = 0,
               n_sweeps: int = 1, heat_bath: bool = False, flags: int | None = None,
               stream=None) -> None:
         """n_sweeps sweeps; flags None = call_flags(L, dtype, k, heat_bath, n_or)."""
-        f = call_flags(self.L, self.dtype, k, heat_bath, n_or) if flags is None else int(flags)
+        f = self._flags(flags, k, heat_bath, n_or)
         p = _SweepParams(float(T), int(k), int(n_or), int(renorm_every),
                          (HSG_HEAT_BATH if heat_bath else 0) | f)
         check(lib().hsg_sweep(ctypes.byref(self._d), ctypes.byref(p), int(n_sweeps),
@@ -316,7 +324,7 @@ class Lattice:
         """As sweep(), with every launch timed by HIP events on the launch stream:
         [(launch kind, ms)] in launch order (hsg_sweep_timed; waits for the stream)."""
         import numpy as np
-        f = call_flags(self.L, self.dtype, k, heat_bath, n_or) if flags is None else int(flags)
+        f = self._flags(flags, k, heat_bath, n_or)
         p = _SweepParams(float(T), int(k), int(n_or), int(renorm_every),
                          (HSG_HEAT_BATH if heat_bath else 0) | f)
         kinds = np.zeros(capacity, dtype=np.int32)
