@@ -173,7 +173,7 @@ int32_t march_max_stages();
 template <typename R>
 hipError_t launch_march(const MarchArgs<R>& a, int32_t n_stages, hipStream_t stream);
 
-// Small lattices: several colour passes per launch (kernels_brick.hip).
+// Small lattices: several colour passes per launch (kernels_brick.h).
 constexpr int kBrickMaxL = 64;
 // One workgroup holds a lattice of that size and element size.
 bool tiny_supported(int32_t L, int32_t elem);

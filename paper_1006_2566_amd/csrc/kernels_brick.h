@@ -19,6 +19,8 @@
 // Site arithmetic (field of eq. 2 in the fixed order, then apply_update) and therefore the
 // spins are those of the single passes, bit for bit; only the order of the binary64 sum of
 // energy changes differs.
+//
+// This file defines the launchers: one source includes it, kernels_march.hip.
 #pragma once
 
 #include "hsg_device.h"
