@@ -140,12 +140,15 @@ def _kinds(specs) -> Counter:
     specs or of a batch's table (a tenth of the time)."""
     if isinstance(specs, Counter):
         return specs
-    if isinstance(specs, np.ndarray):
+    if isinstance(specs, np.ndarray) and specs.size > 256:
         L, k, n_or = (specs[f].astype(np.int64) for f in ("L", "k_hits", "n_or"))
         k = np.where(specs["flags"] & HSG_HEAT_BATH, np.minimum(k, 1), k)
         v, n = np.unique(L << 32 | k << 16 | n_or, return_counts=True)
         return Counter({(int(x) >> 32, int(x) >> 16 & 0xFFFF, int(x) & 0xFFFF): int(m)
                         for x, m in zip(v, n)})
+    if isinstance(specs, np.ndarray):
+        return Counter([(L, min(k, 1) if f & HSG_HEAT_BATH else k, n_or) for L, k, n_or, f in
+                        specs[["L", "k_hits", "n_or", "flags"]].tolist()])
     return Counter([(c.L, 1 if c.heat_bath and c.k else c.k, c.n_or) for c in specs])
 
 
@@ -244,13 +247,6 @@ class Batch:
             order = lpt_order([c.L for c in self.specs], [c.J_group for c in self.specs])
         if not np.array_equal(np.sort(np.asarray(order)), np.arange(self.n)):
             raise ValueError("order must be a permutation of the chain indices")
-        self.order = torch.from_numpy(np.ascontiguousarray(order, dtype=np.int32)).to(dev)
-        self._d = _Batch(self.n, _dtype_code(dtype), self.chains.data_ptr(), self.spins.data_ptr(),
-                         self.J.data_ptr(), self.beta.data_ptr(), self.E.data_ptr(),
-                         self.sweep_ctr.data_ptr(),
-                         self.remaining.data_ptr() if self.remaining is not None else None,
-                         self.order.data_ptr(), threads, 0)
-        self._export_work: dict[int, torch.Tensor] = {}
         self._tiles, self._alone = None, None
         self._largest = int(table["L"].max()) ** 3  # sites
         kinds = _kinds(table)
@@ -261,9 +257,17 @@ class Batch:
             if int((table["L"][large].astype(np.int64) ** 3 // 2 // TILE_SITES).sum()) < self.n:
                 large = None
             self._tiles = self._tile_table(large)
-            small = np.asarray(order)[table["L"][np.asarray(order)] < 32]
-            if large is not None and small.size:
+            if large is not None and large.size < self.n:
+                small = np.asarray(order)[table["L"][np.asarray(order)] < 32]
                 self._alone = torch.from_numpy(small.astype(np.int32)).to(dev)
+        # (a copy to the device waits for the stream: the tile table is ready for any other)
+        self.order = torch.from_numpy(np.ascontiguousarray(order, dtype=np.int32)).to(dev)
+        self._d = _Batch(self.n, _dtype_code(dtype), self.chains.data_ptr(), self.spins.data_ptr(),
+                         self.J.data_ptr(), self.beta.data_ptr(), self.E.data_ptr(),
+                         self.sweep_ctr.data_ptr(),
+                         self.remaining.data_ptr() if self.remaining is not None else None,
+                         self.order.data_ptr(), threads, 0)
+        self._export_work: dict[int, torch.Tensor] = {}
         if init:
             self.init(stream)
 
@@ -283,25 +287,26 @@ class Batch:
         first tile, the number of tiles, their energy partials and the groups: the first tile
         of each, and the number of tiles.  The phases of a sweep are those chains'."""
         own = self.table if chains is None else self.table[chains]
-        self._any = (int((own["k_hits"] > 0).any()), int(own["n_or"].max(initial=0)),
-                     int((own["renorm_every"] > 0).any()))
-        Ls = self.table["L"].astype(np.int64)
-        has = np.zeros(self.n, dtype=np.int64)
-        has[slice(None) if chains is None else chains] = 1
-        count = -(-(Ls ** 3 // 2) // TILE_SITES) * has
-        first = np.concatenate([[0], np.cumsum(count)])
+        self._any = (int(own["k_hits"].any()), int(own["n_or"].max(initial=0)),
+                     int(own["renorm_every"].any()))
+        sites = self.table["L"].astype(np.int64) ** 3
+        if chains is not None:
+            sites[np.setdiff1d(np.arange(self.n), chains)] = 0
+        first = np.zeros(self.n + 1, dtype=np.int64)
+        np.cumsum(-(-sites // (2 * TILE_SITES)), out=first[1:])
         # groups of about the same number of bytes, the last chain of one where its share ends
-        end = np.cumsum(Ls ** 3 * has) * 3 * self.spins.element_size()
+        end = np.cumsum(sites) * (3 * self.spins.element_size())
         n_groups = -(-int(end[-1]) // GROUP_SPIN_BYTES)
-        last = np.searchsorted(end, end[-1] * np.arange(1, n_groups) / n_groups)
-        groups = np.unique(np.concatenate([[0], first[last + 1], first[-1:]])).astype(np.int32)
+        groups = first[[0, -1]].astype(np.int32)
+        if n_groups > 1:
+            last = np.searchsorted(end, end[-1] * np.arange(1, n_groups) / n_groups)
+            groups = np.unique(np.concatenate([groups, first[last + 1]])).astype(np.int32)
         n, dev = int(first[-1]), self.device
         first = torch.from_numpy(first.astype(np.int32)).to(dev)
         tiles = torch.empty(n, 2, dtype=torch.int32, device=dev)
         partials = torch.empty(n, dtype=torch.float64, device=dev)
         check(lib().hsg_batch_tile_table(_ptr(first), self.n, TILE_SITES, _ptr(tiles),
                                          _ptr(partials), _stream(None)))
-        torch.cuda.current_stream().synchronize()  # sweeps may run on another stream
         return tiles, first, n, partials, groups
 
     def _over_tiles(self, n_sweeps: int) -> bool:
