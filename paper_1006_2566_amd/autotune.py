@@ -130,20 +130,23 @@ def sweep_flags(L: int, dtype: torch.dtype = torch.float32, k: int = 4, n_or: in
 
 def batch_threads(batch, n_sweeps: int = 1, retune: bool = False,
                   path: str | None = None) -> int:
-    """Workgroup size of hsg_batch_sweep for this batch (chain sizes, k, n_or).  Of a batch
-    that runs over tiles at the default size, the others are timed with a workgroup per
-    chain."""
+    """Workgroup size of hsg_batch_sweep for this batch (chain sizes, k, n_or).  A batch that
+    runs over tiles keeps the default, with which it does: which form pays is the batch's own
+    rule, and calls of one sweep, as timed here, are not what groups of chains are for."""
     from collections import Counter
+
+    from .batch import THREADS
     hist = sorted(Counter((int(c.L), int(c.k), int(c.n_or)) for c in batch.specs).items())
-    tiles = " tiles" if batch._tiles is not None else ""
-    key = f"batch {str(batch.dtype).replace('torch.', '')} {hist}{tiles}"
+    tiles = batch._tiles is not None
+    key = f"batch {str(batch.dtype).replace('torch.', '')} {hist}{' tiles' if tiles else ''}"
     saved = (batch.threads, batch.sweep_ctr.clone(), batch.E.clone(), batch.spins.clone(),
              batch.remaining.clone() if batch.remaining is not None else None)
 
     def measure(threads):
         batch.threads = threads
         return _event_ms(lambda: batch.sweep(n_sweeps), 2)
-    best = int(pick(key, [64, 128, 256, 512, 1024], measure, retune=retune, path=path))
+    sizes = [THREADS] if tiles else [64, 128, 256, 512, 1024]
+    best = int(pick(key, sizes, measure, retune=retune, path=path))
     # the timing sweeps advanced the chains: put the batch back as it was
     batch.threads = best
     batch.sweep_ctr.copy_(saved[1])

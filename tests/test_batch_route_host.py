@@ -79,3 +79,15 @@ def test_budgets_of_a_batch_in_groups(rec, monkeypatch):
     assert b._tiles[4].size - 1 == 4
     assert route(rec, b, 6) == ["sweep", "group_sweep"]  # the small chains, then the others
     assert route(rec, b, 7) == ["sweep"]
+
+
+def test_tuned_size_keeps_the_tiles(rec, monkeypatch, tmp_path):
+    from paper_1006_2566_amd import autotune
+    monkeypatch.setattr(autotune, "device_key", lambda: "cpu")
+    monkeypatch.setattr(autotune, "_event_ms", lambda fn, reps: fn() or 1.0)
+    path = str(tmp_path / "tune.json")
+    tiled, alone = batch(chains(32, 4)), batch(chains(8, 4))
+    assert autotune.batch_threads(tiled, path=path) == hb.THREADS
+    assert route(rec, tiled) == ["group_sweep"]
+    assert autotune.batch_threads(alone, path=path) == 64  # the first of equals
+    assert route(rec, alone) == ["sweep"]
